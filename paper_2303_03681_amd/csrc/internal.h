@@ -65,6 +65,42 @@ struct TruncItem {        // Eq. (Bl): out (2Dl x k) = C (2Dl x 2Dr) * conj(V)^T
   int rows, dr, k;        // rows = 2Dl; k is the upper bound when k_dev is set
 };
 
+// ---------------------------------------------------------------- LQ preconditioning
+struct LqItem {           // block modified Gram-Schmidt on the rows of w (n x m)
+  double2* w;             // rows, replaced by the orthonormal rows
+  const int* order;       // processing order of the rows (null: as stored)
+  int* order_out;         // launch_lq_order: that order
+  double2* r;             // factor as L^+, row s (of n entries) for step s; may be null
+  double2* out;           // the rows once more as [s][row][r] (m split in halves); may be null
+  double* norm2;          // squared row norms (launch_row_norm, launch_lq_order)
+  const int* k_dev;       // if not null, the number of rows is min(n, *k_dev)
+  int n, m;
+};
+
+struct LqFinItem {        // singular values from the squared row norms, truncation
+  const double* norm2;
+  double* lam_out;        // normalised singular values (k)
+  int* perm_out;          // row of the a-th largest (k)
+  double* inv_out;        // 1 / sigma_a (k)
+  int* k_out;
+  double* scale_out;
+  double* disc_out;
+  int* status_out;
+  int n, cap;
+  double cutoff;
+};
+
+struct LqVecItem {        // V^+ (k x m) = diag(inv) Z[perm] Q[order]
+  const double2* z;       // converged rows (n1 x n1)
+  const int* perm;
+  const double* inv;
+  const double2* q;       // orthonormal rows (n1 of them in processing order) x m
+  const int* order;
+  double2* v;
+  const int* k_dev;
+  int k, m, n1;           // k: the upper bound of *k_dev
+};
+
 // ---------------------------------------------------------------- canonical form
 struct CanonLeftItem {    // W[beta][(s,alpha)] = sum_g B[s][g][beta] T[alpha][g]
   const double2* b;       // site [s][g][beta], (2, Dg, Db)
@@ -177,6 +213,13 @@ hipError_t launch_jacobi_reg(const JacItem* items_dev, int items, int max_pairs,
 hipError_t launch_jacobi_single(const JacItem* items_dev, int items, int max_sweeps,
                                 double eps_scale, size_t lds_bytes, hipStream_t s);
 hipError_t launch_finalize(const FinItem* items_dev, int items, hipStream_t s);
+hipError_t launch_row_norm(const LqItem* items_dev, int items, int max_rows, hipStream_t s);
+hipError_t launch_lq_order(const LqItem* items_dev, int items, hipStream_t s);
+constexpr int kLqMax = 1024;  // longest side of a matrix the LQ kernels take
+hipError_t launch_lq(const LqItem* items_dev, int items, int max_rows, int max_len, int max_steps,
+                     hipStream_t s);
+hipError_t launch_lq_rank(const LqFinItem* items_dev, int items, hipStream_t s);
+hipError_t launch_lq_vec(const LqVecItem* items_dev, int items, int max_k, int max_len, hipStream_t s);
 hipError_t launch_trunc(const TruncItem* items_dev, int items, int max_rows, int max_k,
                         hipStream_t s);
 hipError_t launch_canon_left(const CanonLeftItem* items_dev, int items, int max_db, int max_r,

@@ -285,11 +285,6 @@ struct RegVec {
   double2 v[E];
 };
 
-// Row pointers of the Jacobi work matrices are global memory: typed so, the
-// loads and stores are global (not flat) instructions with immediate offsets.
-typedef double __attribute__((ext_vector_type(2))) dvec2;
-typedef __attribute__((address_space(1))) dvec2 gdvec2;
-
 // Every lane loads (unconditionally, from inside the row: indices past the
 // row end are clamped to its last element; src is always a row of the
 // matrix) and zeroes what lies outside the row or belongs to a padding row,

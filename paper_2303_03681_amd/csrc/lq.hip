@@ -1,0 +1,417 @@
+// LQ preconditioning of the batched gate SVDs (Eq. svd with Algorithm 1).
+//
+// Algorithm 1 applied to the rows of C~ directly needs up to 23 sweeps on the
+// central bonds of a saturated state: the rows carry the graded lambda of
+// Eq. (C~), and the few smallest directions keep relative inner products near
+// one for ten sweeps after the others have converged.  Two LQ factorisations
+// (rows sorted by norm) move the grading to where the rotations see a nearly
+// diagonal matrix:
+//
+//   P C~ = L1 Q1,   L1^+ = L2 Q2,   Algorithm 1 on the rows of L2^+ :
+//   J L2^+ = Sigma Z,  and  V^+ = Z Q1.
+//
+// (The rows of L2^+ have the Gram matrix of the columns of L2; X = Z^+ are the
+// left singular vectors of L1^+, that is the right ones of L1.)  Sweeps until
+// no rotation, measured on captured 512 x 512 C~ of a 30-qubit D = 256
+// brickwork state: 21-23 without, 12-13 after one, 9-10 after two
+// factorisations; 128 x 128 of a UCCSD chain: 18-31 without, 6-8 after two.
+//
+// The factorisations are modified Gram-Schmidt over blocks of rows (the
+// factor L of MGS is as accurate as Householder's): lq_panel_kernel
+// orthonormalises one block of every matrix, lq_update_kernel takes the
+// block's components out of all later rows.  The rows of Z Q1 are orthonormal
+// to eps sigma_1 / sigma_p only (the loss of MGS in Q1), so they go through
+// the same two kernels once more in descending order of sigma, which leaves
+// the leading directions untouched.
+//
+// What bounds it: the panel is a serial chain of LQB steps (norm, broadcast
+// through LDS, dot products, update) on one workgroup per matrix; the update
+// is FP64 vector work on all compute units, its rows read and written once
+// per block.
+#include <hip/hip_runtime.h>
+
+#include <cmath>
+#include <cstdint>
+
+#include "gemm_core.h"
+#include "internal.h"
+#include "wave_ops.h"
+
+namespace mps {
+
+namespace {
+
+inline int cdiv(long long a, long long b) { return (int)((a + b - 1) / b); }
+
+// Row i of the matrix (in processing order).
+__device__ __forceinline__ double2* lq_row(const LqItem& it, int i) {
+  return it.w + (size_t)(it.order ? it.order[i] : i) * it.m;
+}
+
+__device__ __forceinline__ int lq_rows(const LqItem& it) {
+  return it.k_dev ? min(it.n, *it.k_dev) : it.n;
+}
+
+// One row, lane + 64 k to element k: every lane loads from inside the row (the
+// index clamped to its end) and zeroes what lies outside it.
+template <int E>
+__device__ __forceinline__ void load_row(double2 (&x)[E], const double2* src, bool valid, int m, int lane) {
+  const gdvec2* g = (const gdvec2*)src;
+#pragma unroll
+  for (int k = 0; k < E; ++k) {
+    const int e = lane + 64 * k;
+    const dvec2 v = g[e < m ? e : m - 1];
+    const bool keep = valid && e < m;
+    x[k] = make_double2(keep ? v.x : 0.0, keep ? v.y : 0.0);
+  }
+}
+
+}  // namespace
+
+// Squared norms of the rows of every matrix, one wave per row.
+__global__ __launch_bounds__(256) void row_norm_kernel(const LqItem* items, int per_item) {
+  const int item = blockIdx.x / per_item;
+  const LqItem it = items[item];
+  const int row = (blockIdx.x - item * per_item) * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  if (row >= it.n) return;
+  const double2* w = it.w + (size_t)row * it.m;
+  double s = 0.0;
+  for (int e = lane; e < it.m; e += 64) s += w[e].x * w[e].x + w[e].y * w[e].y;
+  s = wave_sum(s);
+  if (lane == 0) it.norm2[row] = s;
+}
+
+hipError_t launch_row_norm(const LqItem* items_dev, int items, int max_rows, hipStream_t s) {
+  if (items <= 0 || max_rows <= 0) return hipSuccess;
+  const int per = cdiv(max_rows, 4);
+  hipLaunchKernelGGL(row_norm_kernel, dim3(items * per), dim3(256), 0, s, items_dev, per);
+  return hipGetLastError();
+}
+
+// Row order by descending norm (ties by index), one workgroup per matrix.
+__global__ __launch_bounds__(1024) void lq_order_kernel(const LqItem* items) {
+  __shared__ double key[1024];
+  const LqItem it = items[blockIdx.x];
+  const int i = threadIdx.x, n = it.n;
+  if (i < n) {
+    // a NaN sorts first, so that every position is written
+    const double v = it.norm2[i];
+    key[i] = v == v ? v : INFINITY;
+  }
+  __syncthreads();
+  if (i >= n) return;
+  const double mine = key[i];
+  int r = 0;
+  for (int j = 0; j < n; ++j) r += (key[j] > mine) || (key[j] == mine && j < i);
+  it.order_out[r] = i;
+}
+
+hipError_t launch_lq_order(const LqItem* items_dev, int items, hipStream_t s) {
+  if (items <= 0) return hipSuccess;
+  hipLaunchKernelGGL(lq_order_kernel, dim3(items), dim3(1024), 0, s, items_dev);
+  return hipGetLastError();
+}
+
+// Modified Gram-Schmidt inside block `panel` (LQB rows) of every matrix: one
+// workgroup of NW waves per matrix, row u of the block in registers of wave
+// u % NW.  At step t the owner normalises row t and hands it on through one
+// of two LDS buffers (one barrier per step: a buffer is rewritten two steps
+// later, after every wave has passed the next barrier).  Row s of the factor
+// gets its diagonal and in-block entries, and zeros before the diagonal.
+template <int E, int NW, int RPW>
+__global__ __launch_bounds__(NW * 64) void lq_panel_kernel(const LqItem* items, int panel) {
+  constexpr int LQB = NW * RPW;
+  __shared__ double2 q_lds[2][64 * E];
+  const LqItem it = items[blockIdx.x];
+  const int n = lq_rows(it), m = it.m, steps = min(n, m);
+  const int s0 = panel * LQB;
+  if (s0 >= steps) return;
+  const int nb = min(LQB, steps - s0);
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double2 x[RPW][E];
+#pragma unroll
+  for (int a = 0; a < RPW; ++a) {
+    const int u = a * NW + wv;
+    load_row<E>(x[a], lq_row(it, s0 + min(u, nb - 1)), u < nb, m, lane);
+  }
+  for (int t = 0; t < nb; ++t) {
+    double2* buf = q_lds[t & 1];
+    if (wv == t % NW) {
+#pragma unroll
+      for (int a = 0; a < RPW; ++a) {
+        if (a != t / NW) continue;
+        double nn = 0.0;
+#pragma unroll
+        for (int k = 0; k < E; ++k) nn += x[a][k].x * x[a][k].x + x[a][k].y * x[a][k].y;
+        nn = wave_sum(nn);
+        const double r = sqrt(nn), inv = r > 0.0 ? 1.0 / r : (r == 0.0 ? 0.0 : r);
+#pragma unroll
+        for (int k = 0; k < E; ++k) buf[lane + 64 * k] = make_double2(x[a][k].x * inv, x[a][k].y * inv);
+        if (it.r && lane == 0) it.r[(size_t)(s0 + t) * it.n + s0 + t] = make_double2(r, 0.0);
+      }
+    }
+    __syncthreads();
+    // the finished row (and the factor's zeros before the diagonal), by all threads
+    {
+      gdvec2* dst = (gdvec2*)lq_row(it, s0 + t);
+      const int half = m / 2;
+      for (int e = threadIdx.x; e < m; e += NW * 64) {
+        const double2 q = buf[e];
+        dst[e] = dvec2{q.x, q.y};
+        if (it.out) {  // [s][row][r], the layout of a right site tensor
+          const int sb = e >= half ? 1 : 0;
+          it.out[((size_t)sb * n + s0 + t) * half + e - sb * half] = q;
+        }
+      }
+      if (it.r)
+        for (int i = threadIdx.x; i < s0 + t; i += NW * 64)
+          it.r[(size_t)(s0 + t) * it.n + i] = make_double2(0.0, 0.0);
+    }
+    if (wv + (RPW - 1) * NW <= t) continue;  // no later row on this wave
+    double2 q[E];
+#pragma unroll
+    for (int k = 0; k < E; ++k) q[k] = buf[lane + 64 * k];
+    double c[2 * RPW];
+#pragma unroll
+    for (int b = 0; b < RPW; ++b) {
+      c[2 * b] = c[2 * b + 1] = 0.0;
+#pragma unroll
+      for (int k = 0; k < E; ++k) {
+        c[2 * b] += q[k].x * x[b][k].x + q[k].y * x[b][k].y;
+        c[2 * b + 1] += q[k].x * x[b][k].y - q[k].y * x[b][k].x;
+      }
+    }
+    wave_sum_scalar<2 * RPW>(c, lane);
+#pragma unroll
+    for (int b = 0; b < RPW; ++b) {
+      const int u = b * NW + wv;
+      if (u <= t || u >= nb) continue;  // done, or padding
+      const double cr = c[2 * b], ci = c[2 * b + 1];
+#pragma unroll
+      for (int k = 0; k < E; ++k) {
+        x[b][k].x -= cr * q[k].x - ci * q[k].y;
+        x[b][k].y -= cr * q[k].y + ci * q[k].x;
+      }
+      if (it.r && lane == 0) it.r[(size_t)(s0 + t) * it.n + s0 + u] = make_double2(cr, -ci);
+    }
+  }
+}
+
+// Takes the components along the rows of block `panel` out of every later row
+// (one after the other, so modified Gram-Schmidt across blocks too): four
+// waves of RPW rows each, the block's rows staged through LDS QC at a time.
+template <int E, int LQB, int RPW>
+__global__ __launch_bounds__(256, 2) void lq_update_kernel(const LqItem* items, int panel, int per_item) {
+  constexpr int QC = LQB < 64 / E ? LQB : 64 / E;  // 64 KB of rows at a time
+  __shared__ double2 q_lds[QC][64 * E];
+  const int item = blockIdx.x / per_item;
+  const LqItem it = items[item];
+  const int n = lq_rows(it), m = it.m, steps = min(n, m);
+  const int s0 = panel * LQB;
+  if (s0 >= steps) return;
+  const int nb = min(LQB, steps - s0);
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int first = s0 + nb + (blockIdx.x - item * per_item) * 4 * RPW;
+  if (first >= n) return;
+  const int i0 = first + wv * RPW;
+  double2 x[RPW][E];
+#pragma unroll
+  for (int a = 0; a < RPW; ++a) {
+    load_row<E>(x[a], lq_row(it, min(i0 + a, n - 1)), i0 + a < n, m, lane);
+  }
+  for (int t0 = 0; t0 < nb; t0 += QC) {
+    const int tc = min(QC, nb - t0);
+    __syncthreads();
+    for (int t = wv; t < tc; t += 4) {
+      double2 v[E];
+      load_row<E>(v, lq_row(it, s0 + t0 + t), true, m, lane);
+#pragma unroll
+      for (int k = 0; k < E; ++k) q_lds[t][lane + 64 * k] = v[k];
+    }
+    __syncthreads();
+    for (int t = 0; t < tc; ++t) {
+      double2 q[E];
+#pragma unroll
+      for (int k = 0; k < E; ++k) q[k] = q_lds[t][lane + 64 * k];
+      double c[2 * RPW];
+#pragma unroll
+      for (int a = 0; a < RPW; ++a) {
+        double re = 0.0, im = 0.0;
+#pragma unroll
+        for (int k = 0; k < E; ++k) {
+          re += q[k].x * x[a][k].x + q[k].y * x[a][k].y;
+          im += q[k].x * x[a][k].y - q[k].y * x[a][k].x;
+        }
+        c[2 * a] = re;
+        c[2 * a + 1] = im;
+      }
+      wave_sum_scalar<2 * RPW>(c, lane);
+#pragma unroll
+      for (int a = 0; a < RPW; ++a) {
+#pragma unroll
+        for (int k = 0; k < E; ++k) {
+          x[a][k].x -= c[2 * a] * q[k].x - c[2 * a + 1] * q[k].y;
+          x[a][k].y -= c[2 * a] * q[k].y + c[2 * a + 1] * q[k].x;
+        }
+        if (it.r && lane == a && i0 + a < n)
+          it.r[(size_t)(s0 + t0 + t) * it.n + i0 + a] = make_double2(c[2 * a], -c[2 * a + 1]);
+      }
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < RPW; ++a) {
+    if (i0 + a >= n) continue;
+    gdvec2* dst = (gdvec2*)lq_row(it, i0 + a);
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+      const int e = lane + 64 * k;
+      if (e < m) dst[e] = dvec2{x[a][k].x, x[a][k].y};
+    }
+  }
+}
+
+namespace {
+
+template <int E, int NW, int RPW, int URPW>
+hipError_t launch_lq_e(const LqItem* items_dev, int items, int max_rows, int max_steps, hipStream_t s) {
+  constexpr int LQB = NW * RPW;
+  for (int p = 0; p * LQB < max_steps; ++p) {
+    hipLaunchKernelGGL((lq_panel_kernel<E, NW, RPW>), dim3(items), dim3(NW * 64), 0, s, items_dev, p);
+    // rows after the block; a matrix with fewer steps than the longest has a
+    // shorter last block, hence more rows after it than max_rows - (p + 1) LQB
+    const int rest = max_rows - p * LQB - 1;
+    if (rest > 0) {
+      const int per = cdiv(rest, 4 * URPW);
+      hipLaunchKernelGGL((lq_update_kernel<E, LQB, URPW>), dim3(items * per), dim3(256), 0, s, items_dev, p,
+                         per);
+    }
+  }
+  return hipGetLastError();
+}
+
+}  // namespace
+
+// LQ factorisation of every matrix (max_rows x max_len the largest): rows
+// become Q in place (in processing order), the factor goes to r as L^+.
+// Blocks of 32 rows, 16 where a row takes 64 registers per lane.
+hipError_t launch_lq(const LqItem* items_dev, int items, int max_rows, int max_len, int max_steps,
+                     hipStream_t s) {
+  if (items <= 0 || max_rows <= 0 || max_len <= 0) return hipSuccess;
+  if (max_len <= 128) return launch_lq_e<2, 8, 2, 4>(items_dev, items, max_rows, max_steps, s);
+  if (max_len <= 256) return launch_lq_e<4, 8, 2, 4>(items_dev, items, max_rows, max_steps, s);
+  if (max_len <= 512) return launch_lq_e<8, 8, 2, 4>(items_dev, items, max_rows, max_steps, s);
+  if (max_len <= 1024) return launch_lq_e<16, 8, 2, 2>(items_dev, items, max_rows, max_steps, s);
+  return hipErrorInvalidValue;
+}
+
+// sigma_i = ||a_i|| from the squared norms, stable descending order,
+// k = min(cap, #{sigma > cutoff ||sigma||}) >= 1, lambda, scale and discarded
+// weight as finalize_kernel; perm and 1 / sigma for the rows of V^+.
+__global__ __launch_bounds__(1024) void lq_rank_kernel(const LqFinItem* items) {
+  __shared__ double sig[1024];
+  __shared__ int perm[1024];
+  __shared__ int s_k;
+  __shared__ double s_inv;
+  const LqFinItem it = items[blockIdx.x];
+  const int n = it.n, i = threadIdx.x;
+  if (i < n) {
+    sig[i] = sqrt(it.norm2[i]);
+    perm[i] = i;
+  }
+  __syncthreads();
+  if (i < n) {
+    const double si = sig[i];
+    int r = 0;
+    for (int j = 0; j < n; ++j) {
+      const double sj = sig[j];
+      r += (sj > si) || (sj == si && j < i);
+    }
+    perm[r] = i;
+  }
+  __syncthreads();
+  if (i == 0) {
+    double tot = 0.0;
+    bool bad = false;
+    for (int a = 0; a < n; ++a) {
+      const double sv = sig[perm[a]];
+      if (!isfinite(sv)) bad = true;
+      tot += sv * sv;
+    }
+    const double nrm = sqrt(tot);
+    int k = 0;
+    while (k < n && sig[perm[k]] > it.cutoff * nrm) ++k;
+    if (k < 1) k = 1;
+    if (k > it.cap) k = it.cap;
+    double kept2 = 0.0, disc2 = 0.0;
+    for (int a = 0; a < n; ++a) {
+      const double sv = sig[perm[a]];
+      if (a < k) kept2 += sv * sv;
+      else disc2 += sv * sv;
+    }
+    const double kept = sqrt(kept2);
+    bad = bad || !isfinite(tot) || !(kept > 0.0) || !isfinite(kept);
+    *it.status_out = bad ? 1 : 0;
+    s_inv = bad ? 0.0 : 1.0 / kept;
+    *it.k_out = k;
+    *it.scale_out = s_inv;
+    *it.disc_out = tot > 0.0 ? disc2 / tot : 0.0;
+    s_k = k;
+  }
+  __syncthreads();
+  if (i < s_k) {
+    const double sv = sig[perm[i]];
+    it.lam_out[i] = sv * s_inv;
+    it.perm_out[i] = perm[i];
+    it.inv_out[i] = sv > 0.0 ? 1.0 / sv : 0.0;
+  }
+}
+
+hipError_t launch_lq_rank(const LqFinItem* items_dev, int items, hipStream_t s) {
+  if (items <= 0) return hipSuccess;
+  hipLaunchKernelGGL(lq_rank_kernel, dim3(items), dim3(1024), 0, s, items_dev);
+  return hipGetLastError();
+}
+
+// V^+ (k x m) = Z Q1: row a of Z is the converged row perm[a] over its norm,
+// row s of Q1 the s-th processed row of the first factorisation.
+struct LqVecP {
+  using T = double;
+  using Ctx = LqVecItem;
+  static constexpr bool A_CONTIG_K = true, B_CONTIG_N = true, REAL_ONLY = false;
+  const LqVecItem* items;
+  __device__ Ctx context(int i) const {
+    LqVecItem t = items[i];
+    t.k = min(t.k, *t.k_dev);
+    return t;
+  }
+  __device__ static void dims(const Ctx& c, int& M, int& N, int& K) {
+    M = c.k;
+    N = c.m;
+    K = c.n1;
+  }
+  struct RowA {
+    const double2* z;
+    double inv;
+  };
+  using ColB = const double2*;
+  __device__ static RowA rowA(const Ctx& c, int i) {
+    return RowA{c.z + (size_t)c.perm[i] * c.n1, c.inv[i]};
+  }
+  __device__ static ColB colB(const Ctx& c, int j) { return c.q + j; }
+  __device__ static double2 loadA(const Ctx&, RowA r, int, int k) {
+    const double2 v = r.z[k];
+    return make_double2(v.x * r.inv, v.y * r.inv);
+  }
+  __device__ static double2 loadB(const Ctx& c, ColB b, int k, int) { return b[(size_t)c.order[k] * c.m]; }
+  __device__ static void store(const Ctx& c, int i, int j, double re, double im) {
+    c.v[(size_t)i * c.m + j] = make_double2(re, im);
+  }
+};
+
+hipError_t launch_lq_vec(const LqVecItem* items_dev, int items, int max_k, int max_len, hipStream_t s) {
+  LqVecP p{items_dev};
+  return launch_cgemm<64, 64, 16>(p, items, max_k, max_len, s);
+}
+
+}  // namespace mps

@@ -40,6 +40,7 @@ constexpr int kMaxStatevectorQubits = 26;
 constexpr double kEpsScale = 1.1102230246251565e-16;  // 2^-53: eps = m * 2^-53 (Algorithm 1)
 constexpr double kCanonCutoff = 1e-14;                  // round-off singular values only
 constexpr int kDefaultSweeps = 60;
+constexpr int kPreMin = 24;  // batched SVDs of at least this on both sides are LQ-preconditioned
 constexpr int kMaxBond = 512;                           // finalize handles 2D <= 1024 vectors
 constexpr int kMaxJacobiGroups = 3;      // streams of the batched register Jacobi rounds
 constexpr int kDefaultJacobiGroups = 2;
@@ -174,6 +175,16 @@ struct mps_state {
   size_t ws_stride = 0;  // complex elements per item
   double2* ws_c = nullptr;
   double2* ws_w = nullptr;
+  // LQ preconditioning of the batched SVDs: the two factors of each gate (the
+  // first one's space then takes V^+).  Optional: given back when the budget
+  // or the device has no room for something else.
+  int pre_items = 0;
+  bool pre_busy = false;
+  double2* ws_l1 = nullptr;
+  double2* ws_l2 = nullptr;
+  int lq_items = 0;          // per-item row norms, orders and 1 / sigma
+  double* d_lqval = nullptr; // [item][2][kLqMax]: squared norms, 1 / sigma
+  int* d_lqidx = nullptr;    // [item][2][kLqMax]: row order, singular value order
   double* d_fro2 = nullptr;
   int* d_rot = nullptr;
   int* d_sweeps = nullptr;
@@ -240,13 +251,20 @@ mps_status dev_fail(mps_state* h, const char* what, hipError_t e) {
     if (e_ != hipSuccess) return dev_fail((h), #expr, e_); \
   } while (0)
 
+bool drop_pre(mps_state* h);
+
 mps_status dalloc(mps_state* h, void** p, size_t bytes) {
   *p = nullptr;
   if (bytes == 0) bytes = 256;
+  if (h->budget && h->held + bytes > h->budget) drop_pre(h);
   if (h->budget && h->held + bytes > h->budget)
     return fail(MPS_ERR_BUDGET, "HBM budget exceeded: need " + std::to_string(h->held + bytes) +
                                     " bytes, budget " + std::to_string(h->budget));
   hipError_t e = hipMalloc(p, bytes);
+  if (e != hipSuccess && drop_pre(h)) {
+    (void)hipGetLastError();
+    e = hipMalloc(p, bytes);
+  }
   if (e != hipSuccess) {
     (void)hipGetLastError();
     *p = nullptr;
@@ -266,6 +284,19 @@ void dfree(mps_state* h, void* p) {
       (void)hipFree(p);
       return;
     }
+}
+
+// Gives the preconditioning workspace back; false if there is none (or a
+// batch is using it).
+bool drop_pre(mps_state* h) {
+  if (h->pre_busy || (!h->ws_l1 && !h->ws_l2 && !h->d_lqval && !h->d_lqidx)) return false;
+  (void)hipStreamSynchronize(h->stream);
+  for (void* p : {(void*)h->ws_l1, (void*)h->ws_l2, (void*)h->d_lqval, (void*)h->d_lqidx}) dfree(h, p);
+  h->ws_l1 = h->ws_l2 = nullptr;
+  h->d_lqval = nullptr;
+  h->d_lqidx = nullptr;
+  h->pre_items = h->lq_items = 0;
+  return true;
 }
 
 template <typename T>
@@ -392,6 +423,45 @@ mps_status ensure_ws(mps_state* h, int items) {
   }
   h->ws_items = items;
   return MPS_OK;
+}
+
+// Preconditioning workspace of h for `items` gates (the factors), and of the
+// driver (per-item vectors); false, without any, when there is no room.  The
+// caller has marked it busy, so that an allocation does not give it back.
+bool ensure_pre(mps_state* h, int items) {
+  if (items <= h->pre_items) return true;
+  if (sync(h) != MPS_OK) return false;
+  dfree(h, h->ws_l1);
+  dfree(h, h->ws_l2);
+  h->ws_l1 = h->ws_l2 = nullptr;
+  h->pre_items = 0;
+  if (dalloc_t(h, &h->ws_l1, h->ws_stride * items) != MPS_OK ||
+      dalloc_t(h, &h->ws_l2, h->ws_stride * items) != MPS_OK) {
+    dfree(h, h->ws_l1);
+    h->ws_l1 = h->ws_l2 = nullptr;
+    return false;
+  }
+  h->pre_items = items;
+  return true;
+}
+
+bool ensure_lq_vectors(mps_state* drv, int items) {
+  if (items <= drv->lq_items) return true;
+  if (sync(drv) != MPS_OK) return false;
+  dfree(drv, drv->d_lqval);
+  dfree(drv, drv->d_lqidx);
+  drv->d_lqval = nullptr;
+  drv->d_lqidx = nullptr;
+  drv->lq_items = 0;
+  if (dalloc_t(drv, &drv->d_lqval, (size_t)2 * kLqMax * items) != MPS_OK ||
+      dalloc_t(drv, &drv->d_lqidx, (size_t)2 * kLqMax * items) != MPS_OK) {
+    dfree(drv, drv->d_lqval);
+    drv->d_lqval = nullptr;
+    drv->d_lqidx = nullptr;
+    return false;
+  }
+  drv->lq_items = items;
+  return true;
 }
 
 // ----------------------------------------------------------------------------
@@ -735,12 +805,62 @@ mps_status apply_2q_refs(mps_state* drv, const std::vector<GateRef>& g, bool all
       if (g[c].h == g[b].h) ++slot[b];
     if ((st = ensure_ws(g[b].h, slot[b] + 1)) != MPS_OK) return st;
   }
+  // Gates whose SVD is preconditioned: matrices above kPreMin on both sides
+  // (below, one workgroup runs all sweeps), on handles with the default sweep
+  // limit or more (a lowered limit counts the sweeps of the direct iteration).
+  std::vector<char> pre(items, 0);
+  int n_pre = 0;
+  for (int b = 0; b < items; ++b) {
+    const mps_state* h = g[b].h;
+    const int n = 2 * h->dims[g[b].q], m = 2 * h->dims[g[b].q + 2];
+    pre[b] = h->max_sweeps >= kDefaultSweeps && std::min(n, m) >= kPreMin && n * m > 64 * 64 &&
+             std::max(n, m) <= kLqMax;
+    n_pre += pre[b];
+  }
+  struct PreBusy {  // the workspace stays while this batch uses it
+    std::vector<mps_state*> hs;
+    void take(mps_state* h) {
+      h->pre_busy = true;
+      hs.push_back(h);
+    }
+    void release() {
+      for (mps_state* h : hs) h->pre_busy = false;
+      hs.clear();
+    }
+    ~PreBusy() { release(); }
+  } busy;
+  // descriptors of the launches: 256-byte aligned blocks
+  const size_t desc_direct = (sizeof(ThetaItem) + sizeof(MixItem) + sizeof(FinItem) + sizeof(TruncItem) +
+                              3 * sizeof(JacItem)) * items + 8 * 256;
+  const size_t desc_pre = desc_direct + (4 * sizeof(LqItem) + sizeof(LqFinItem) + sizeof(LqVecItem)) * items +
+                          8 * 256;
+  if (n_pre > 0) {
+    busy.take(drv);
+    bool room = ensure_desc(drv, desc_pre) == MPS_OK && ensure_lq_vectors(drv, items);
+    for (int b = 0; b < items && room; ++b) {
+      if (!pre[b]) continue;
+      if (!g[b].h->pre_busy) busy.take(g[b].h);
+      room = ensure_pre(g[b].h, slot[b] + 1);
+    }
+    if (!room) {  // the direct iteration needs none of it
+      const std::vector<mps_state*> hs = busy.hs;
+      busy.release();
+      for (mps_state* h : hs) drop_pre(h);
+      std::fill(pre.begin(), pre.end(), 0);
+      n_pre = 0;
+    }
+  }
+  if ((st = ensure_desc(drv, n_pre > 0 ? desc_pre : desc_direct)) != MPS_OK) return st;
   std::vector<ThetaItem> th(items);
   std::vector<MixItem> mx(items);
   std::vector<JacItem> jc(items);
-  std::vector<FinItem> fn(items);
+  std::vector<FinItem> fn;
   std::vector<TruncItem> tr(items);
+  std::vector<LqItem> l1, l2, l3, l4;  // the two factorisations, final norms, V^+
+  std::vector<LqFinItem> lf;
+  std::vector<LqVecItem> lv;
   int max_rows = 0, max_cols = 0, max_dldr = 0, max_k = 0;
+  int pre_n = 0, pre_m = 0, pre_n1 = 0, pre_k = 0;
   for (int b = 0; b < items; ++b) {
     mps_state* h = g[b].h;
     const int q = g[b].q;
@@ -753,8 +873,31 @@ mps_status apply_2q_refs(mps_state* drv, const std::vector<GateRef>& g, bool all
     th[b] = ThetaItem{h->cur(q), h->cur(q + 1), c, dl, dm, dr};
     mx[b] = MixItem{c, w, h->lcur(q), g[b].u, drv->d_fro2 + b, dl, dr};
     jc[b] = JacItem{w, drv->d_fro2 + b, drv->d_rot + b, drv->d_sweeps + b, 2 * dl, 2 * dr, 0, 0, items};
-    fn[b] = FinItem{w, h->spare(q + 1), h->lspare(q + 1), drv->d_k + b, drv->d_scale + b,
-                    drv->d_disc + b, drv->d_status + b, 2 * dl, 2 * dr, capk, h->cutoff, FIN_GATE};
+    if (!pre[b]) {
+      fn.push_back(FinItem{w, h->spare(q + 1), h->lspare(q + 1), drv->d_k + b, drv->d_scale + b,
+                           drv->d_disc + b, drv->d_status + b, 2 * dl, 2 * dr, capk, h->cutoff, FIN_GATE});
+    } else {
+      const int n = 2 * dl, m = 2 * dr, n1 = std::min(n, m);
+      double2* f1 = h->ws_l1 + (size_t)slot[b] * h->ws_stride;
+      double2* f2 = h->ws_l2 + (size_t)slot[b] * h->ws_stride;
+      double* norm2 = drv->d_lqval + (size_t)b * 2 * kLqMax;
+      double* inv = norm2 + kLqMax;
+      int* order = drv->d_lqidx + (size_t)b * 2 * kLqMax;
+      int* perm = order + kLqMax;
+      l1.push_back(LqItem{w, order, order, f1, nullptr, norm2, nullptr, n, m});
+      l2.push_back(LqItem{f1, nullptr, nullptr, f2, nullptr, nullptr, nullptr, n1, n});
+      jc[b].w = f2;
+      jc[b].n = jc[b].m = n1;
+      l3.push_back(LqItem{f2, nullptr, nullptr, nullptr, nullptr, norm2, nullptr, n1, n1});
+      lf.push_back(LqFinItem{norm2, h->lspare(q + 1), perm, inv, drv->d_k + b, drv->d_scale + b,
+                             drv->d_disc + b, drv->d_status + b, n1, capk, h->cutoff});
+      lv.push_back(LqVecItem{f2, perm, inv, w, order, f1, drv->d_k + b, capk, m, n1});
+      l4.push_back(LqItem{f1, nullptr, nullptr, nullptr, h->spare(q + 1), nullptr, drv->d_k + b, capk, m});
+      pre_n = std::max(pre_n, n);
+      pre_m = std::max(pre_m, m);
+      pre_n1 = std::max(pre_n1, n1);
+      pre_k = std::max(pre_k, capk);
+    }
     // Eq. (Bl) with k read on the device: it is enqueued before the host
     // learns k; the result stays in the spare buffers until committed.
     tr[b] = TruncItem{c, h->spare(q + 1), h->spare(q), drv->d_scale + b, drv->d_k + b, 2 * dl, dr, capk};
@@ -768,24 +911,42 @@ mps_status apply_2q_refs(mps_state* drv, const std::vector<GateRef>& g, bool all
   auto place = [&](const void* src, size_t bytes) {
     const size_t o = blob.size();
     blob.resize(o + ((bytes + 255) & ~(size_t)255));
-    std::memcpy(blob.data() + o, src, bytes);
+    if (bytes) std::memcpy(blob.data() + o, src, bytes);
     return o;
   };
   const size_t o_th = place(th.data(), sizeof(ThetaItem) * items);
   const size_t o_mx = place(mx.data(), sizeof(MixItem) * items);
-  const size_t o_fn = place(fn.data(), sizeof(FinItem) * items);
+  const size_t o_fn = place(fn.data(), sizeof(FinItem) * fn.size());
+  const size_t o_l1 = place(l1.data(), sizeof(LqItem) * n_pre);
+  const size_t o_l2 = place(l2.data(), sizeof(LqItem) * n_pre);
+  const size_t o_l3 = place(l3.data(), sizeof(LqItem) * n_pre);
+  const size_t o_l4 = place(l4.data(), sizeof(LqItem) * n_pre);
+  const size_t o_lf = place(lf.data(), sizeof(LqFinItem) * n_pre);
+  const size_t o_lv = place(lv.data(), sizeof(LqVecItem) * n_pre);
   const size_t o_tr = place(tr.data(), sizeof(TruncItem) * items);
   const size_t o_jac = blob.size();
-  if ((st = ensure_desc(drv, o_jac + 3 * sizeof(JacItem) * items + 512)) != MPS_OK) return st;
+  if (o_jac + sizeof(JacItem) * items > drv->desc_bytes) return fail(MPS_ERR_STATE, "internal: descriptors");
   char* d = (char*)drv->d_desc;
   if ((st = upload(drv, d, blob.data(), blob.size())) != MPS_OK) return st;
   HIP_TRY(drv, hipMemsetAsync(drv->d_fro2, 0, sizeof(double) * items, drv->stream));
   HIP_TRY(drv, hipMemsetAsync(drv->d_rot, 0, sizeof(int) * items * drv->max_sweeps, drv->stream));
   HIP_TRY(drv, launch_theta((const ThetaItem*)(d + o_th), items, max_rows, max_cols, drv->stream));
   HIP_TRY(drv, launch_mix((const MixItem*)(d + o_mx), items, max_dldr, drv->stream));
+  if (n_pre > 0) {
+    HIP_TRY(drv, launch_row_norm((const LqItem*)(d + o_l1), n_pre, pre_n, drv->stream));
+    HIP_TRY(drv, launch_lq_order((const LqItem*)(d + o_l1), n_pre, drv->stream));
+    HIP_TRY(drv, launch_lq((const LqItem*)(d + o_l1), n_pre, pre_n, pre_m, pre_n1, drv->stream));
+    HIP_TRY(drv, launch_lq((const LqItem*)(d + o_l2), n_pre, pre_n1, pre_n, pre_n1, drv->stream));
+  }
   std::vector<int> sweeps;
   if ((st = run_jacobi(drv, jc, o_jac, sweeps)) != MPS_OK) return st;
-  HIP_TRY(drv, launch_finalize((const FinItem*)(d + o_fn), items, drv->stream));
+  HIP_TRY(drv, launch_finalize((const FinItem*)(d + o_fn), (int)fn.size(), drv->stream));
+  if (n_pre > 0) {
+    HIP_TRY(drv, launch_row_norm((const LqItem*)(d + o_l3), n_pre, pre_n1, drv->stream));
+    HIP_TRY(drv, launch_lq_rank((const LqFinItem*)(d + o_lf), n_pre, drv->stream));
+    HIP_TRY(drv, launch_lq_vec((const LqVecItem*)(d + o_lv), n_pre, pre_k, pre_m, drv->stream));
+    HIP_TRY(drv, launch_lq((const LqItem*)(d + o_l4), n_pre, pre_k, pre_m, pre_k, drv->stream));
+  }
   HIP_TRY(drv, launch_trunc((const TruncItem*)(d + o_tr), items, max_rows, max_k, drv->stream));
   std::vector<int> k(items), status(items);
   std::vector<double> disc(items);

@@ -5,6 +5,11 @@
 
 namespace mps {
 
+// Row pointers of the work matrices are global memory: typed so, the loads
+// and stores are global (not flat) instructions with immediate offsets.
+typedef double __attribute__((ext_vector_type(2))) dvec2;
+typedef __attribute__((address_space(1))) dvec2 gdvec2;
+
 // Lane permutation within rows of 16 lanes (DPP control CTRL) of a double.
 template <int CTRL>
 __device__ __forceinline__ double dpp_mov(double x) {
@@ -49,6 +54,37 @@ __device__ __forceinline__ void wave_sum_n(double (&v)[N]) {
   for (int i = 0; i < N; ++i) v[i] += __shfl_xor(v[i], 16, 64);
 #pragma unroll
   for (int i = 0; i < N; ++i) v[i] += __shfl_xor(v[i], 32, 64);
+}
+
+// Sums of N = 4 or 8 values over the wave, handed back in scalar registers:
+// reduce-scattered over lane bits 3, 2 (and 1 for N = 8), so that every lane
+// carries one sum through the remaining steps, then read from the lane that
+// holds it.  About half the instructions of wave_sum_n for these N.
+template <int N>
+__device__ __forceinline__ void wave_sum_scalar(double (&v)[N], int lane) {
+  static_assert(N == 4 || N == 8, "N sums");
+  double a[N / 2], b[N / 4], x;
+  const bool h3 = (lane >> 3) & 1, h2 = (lane >> 2) & 1, h1 = (lane >> 1) & 1;
+#pragma unroll
+  for (int j = 0; j < N / 2; ++j)
+    a[j] = (h3 ? v[N / 2 + j] : v[j]) + dpp_mov<0x140>(h3 ? v[j] : v[N / 2 + j]);  // row_mirror
+#pragma unroll
+  for (int j = 0; j < N / 4; ++j)
+    b[j] = (h2 ? a[N / 4 + j] : a[j]) + dpp_mov<0x141>(h2 ? a[j] : a[N / 4 + j]);  // row_half_mirror
+  if constexpr (N == 8) {
+    x = (h1 ? b[1] : b[0]) + dpp_mov<0x4E>(h1 ? b[0] : b[1]);  // quad_perm [2,3,0,1]
+  } else {
+    x = b[0] + dpp_mov<0x4E>(b[0]);
+  }
+  x += dpp_mov<0xB1>(x);  // quad_perm [1,0,3,2]
+  x += __shfl_xor(x, 16, 64);
+  x += __shfl_xor(x, 32, 64);
+#pragma unroll
+  for (int i = 0; i < N; ++i) {
+    const int l = N == 8 ? i << 1 : i << 2;  // lane bits 3.. hold the index of the sum
+    v[i] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l),
+                            __builtin_amdgcn_readlane(__double2loint(x), l));
+  }
 }
 
 __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
