@@ -37,46 +37,20 @@ constexpr int FB = 8;      // rows per block
 constexpr int FMAXN = 128; // rows (2 D_l) and row length (2 D_r) limit
 constexpr int FVS = 65;    // LDS row stride (double2) of the staged V^+ (bank spread)
 
-// Position p of the block round-robin in round r holds block pos_id(p, r).
-__device__ __forceinline__ int pos_id(int p, int r, int nb) {
-  return p == 0 ? 0 : 1 + ((p - 1 + r) % (nb - 1));
-}
-
-// Player at position p in sub-round s of the 8-player circle method.
-constexpr int rr8(int p, int s) { return p == 0 ? 0 : 1 + ((p - 1 + s) % 7); }
-constexpr int cmin(int a, int b) { return a < b ? a : b; }
-constexpr int cmax(int a, int b) { return a < b ? b : a; }
-
 // ---------------------------------------------------------------------------
-// Eight pairs at a time.  The 32 per-lane partial sums (x^+x, y^+y, Re x^+y,
-// Im x^+y of 8 pairs) are reduce-scattered over the wave (each lane ends with
-// one full sum instead of all 32), gathered so that every lane holds the four
-// sums of one pair, and Algorithm 1's rotation of that pair is computed lane-
-// parallel (8 pairs per instruction stream); the coefficients then go to
-// scalar registers for the vector updates.
-
-// Which register block (0 top, 1 bottom) and row each pair of a group uses.
-template <int S>
-struct CrossPairs {  // (top[i], bottom[(i + S) % 8])
-  static constexpr int xa(int) { return 0; }
-  static constexpr int xr(int i) { return i; }
-  static constexpr int ya(int) { return 1; }
-  static constexpr int yr(int i) { return (i + S) % FB; }
-};
-
-template <int S>
-struct IntraPairs {  // circle-method sub-round S inside the top (i < 4) and bottom block
-  static constexpr int xa(int i) { return i < 4 ? 0 : 1; }
-  static constexpr int xr(int i) { return cmin(rr8(i % 4, S), rr8(7 - i % 4, S)); }
-  static constexpr int ya(int i) { return xa(i); }
-  static constexpr int yr(int i) { return cmax(rr8(i % 4, S), rr8(7 - i % 4, S)); }
-};
-
-template <int E, int A>
-__device__ __forceinline__ double2 (&blk(double2 (&T)[FB][E], double2 (&B)[FB][E]))[FB][E] {
-  if constexpr (A == 0) return T;
-  else return B;
-}
+// Eight pairs at a time.  The 16 per-lane partial sums (Re and Im of x^+y of 8
+// pairs) are reduce-scattered over the wave (each lane ends with one full sum
+// instead of all 16), so that lane l computes Algorithm 1's rotation of pair
+// l & 7 (8 pairs per instruction stream); the coefficients then go to scalar
+// registers for the vector updates.  The squared norms of the wave's 16 rows
+// live in two registers, row l & 7 of the top and of the bottom block on lane
+// l, fresh at every round and moved by +-t |b_ij| per rotation.
+//
+// What bounds it: instruction issue on one compute unit.  The pairings of a
+// round are therefore loops over a few unrolled sub-rounds (rows move between
+// registers instead), which keeps the kernel inside the 64 KB instruction
+// cache that two compute units share: with all 15 sub-rounds of both register
+// widths unrolled the code took 169 KB and a 128 x 128 sweep 650 us.
 
 // One reduce-scatter stage: keep the half of v selected by this lane's bit,
 // add the partner's copy of it (the partner keeps the other half).
@@ -85,137 +59,164 @@ __device__ __forceinline__ double rs_pick(const double (&v)[2 * H], int j, bool 
   return (hi != send) ? v[H + j] : v[j];
 }
 
+// The full sum of v[l & 15] on lane l: lane bits 3, 2, 1, 0 by DPP, then full
+// sums over bits 4 and 5 (the same bits in every lane that holds a sum).
+__device__ __forceinline__ double reduce_scatter16(const double (&v)[16], int lane) {
+  double v8[8], v4[4], v2[2];
+  const bool h3 = (lane >> 3) & 1, h2 = (lane >> 2) & 1, h1 = (lane >> 1) & 1, h0 = lane & 1;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) v8[j] = rs_pick<8>(v, j, h3, false) + dpp_mov<0x140>(rs_pick<8>(v, j, h3, true));
+#pragma unroll
+  for (int j = 0; j < 4; ++j) v4[j] = rs_pick<4>(v8, j, h2, false) + dpp_mov<0x141>(rs_pick<4>(v8, j, h2, true));
+#pragma unroll
+  for (int j = 0; j < 2; ++j) v2[j] = rs_pick<2>(v4, j, h1, false) + dpp_mov<0x4E>(rs_pick<2>(v4, j, h1, true));
+  const double x = rs_pick<1>(v2, 0, h0, false) + dpp_mov<0xB1>(rs_pick<1>(v2, 0, h0, true));
+  return add_xor32(add_xor16(x));
+}
+
+// Lane l receives lane (l + S) & 7 of a value that repeats every 8 lanes.
+template <int S>
+__device__ __forceinline__ double ror8(double x) {
+  if constexpr (S % 8 == 0) return x;
+  else return dpp_mov<0x120 + 8 - S % 8>(x);
+}
+
+// Row pairs of one group: pair i joins row xr(i) and row yr(i) of the 16 rows
+// (0..7 top, 8..15 bottom).
+template <int S>
+struct CrossPairs {  // (top[i], bottom[(i + S) % 8])
+  static constexpr int xr(int i) { return i; }
+  static constexpr int yr(int i) { return FB + (i + S) % FB; }
+};
+struct IntraPairs {  // (position i, position 7 - i) inside the top (i < 4) and the bottom block
+  static constexpr int xr(int i) { return i < 4 ? i : FB + i - 4; }
+  static constexpr int yr(int i) { return i < 4 ? 7 - i : FB + 11 - i; }
+};
+
+template <int E, int R>
+__device__ __forceinline__ double2 (&row(double2 (&T)[FB][E], double2 (&B)[FB][E]))[E] {
+  if constexpr (R < FB) return T[R];
+  else return B[R - FB];
+}
+
 template <int E, class P, int I>
 __device__ __forceinline__ void partials_one(double2 (&T)[FB][E], double2 (&B)[FB][E], double (&v)[16]) {
-  double2 (&X)[FB][E] = blk<E, P::xa(I)>(T, B);
-  double2 (&Y)[FB][E] = blk<E, P::ya(I)>(T, B);
-  pair_partials_xy<E>(X[P::xr(I)], Y[P::yr(I)], v[I], v[8 + I]);
-}
-
-// Tracked squared norms live in LDS, 16 per wave (wn[0..7] top rows,
-// wn[8..15] bottom rows): index of row r of block A.
-template <int A>
-constexpr int nidx(int r) { return A * FB + r; }
-
-// This lane's pair (lane & 7) picks its two tracked norms.
-template <class P, int I>
-__device__ __forceinline__ void pick_idx(int li, int& ix, int& iy) {
-  if (li == I) {
-    ix = nidx<P::xa(I)>(P::xr(I));
-    iy = nidx<P::ya(I)>(P::yr(I));
-  }
+  pair_partials_xy<E>(row<E, P::xr(I)>(T, B), row<E, P::yr(I)>(T, B), v[I], v[8 + I]);
 }
 
 template <int E, class P, int I>
-__device__ __forceinline__ int apply_one(double2 (&T)[FB][E], double2 (&B)[FB][E], double* wn, int lane,
-                                         uint64_t act, const Rot& mine, double dn, bool x_is_i) {
-  // pair I is held (real part) by lane I after the reduce-scatter
+__device__ __forceinline__ int apply_one(double2 (&T)[FB][E], double2 (&B)[FB][E], uint64_t act, const Rot& mine) {
   if (!((act >> I) & 1)) return 0;
-  Rot rt;
+  Rot rt;  // row x plays a_i: x' = c x + s conj(e) y, y' = c y - s e x
   rt.c = readlane_d(mine.c, I);
   rt.ar = readlane_d(mine.ar, I);
   rt.ai = readlane_d(mine.ai, I);
-  rt.br = readlane_d(mine.br, I);
-  rt.bi = readlane_d(mine.bi, I);
-  const double d = readlane_d(dn, I);
-  double2 (&X)[FB][E] = blk<E, P::xa(I)>(T, B);
-  double2 (&Y)[FB][E] = blk<E, P::ya(I)>(T, B);
-  pair_apply<E>(X[P::xr(I)], Y[P::yr(I)], rt);
-  if (lane == 0) {
-    wn[nidx<P::xa(I)>(P::xr(I))] += x_is_i ? d : -d;
-    wn[nidx<P::ya(I)>(P::yr(I))] -= x_is_i ? d : -d;
-  }
+  rt.br = -rt.ar;
+  rt.bi = rt.ai;
+  pair_apply<E>(row<E, P::xr(I)>(T, B), row<E, P::yr(I)>(T, B), rt);
   return 1;
 }
 
-// Eight disjoint pairs with tracked squared norms: the 16 partial sums of
-// x^+y are reduce-scattered (lane bits 3, 2, 1, 0 by DPP, then full sums over
-// bits 4 and 5), so lane l holds component (l >> 3) & 1 (Re, Im) of pair
-// l & 7; the other component comes by a swizzle and every lane computes the
-// rotation of its pair (eight at once).
+// Eight disjoint pairs: bxx, byy are the squared norms of lane l's pair
+// (l & 7); *d receives t |b_ij| of the pairs that rotate (0 for the others).
 template <int E, class P, int... I>
-__device__ __forceinline__ int rot8_impl(double2 (&T)[FB][E], double2 (&B)[FB][E], double* wn,
-                                         bool x_is_i, double eps, double floor, int lane,
-                                         std::integer_sequence<int, I...>) {
+__device__ __forceinline__ int rot8(double2 (&T)[FB][E], double2 (&B)[FB][E], double bxx, double byy, double* d,
+                                    double eps, double floor, int lane, std::integer_sequence<int, I...>) {
   double v[16];  // v[8c + i]: component c (0 Re, 1 Im) of x_i^+ y_i
   (partials_one<E, P, I>(T, B, v), ...);
-  double v8[8], v4[4], v2[2];
-  {
-    const bool hi = (lane >> 3) & 1;
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-      v8[j] = rs_pick<8>(v, j, hi, false) + dpp_mov<0x140>(rs_pick<8>(v, j, hi, true));
-  }
-  {
-    const bool hi = (lane >> 2) & 1;
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-      v4[j] = rs_pick<4>(v8, j, hi, false) + dpp_mov<0x141>(rs_pick<4>(v8, j, hi, true));
-  }
-  {
-    const bool hi = (lane >> 1) & 1;
-#pragma unroll
-    for (int j = 0; j < 2; ++j)
-      v2[j] = rs_pick<2>(v4, j, hi, false) + dpp_mov<0x4E>(rs_pick<2>(v4, j, hi, true));
-  }
-  double x;
-  {
-    const bool hi = lane & 1;
-    x = rs_pick<1>(v2, 0, hi, false) + dpp_mov<0xB1>(rs_pick<1>(v2, 0, hi, true));
-  }
-  x += swizzle<swz(16)>(x);
-  x += __shfl_xor(x, 32, 64);  // the same bits in every lane that holds this sum
-  const double other = swizzle<swz(8)>(x);
+  const double x = reduce_scatter16(v, lane);
+  const double other = dpp_mov<0x128>(x);  // row_ror:8, the lane with the other component
   const bool im_lane = (lane >> 3) & 1;
-  const int li = lane & 7;
-  int ix = 0, iy = 0;
-  (pick_idx<P, I>(li, ix, iy), ...);
-  const double bxx = wn[ix], byy = wn[iy];
   const double br = im_lane ? other : x, bi = im_lane ? x : other;
-  const uint64_t act = __ballot(pair_needs_rot(bxx, byy, br, bi, eps, floor)) & 0xFFull;
+  const bool need = pair_needs_rot(bxx, byy, br, bi, eps, floor);
+  const uint64_t act = __ballot(need) & 0xFFull;
+  *d = 0.0;
   if (act == 0) return 0;  // no pair rotates: skip the rotation formula
   Rot mine{1.0, 0.0, 0.0, 0.0, 0.0};
   double dn = 0.0;
-  pair_rot_coeffs(bxx, byy, br, bi, x_is_i, mine, &dn);
-  return (apply_one<E, P, I>(T, B, wn, lane, act, mine, dn, x_is_i) + ...);
+  pair_rot_coeffs(bxx, byy, br, bi, true, mine, &dn);
+  *d = need ? dn : 0.0;
+  return (apply_one<E, P, I>(T, B, act, mine) + ...);
 }
 
-template <int E, class P>
-__device__ __forceinline__ int rot8(double2 (&T)[FB][E], double2 (&B)[FB][E], double* wn, bool x_is_i,
-                                    double eps, double floor, int lane) {
-  return rot8_impl<E, P>(T, B, wn, x_is_i, eps, floor, lane, std::make_integer_sequence<int, 8>{});
-}
-
-template <int E, int... S>
-__device__ __forceinline__ int cross_all_impl(double2 (&T)[FB][E], double2 (&B)[FB][E], double* wn,
-                                              bool top_is_i, double eps, double floor, int lane,
-                                              std::integer_sequence<int, S...>) {
-  return (rot8<E, CrossPairs<S>>(T, B, wn, top_is_i, eps, floor, lane) + ...);
-}
-
-template <int E, int... S>
-__device__ __forceinline__ int intra_all_impl(double2 (&T)[FB][E], double2 (&B)[FB][E], double* wn,
-                                              double eps, double floor, int lane,
-                                              std::integer_sequence<int, S...>) {
-  return (rot8<E, IntraPairs<S>>(T, B, wn, true, eps, floor, lane) + ...);
-}
-
-template <int E>
-__device__ __forceinline__ int cross_all(double2 (&T)[FB][E], double2 (&B)[FB][E], double* wn,
-                                         bool top_is_i, double eps, double floor, int lane) {
-  return cross_all_impl<E>(T, B, wn, top_is_i, eps, floor, lane, std::make_integer_sequence<int, 8>{});
-}
-
-template <int E>
-__device__ __forceinline__ int intra_all(double2 (&T)[FB][E], double2 (&B)[FB][E], double* wn,
+template <int E, int S>
+__device__ __forceinline__ int cross_sub(double2 (&T)[FB][E], double2 (&B)[FB][E], double& nt, double& nbm,
                                          double eps, double floor, int lane) {
-  return intra_all_impl<E>(T, B, wn, eps, floor, lane, std::make_integer_sequence<int, 7>{});
+  double d;
+  const int rot = rot8<E, CrossPairs<S>>(T, B, nt, ror8<S>(nbm), &d, eps, floor, lane,
+                                         std::make_integer_sequence<int, 8>{});
+  nt += d;
+  nbm -= ror8<8 - S>(d);
+  return rot;
 }
 
-// Fresh squared norms of the 16 rows a wave holds, into the wave's LDS row wn.
+// The 64 pairs of the top and the bottom block: sub-rounds of eight disjoint
+// pairs, four unrolled, then the halves of the bottom block change places
+// (twice, so they end where they were).
 template <int E>
-__device__ __forceinline__ void row_norms(const double2 (&T)[FB][E], const double2 (&B)[FB][E],
-                                          double* wn, int lane) {
+__device__ __forceinline__ int cross_all(double2 (&T)[FB][E], double2 (&B)[FB][E], double& nt, double& nbm,
+                                         double eps, double floor, int lane) {
+  int rot = 0;
+#pragma clang loop unroll(disable)
+  for (int h = 0; h < 2; ++h) {
+    rot += cross_sub<E, 0>(T, B, nt, nbm, eps, floor, lane);
+    rot += cross_sub<E, 1>(T, B, nt, nbm, eps, floor, lane);
+    rot += cross_sub<E, 2>(T, B, nt, nbm, eps, floor, lane);
+    rot += cross_sub<E, 3>(T, B, nt, nbm, eps, floor, lane);
+#pragma unroll
+    for (int t = 0; t < FB / 2; ++t)
+#pragma unroll
+      for (int k = 0; k < E; ++k) {
+        const double2 x = B[t][k];
+        B[t][k] = B[t + FB / 2][k];
+        B[t + FB / 2][k] = x;
+      }
+    nbm = ror8<4>(nbm);
+  }
+  return rot;
+}
+
+// The 28 pairs inside each block by the circle method: seven sub-rounds of
+// (position i, position 7 - i), after each of which positions 1..7 advance by
+// one (seven advances restore the order).
+template <int E>
+__device__ __forceinline__ int intra_all(double2 (&T)[FB][E], double2 (&B)[FB][E], double& nt, double& nbm,
+                                         double eps, double floor, int lane) {
+  int rot = 0;
+  const int l8 = lane & 7;
+  const bool low = l8 < 4;
+  const int from = (lane & ~7) | (l8 == 0 ? 0 : (l8 == 7 ? 1 : l8 + 1));
+#pragma clang loop unroll(disable)
+  for (int s = 0; s < FB - 1; ++s) {
+    // lane l < 4: pair (top l, top 7 - l); l >= 4: (bottom l - 4, bottom 11 - l)
+    const double bs = ror8<4>(nbm);
+    const double bxx = low ? nt : bs, byy = dpp_mov<0x141>(low ? bs : nt);  // half mirror: lane 7 - l
+    double d;
+    rot += rot8<E, IntraPairs>(T, B, bxx, byy, &d, eps, floor, lane, std::make_integer_sequence<int, 8>{});
+    const double dm = dpp_mov<0x141>(d);
+    nt += low ? d : -dm;
+    nbm = ror8<4>(bs + (low ? -dm : d));
+    nt = __shfl(nt, from, 64);
+    nbm = __shfl(nbm, from, 64);
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+      const double2 t1 = T[1][k], b1 = B[1][k];
+#pragma unroll
+      for (int t = 1; t < FB - 1; ++t) {
+        T[t][k] = T[t + 1][k];
+        B[t][k] = B[t + 1][k];
+      }
+      T[FB - 1][k] = t1;
+      B[FB - 1][k] = b1;
+    }
+  }
+  return rot;
+}
+
+// Fresh squared norms of the 16 rows a wave holds.
+template <int E>
+__device__ __forceinline__ void row_norms(const double2 (&T)[FB][E], const double2 (&B)[FB][E], double& nt,
+                                          double& nbm, int lane) {
   double v[2 * FB];
 #pragma unroll
   for (int t = 0; t < FB; ++t) {
@@ -228,10 +229,10 @@ __device__ __forceinline__ void row_norms(const double2 (&T)[FB][E], const doubl
     v[t] = a;
     v[FB + t] = b;
   }
-  wave_sum_n<2 * FB>(v);
-#pragma unroll
-  for (int t = 0; t < 2 * FB; ++t)
-    if (lane == t) wn[t] = v[t];
+  const double x = reduce_scatter16(v, lane), other = dpp_mov<0x128>(x);
+  const bool bottom = (lane >> 3) & 1;
+  nt = bottom ? other : x;
+  nbm = bottom ? x : other;
 }
 
 template <int E>
@@ -280,24 +281,21 @@ __device__ __forceinline__ void advance(double2 (&T)[FB][E], double2 (&B)[FB][E]
 // the caller: wave w holds blocks w and nb-1-w): sweeps until one makes no
 // rotation.  Returns the sweeps used, or 0 if max_sweeps were not enough.
 // The block arrangement is the initial one again on return.  s_rot: two ints
-// of shared memory, zero on entry; norms: FW x 16 doubles of shared memory.
-// Every thread of the workgroup calls this.
+// of shared memory, zero on entry.  Every thread of the workgroup calls this.
 template <int E>
 __device__ __forceinline__ int jacobi_sweeps(double2 (&T)[FB][E], double2 (&B)[FB][E], double2* xs,
-                                             int* s_rot, double* norms, int nb, int max_sweeps,
-                                             double eps, double floor) {
+                                             int* s_rot, int nb, int max_sweeps, double eps, double floor) {
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  double* wn = norms + wv * 2 * FB;
   const int nwa = nb / 2;
   for (int sw = 0; sw < max_sweeps; ++sw) {
     int rot = 0;
     for (int r = 0; r < nb - 1; ++r) {
       if (wv < nwa) {
         // squared norms, fresh for every round and then tracked through its rotations
-        row_norms<E>(T, B, wn, lane);
-        if (r == 0) rot += intra_all<E>(T, B, wn, eps, floor, lane);
-        const bool top_is_i = pos_id(wv, r, nb) < pos_id(nb - 1 - wv, r, nb);
-        rot += cross_all<E>(T, B, wn, top_is_i, eps, floor, lane);
+        double nt, nbm;
+        row_norms<E>(T, B, nt, nbm, lane);
+        if (r == 0) rot += intra_all<E>(T, B, nt, nbm, eps, floor, lane);
+        rot += cross_all<E>(T, B, nt, nbm, eps, floor, lane);
       }
       if (nb > 2) advance<E>(T, B, xs, wv, nwa, lane);
     }
@@ -321,7 +319,6 @@ __device__ __forceinline__ void set_status(const FusedGate& g, int code) {
 
 // Workgroup-shared scalars of one gate.
 struct FusedShared {
-  double norms[FW * 2 * FB];  // tracked squared row norms of the Jacobi sweeps
   double sig[FMAXN];
   int perm[FMAXN];
   int rank[FMAXN];
@@ -436,7 +433,7 @@ __device__ __forceinline__ void gate_body(const FusedGate& g, double2* xs, Fused
   const double floor = eps * eps * fro2;
 
   // ---- Algorithm 1
-  const int done = jacobi_sweeps<E>(T, B, xs, s_rot, sh.norms, nb, g.max_sweeps, eps, floor);
+  const int done = jacobi_sweeps<E>(T, B, xs, s_rot, nb, g.max_sweeps, eps, floor);
   if (!done) {
     if (threadIdx.x == 0) set_status(g, 2);
     return;
@@ -645,7 +642,7 @@ __global__ void gate1q_dev_kernel(double2* b, const double2* u, const int* dims,
 // from *it.fro2.
 template <int E>
 __device__ __forceinline__ void jacobi_small_body(const JacItem& it, int max_sweeps, double eps_scale,
-                                                  double2* xs, int* s_rot, double* norms) {
+                                                  double2* xs, int* s_rot) {
   const int n = it.n, m = it.m;
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   int nb = (n + FB - 1) / FB;
@@ -663,7 +660,7 @@ __device__ __forceinline__ void jacobi_small_body(const JacItem& it, int max_swe
     }
   const double eps = eps_scale * (double)m;
   const double floor = eps * eps * (*it.fro2);
-  const int done = jacobi_sweeps<E>(T, B, xs, s_rot, norms, nb, max_sweeps, eps, floor);
+  const int done = jacobi_sweeps<E>(T, B, xs, s_rot, nb, max_sweeps, eps, floor);
   if (wv < nwa) {
 #pragma unroll
     for (int t = 0; t < FB; ++t)
@@ -683,15 +680,14 @@ __global__ __launch_bounds__(FW * 64) void jacobi_small_kernel(const JacItem* it
                                                                double eps_scale) {
   extern __shared__ double2 xs[];
   __shared__ int s_rot[2];
-  __shared__ double norms[FW * 2 * FB];
   const JacItem it = items[blockIdx.x];
   if (threadIdx.x == 0) {
     s_rot[0] = 0;
     s_rot[1] = 0;
   }
   __syncthreads();
-  if (it.m <= 64) jacobi_small_body<1>(it, max_sweeps, eps_scale, xs, s_rot, norms);
-  else jacobi_small_body<2>(it, max_sweeps, eps_scale, xs, s_rot, norms);
+  if (it.m <= 64) jacobi_small_body<1>(it, max_sweeps, eps_scale, xs, s_rot);
+  else jacobi_small_body<2>(it, max_sweeps, eps_scale, xs, s_rot);
 }
 
 size_t fused_lds_bytes() {

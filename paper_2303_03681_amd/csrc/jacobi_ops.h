@@ -1,7 +1,6 @@
 // Algorithm 1's pair step on register-resident rows, shared by the Jacobi
-// kernels: partial sums of (x^+x, y^+y, x^+y) per lane, the rotation of one
-// pair from the reduced sums, and its application; plus the lane-exchange
-// helpers used to reduce several pairs at once.
+// kernels: partial sums of x^+y per lane, the rotation test and the rotation
+// of one pair from the reduced sums, and its application.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -9,24 +8,6 @@
 #include "wave_ops.h"
 
 namespace mps {
-
-template <int E>
-__device__ __forceinline__ void pair_partials(const double2 (&x)[E], const double2 (&y)[E],
-                                              double* acc) {
-  double xx = 0.0, yy = 0.0, re = 0.0, im = 0.0;
-#pragma unroll
-  for (int k = 0; k < E; ++k) {
-    const double2 a = x[k], b = y[k];
-    xx += a.x * a.x + a.y * a.y;
-    yy += b.x * b.x + b.y * b.y;
-    re += a.x * b.x + a.y * b.y;
-    im += a.x * b.y - a.y * b.x;
-  }
-  acc[0] = xx;
-  acc[1] = yy;
-  acc[2] = re;
-  acc[3] = im;
-}
 
 struct Rot {
   double c, ar, ai, br, bi;  // x' = c x + (ar + i ai) y,  y' = c y + (br + i bi) x
@@ -68,19 +49,6 @@ __device__ __forceinline__ void pair_rot_coeffs(double bxx, double byy, double b
   if (dn) *dn = t * (mag2 * rinv);
 }
 
-__device__ __forceinline__ bool pair_rot_core(double bxx, double byy, double br, double bi, bool x_is_i,
-                                              double eps, double floor, Rot& rt, double* dn) {
-  if (!pair_needs_rot(bxx, byy, br, bi, eps, floor)) return false;
-  pair_rot_coeffs(bxx, byy, br, bi, x_is_i, rt, dn);
-  return true;
-}
-
-// The same from the reduced (x^+x, y^+y, Re x^+y, Im x^+y).
-__device__ __forceinline__ bool pair_rot_lane(const double* acc, bool x_is_i, double eps,
-                                              double floor, Rot& rt) {
-  return pair_rot_core(acc[0], acc[1], acc[2], acc[3], x_is_i, eps, floor, rt, nullptr);
-}
-
 // Partial sums of Re and Im of x^+y over this lane's elements.
 template <int E>
 __device__ __forceinline__ void pair_partials_xy(const double2 (&x)[E], const double2 (&y)[E],
@@ -104,15 +72,6 @@ __device__ __forceinline__ void pair_apply(double2 (&x)[E], double2 (&y)[E], con
     y[k] = make_double2(rt.c * b.x + (rt.br * a.x - rt.bi * a.y), rt.c * b.y + (rt.br * a.y + rt.bi * a.x));
   }
 }
-
-template <int PAT>
-__device__ __forceinline__ double swizzle(double x) {
-  const int lo = __builtin_amdgcn_ds_swizzle(__double2loint(x), PAT);
-  const int hi = __builtin_amdgcn_ds_swizzle(__double2hiint(x), PAT);
-  return __hiloint2double(hi, lo);
-}
-// ds_swizzle bit mode: lane' = ((lane & and) | or) ^ xor within 32 lanes
-constexpr int swz(int x) { return 0x1F | (x << 10); }
 
 __device__ __forceinline__ double readlane_d(double x, int l) {
   const int lo = __builtin_amdgcn_readlane(__double2loint(x), l);

@@ -504,7 +504,7 @@ __global__ __launch_bounds__(IW * 64) void jacobi_reg_intra_kernel(const JacItem
 // only x^+y is reduced (4 partial sums, reduce-scattered over lane bits 3
 // and 2, then full sums over bits 1, 0, 4, 5), so lane l holds component
 // (l >> 3) & 1 (Re, Im) of pair (l >> 2) & 1; the other component comes by a
-// swizzle, the rotation is computed lane-parallel and the norms move by
+// row rotation, the rotation is computed lane-parallel and the norms move by
 // +-t |b_ij| (Algorithm 1 recomputes them; the caller does so at every
 // launch, so at most a few updates accumulate).
 template <int E>
@@ -527,9 +527,8 @@ __device__ __forceinline__ int rot2n(RegVec<E>& x0, RegVec<E>& y0, double& nx0, 
   }
   x += dpp_mov<0x4E>(x);
   x += dpp_mov<0xB1>(x);
-  x += swizzle<swz(16)>(x);
-  x += __shfl_xor(x, 32, 64);
-  const double other = swizzle<swz(8)>(x);
+  x = add_xor32(add_xor16(x));
+  const double other = dpp_mov<0x128>(x);  // row_ror:8, the lane with the other component
   const bool im_lane = (lane >> 3) & 1;
   const bool p1 = (lane >> 2) & 1;
   const double bxx = p1 ? nx1 : nx0, byy = p1 ? ny1 : ny0;

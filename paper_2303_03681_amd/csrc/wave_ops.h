@@ -18,6 +18,20 @@ __device__ __forceinline__ double dpp_mov(double x) {
   return __hiloint2double(hi, lo);
 }
 
+// v + (v of lane ^ 16) and v + (v of lane ^ 32), by the row and half-wave
+// swaps of gfx950 (vector instructions; the LDS crossbar path of a shuffle
+// takes several times their latency).  Both partners add in the same order.
+__device__ __forceinline__ double add_xor16(double v) {
+  const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(v), __double2loint(v), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(v), __double2hiint(v), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+__device__ __forceinline__ double add_xor32(double v) {
+  const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(v), __double2loint(v), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(v), __double2hiint(v), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+
 // A wave-uniform value moved to scalar registers (it is identical in all lanes).
 __device__ __forceinline__ double wave_uniform(double x) {
   const int lo = __builtin_amdgcn_readfirstlane(__double2loint(x));
@@ -27,15 +41,13 @@ __device__ __forceinline__ double wave_uniform(double x) {
 
 // Sum over the 64 lanes of a wave, the same bits in every lane (each step
 // adds a and b in both orders, and a + b == b + a exactly): DPP moves within
-// rows of 16 lanes, then two cross-row exchanges.
+// rows of 16 lanes, then two cross-row swaps.
 __device__ __forceinline__ double wave_sum(double v) {
   v += dpp_mov<0xB1>(v);   // quad_perm [1,0,3,2]
   v += dpp_mov<0x4E>(v);   // quad_perm [2,3,0,1]
   v += dpp_mov<0x141>(v);  // row_half_mirror
   v += dpp_mov<0x140>(v);  // row_mirror
-  v += __shfl_xor(v, 16, 64);
-  v += __shfl_xor(v, 32, 64);
-  return v;
+  return add_xor32(add_xor16(v));
 }
 
 // wave_sum of N independent values, stage by stage so the N dependency
@@ -51,9 +63,9 @@ __device__ __forceinline__ void wave_sum_n(double (&v)[N]) {
 #pragma unroll
   for (int i = 0; i < N; ++i) v[i] += dpp_mov<0x140>(v[i]);
 #pragma unroll
-  for (int i = 0; i < N; ++i) v[i] += __shfl_xor(v[i], 16, 64);
+  for (int i = 0; i < N; ++i) v[i] = add_xor16(v[i]);
 #pragma unroll
-  for (int i = 0; i < N; ++i) v[i] += __shfl_xor(v[i], 32, 64);
+  for (int i = 0; i < N; ++i) v[i] = add_xor32(v[i]);
 }
 
 // Sums of N = 4 or 8 values over the wave, handed back in scalar registers:
@@ -77,8 +89,7 @@ __device__ __forceinline__ void wave_sum_scalar(double (&v)[N], int lane) {
     x = b[0] + dpp_mov<0x4E>(b[0]);
   }
   x += dpp_mov<0xB1>(x);  // quad_perm [1,0,3,2]
-  x += __shfl_xor(x, 16, 64);
-  x += __shfl_xor(x, 32, 64);
+  x = add_xor32(add_xor16(x));
 #pragma unroll
   for (int i = 0; i < N; ++i) {
     const int l = N == 8 ? i << 1 : i << 2;  // lane bits 3.. hold the index of the sum
