@@ -223,8 +223,8 @@ __device__ __forceinline__ void row_norms(const double2 (&T)[FB][E], const doubl
     double a = 0.0, b = 0.0;
 #pragma unroll
     for (int k = 0; k < E; ++k) {
-      a += T[t][k].x * T[t][k].x + T[t][k].y * T[t][k].y;
-      b += B[t][k].x * B[t][k].x + B[t][k].y * B[t][k].y;
+      a = norm_acc(T[t][k], a);
+      b = norm_acc(B[t][k], b);
     }
     v[t] = a;
     v[FB + t] = b;
@@ -285,7 +285,7 @@ __device__ __forceinline__ void advance(double2 (&T)[FB][E], double2 (&B)[FB][E]
 template <int E>
 __device__ __forceinline__ int jacobi_sweeps(double2 (&T)[FB][E], double2 (&B)[FB][E], double2* xs,
                                              int* s_rot, int nb, int max_sweeps, double eps, double floor) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int nwa = nb / 2;
   for (int sw = 0; sw < max_sweeps; ++sw) {
     int rot = 0;
@@ -345,7 +345,7 @@ __device__ __forceinline__ void gate_body(const FusedGate& g, double2* xs, Fused
   if (g.status[0] != 0) return;  // an earlier gate of this run failed: apply nothing
   const int Dl = g.dims[g.q], Dm = g.dims[g.q + 1], Dr = g.dims[g.q + 2];
   const int n = 2 * Dl, m = 2 * Dr;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   double2* C = g.c;
 
   // ---- Eq. (C): C[(i,a)][(j,r)] = sum_{i'j'} Q[2i+j][2i'+j'] (B_q^{i'} B_{q+1}^{j'})[a][r]
@@ -644,7 +644,7 @@ template <int E>
 __device__ __forceinline__ void jacobi_small_body(const JacItem& it, int max_sweeps, double eps_scale,
                                                   double2* xs, int* s_rot) {
   const int n = it.n, m = it.m;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int nb = (n + FB - 1) / FB;
   nb = nb < 2 ? 2 : nb + (nb & 1);
   const int nwa = nb / 2;

@@ -56,11 +56,7 @@ __device__ __forceinline__ void pair_partials_xy(const double2 (&x)[E], const do
   re = 0.0;
   im = 0.0;
 #pragma unroll
-  for (int k = 0; k < E; ++k) {
-    const double2 a = x[k], b = y[k];
-    re += a.x * b.x + a.y * b.y;
-    im += a.x * b.y - a.y * b.x;
-  }
+  for (int k = 0; k < E; ++k) dot_acc(x[k], y[k], re, im);
 }
 
 template <int E>

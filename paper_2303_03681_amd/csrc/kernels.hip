@@ -323,50 +323,35 @@ __device__ __forceinline__ void rv_from_lds(RegVec<E>& r, const double2* slot, i
   for (int k = 0; k < E; ++k) r.v[k] = slot[64 * k + lane];
 }
 
-// Algorithm 1's pair step on register vectors x and y; the one with the lower
-// global index plays a_i.  One code path for both orientations:
-//   x' = c x + alpha y,  y' = c y + beta x  with (alpha, beta) =
-//   (s conj(e), -s e) if x is a_i, (-s e, s conj(e)) if y is a_i.
 template <int E>
-__device__ __forceinline__ bool jacobi_pair_ordered(RegVec<E>& x, int gx, RegVec<E>& y, int gy,
-                                                    double eps, double floor) {
-  if (gx < 0 || gy < 0) return false;
-  double bxx = 0.0, byy = 0.0, br = 0.0, bi = 0.0;  // x^+ x, y^+ y, x^+ y
+__device__ __forceinline__ double rv_norm2(const RegVec<E>& r) {
+  double s = 0.0;
 #pragma unroll
-  for (int k = 0; k < E; ++k) {
-    const double2 a = x.v[k], b = y.v[k];
-    bxx += a.x * a.x + a.y * a.y;
-    byy += b.x * b.x + b.y * b.y;
-    br += a.x * b.x + a.y * b.y;
-    bi += a.x * b.y - a.y * b.x;
-  }
-  bxx = wave_sum(bxx);
-  byy = wave_sum(byy);
-  br = wave_sum(br);
-  bi = wave_sum(bi);
-  const bool x_is_i = gx < gy;
-  const double bii = x_is_i ? bxx : byy, bjj = x_is_i ? byy : bxx;
-  const double mag = sqrt(br * br + bi * bi);
-  if (!(mag > floor) || !(mag > eps * sqrt(bii * bjj))) return false;
-  const double tau = (bii - bjj) / (2.0 * mag);
-  const double at = fabs(tau);
-  const double sg = tau >= 0.0 ? 1.0 : -1.0;
-  const double t = at > 1e100 ? sg * (0.5 / at) : sg / (at + sqrt(1.0 + tau * tau));
-  const double c = 1.0 / sqrt(1.0 + t * t);
-  const double s = t * c;
-  // e = b_ij / |b_ij| with b_ij = x^+ y (x is a_i) or y^+ x = conj(x^+ y)
-  const double er = br / mag, ei = x_is_i ? bi / mag : -bi / mag;
-  // s conj(e) and -s e
-  const double pr = s * er, pi = -s * ei, qr = -s * er, qi = -s * ei;
-  const double ar = wave_uniform(x_is_i ? pr : qr), ai = wave_uniform(x_is_i ? pi : qi);
-  const double brr = wave_uniform(x_is_i ? qr : pr), bri = wave_uniform(x_is_i ? qi : pi);
-  const double cu = wave_uniform(c);
-#pragma unroll
-  for (int k = 0; k < E; ++k) {
-    const double2 a = x.v[k], b = y.v[k];
-    x.v[k] = make_double2(cu * a.x + (ar * b.x - ai * b.y), cu * a.y + (ar * b.y + ai * b.x));
-    y.v[k] = make_double2(cu * b.x + (brr * a.x - bri * a.y), cu * b.y + (brr * a.y + bri * a.x));
-  }
+  for (int k = 0; k < E; ++k) s = norm_acc(r.v[k], s);
+  return wave_sum(s);
+}
+
+// Algorithm 1's pair step on register vectors x (as a_i) and y (as a_j) with
+// their squared norms nx and ny, which move with the rotation: only x^+y is
+// reduced.  (Exchanging the parts of a_i and a_j gives the same rotation.)
+template <int E>
+__device__ __forceinline__ bool jacobi_pair_tracked(RegVec<E>& x, double& nx, RegVec<E>& y, double& ny,
+                                                    double eps, double floor, int lane) {
+  double v[2];
+  pair_partials_xy<E>(x.v, y.v, v[0], v[1]);
+  wave_sum_scalar<2>(v, lane);
+  if (!pair_needs_rot(nx, ny, v[0], v[1], eps, floor)) return false;
+  Rot rt;
+  double dn;
+  pair_rot_coeffs(nx, ny, v[0], v[1], true, rt, &dn);
+  rt.c = wave_uniform(rt.c);
+  rt.ar = wave_uniform(rt.ar);
+  rt.ai = wave_uniform(rt.ai);
+  rt.br = -rt.ar;
+  rt.bi = rt.ai;
+  pair_apply<E>(x.v, y.v, rt);
+  nx += dn;
+  ny -= dn;
   return true;
 }
 
@@ -393,36 +378,24 @@ __device__ __forceinline__ bool reg_prologue(const JacItem* items, int max_pairs
   return true;
 }
 
-template <int E>
-__device__ __forceinline__ void reg_epilogue(const RegCtx& c, int rot, int* s_rot, const RegVec<E>& x,
-                                             int gx, const RegVec<E>& y, int gy, int sweep) {
-  const int lane = threadIdx.x & 63;
-  if (lane == 0 && rot) atomicAdd(s_rot, rot);
-  __syncthreads();
-  if (*s_rot > 0) {
-    if (gx >= 0) rv_store<E>(x, c.it.w + (size_t)gx * c.it.m, c.it.m, lane);
-    if (gy >= 0) rv_store<E>(y, c.it.w + (size_t)gy * c.it.m, c.it.m, lane);
-    if (threadIdx.x == 0) atomicAdd(&c.it.rot[sweep * c.it.rot_stride], *s_rot);
-  }
-}
-
 // Circle method over the 2W rows that W waves hold (wave w: positions w and
 // 2W - 1 - w): every pair of them is visited once in 2W - 1 steps; after
 // each step positions 1..2W-1 advance by one through 2 x W LDS slots
 // (position 0 fixed), in C chunks of E / C elements per lane so that the
-// slots take 2 W 64 (E / C) elements.  gx, gy follow the rows (global
-// indices, -1 padding).
+// slots take 2 W 64 (E / C) elements.  gx, gy (global indices, -1 padding)
+// and the squared norms follow the rows.
 template <int E, int W, int C>
 __device__ __forceinline__ int circle_pairs(RegVec<E>& x, int& gx, RegVec<E>& y, int& gy, double2* slots,
-                                            int* g_top, int* g_bot, double eps, double floor, int lane,
-                                            int wv) {
+                                            int* g_top, int* g_bot, double* n_top, double* n_bot, double eps,
+                                            double floor, int lane, int wv) {
   static_assert(E % C == 0, "chunks must divide the elements per lane");
   constexpr int EC = E / C;
   double2* top = slots;
   double2* bot = slots + (size_t)W * 64 * EC;
   int rot = 0;
+  double sx = rv_norm2<E>(x), sy = rv_norm2<E>(y);
   for (int t = 0; t < 2 * W - 1; ++t) {
-    rot += jacobi_pair_ordered<E>(x, gx, y, gy, eps, floor);
+    rot += jacobi_pair_tracked<E>(x, sx, y, sy, eps, floor, lane);
     int nx = gx, ny = gy;
 #pragma unroll
     for (int c = 0; c < C; ++c) {
@@ -434,21 +407,26 @@ __device__ __forceinline__ int circle_pairs(RegVec<E>& x, int& gx, RegVec<E>& y,
       if (c == 0 && lane == 0) {
         g_top[wv] = gx;
         g_bot[wv] = gy;
+        n_top[wv] = sx;
+        n_bot[wv] = sy;
       }
       __syncthreads();
       // new pos j+1 <- old pos j for j = 1..2W-2, new pos 1 <- old pos 2W-1, pos 0 fixed
-      const double2* sx = wv >= 2 ? top + (size_t)(wv - 1) * EC * 64 : (wv == 1 ? bot : nullptr);
-      const double2* sy = wv <= W - 2 ? bot + (size_t)(wv + 1) * EC * 64 : top + (size_t)(W - 1) * EC * 64;
-      if (sx) {
+      const double2* px = wv >= 2 ? top + (size_t)(wv - 1) * EC * 64 : (wv == 1 ? bot : nullptr);
+      const double2* py = wv <= W - 2 ? bot + (size_t)(wv + 1) * EC * 64 : top + (size_t)(W - 1) * EC * 64;
+      if (px) {
 #pragma unroll
-        for (int k = 0; k < EC; ++k) x.v[c * EC + k] = sx[(size_t)k * 64 + lane];
+        for (int k = 0; k < EC; ++k) x.v[c * EC + k] = px[(size_t)k * 64 + lane];
       }
 #pragma unroll
-      for (int k = 0; k < EC; ++k) y.v[c * EC + k] = sy[(size_t)k * 64 + lane];
+      for (int k = 0; k < EC; ++k) y.v[c * EC + k] = py[(size_t)k * 64 + lane];
       if (c == 0) {
-        if (wv >= 2) nx = g_top[wv - 1];
-        if (wv == 1) nx = g_bot[0];
+        if (wv >= 1) {
+          nx = wv >= 2 ? g_top[wv - 1] : g_bot[0];
+          sx = wv >= 2 ? n_top[wv - 1] : n_bot[0];
+        }
         ny = wv <= W - 2 ? g_bot[wv + 1] : g_top[W - 1];
+        sy = wv <= W - 2 ? n_bot[wv + 1] : n_top[W - 1];
       }
       __syncthreads();
     }
@@ -474,13 +452,14 @@ __global__ __launch_bounds__(IW * 64) void jacobi_reg_intra_kernel(const JacItem
   extern __shared__ double2 slots[];  // 2 * IW slots of 64 * E / intra_chunks<E>() elements
   __shared__ int s_rot;
   __shared__ int g_top[IW], g_bot[IW];
+  __shared__ double n_top[IW], n_bot[IW];
   const int item = blockIdx.x / max_blocks;
   const int b = blockIdx.x - item * max_blocks;
   const JacItem it = items[item];
   if (b >= it.nb) return;
   if (sweep > 0 && it.rot[(sweep - 1) * it.rot_stride] == 0) return;  // converged
   const int m = it.m, n = it.n;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (threadIdx.x == 0) s_rot = 0;
   const double eps = eps_scale * (double)m;
   const double floor = eps * eps * (*it.fro2);
@@ -490,7 +469,8 @@ __global__ __launch_bounds__(IW * 64) void jacobi_reg_intra_kernel(const JacItem
   gy = gy < n ? gy : -1;
   rv_load<E>(x, it.w + (size_t)max(gx, 0) * m, gx >= 0, m, lane);
   rv_load<E>(y, it.w + (size_t)max(gy, 0) * m, gy >= 0, m, lane);
-  const int rot = circle_pairs<E, IW, intra_chunks<E>()>(x, gx, y, gy, slots, g_top, g_bot, eps, floor, lane, wv);
+  const int rot = circle_pairs<E, IW, intra_chunks<E>()>(x, gx, y, gy, slots, g_top, g_bot, n_top, n_bot, eps, floor,
+                                                            lane, wv);
   if (lane == 0 && rot) atomicAdd(&s_rot, rot);
   __syncthreads();
   if (s_rot > 0) {
@@ -561,14 +541,6 @@ __device__ __forceinline__ int rot2n(RegVec<E>& x0, RegVec<E>& y0, double& nx0, 
   return rot;
 }
 
-template <int E>
-__device__ __forceinline__ double rv_norm2(const RegVec<E>& r) {
-  double s = 0.0;
-#pragma unroll
-  for (int k = 0; k < E; ++k) s += r.v[k].x * r.v[k].x + r.v[k].y * r.v[k].y;
-  return wave_sum(s);
-}
-
 // Every outer round: the 64 cross pairs of blocks bp and bq on CW = 4 waves.
 // Wave w keeps resident rows bp*8 + 2w, 2w + 1 and holds two travellers from
 // block bq, which move one wave along per step through LDS (4 steps) with
@@ -585,7 +557,7 @@ __global__ __launch_bounds__(CW * 64, 2) void jacobi_reg_cross_kernel(const JacI
   RegCtx c;
   if (!reg_prologue(items, max_pairs, round, sweep, eps_scale, c)) return;
   const int m = c.it.m, n = c.it.n;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if (threadIdx.x == 0) s_rot = 0;
   RegVec<E> r0, r1, t0, t1;
   const int g0 = c.bp * JW + 2 * wv, g1 = g0 + 1;
@@ -658,20 +630,24 @@ hipError_t launch_reg_e(const JacItem* items_dev, int items, int max_pairs, int 
 // cross pairs, so that every pair is visited once per outer sweep as with
 // the shorter rows.
 template <int E, int NW>
-__device__ __forceinline__ int lds_intra_block(double2* lds, int b, int n, double eps, double floor, int wv,
+__device__ __forceinline__ int lds_intra_block(double2* lds, double* nrm, double eps, double floor, int wv,
                                                int lane) {
   int rot = 0;
   for (int t = 0; t < NW - 1; ++t) {
     if (wv < NW / 2) {
       auto pos = [&](int k) { return k == 0 ? 0 : 1 + (k - 1 + t) % (NW - 1); };
       const int a = pos(wv), bb = pos(NW - 1 - wv);
-      const int ga = b * NW + a, gb = b * NW + bb;
       RegVec<E> x, y;
       rv_from_lds<E>(x, lds + (size_t)a * 64 * E, lane);
       rv_from_lds<E>(y, lds + (size_t)bb * 64 * E, lane);
-      if (jacobi_pair_ordered<E>(x, ga < n ? ga : -1, y, gb < n ? gb : -1, eps, floor)) {
+      double nx = nrm[a], ny = nrm[bb];
+      if (jacobi_pair_tracked<E>(x, nx, y, ny, eps, floor, lane)) {
         rv_to_lds<E>(x, lds + (size_t)a * 64 * E, lane);
         rv_to_lds<E>(y, lds + (size_t)bb * 64 * E, lane);
+        if (lane == 0) {
+          nrm[a] = nx;
+          nrm[bb] = ny;
+        }
         ++rot;
       }
     }
@@ -694,22 +670,22 @@ __global__ __launch_bounds__(NW * 64, 1) void jacobi_reg_lds_kernel(const JacIte
                                                                     int round, int sweep, double eps_scale) {
   extern __shared__ double2 lds[];  // NW rows of 64 E elements
   __shared__ int s_rot;
+  __shared__ double s_nrm[NW];  // their squared norms, fresh at every launch, then tracked
   RegCtx c;
   if (!reg_prologue(items, max_pairs, round, sweep, eps_scale, c)) return;
   const int m = c.it.m, n = c.it.n;
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   // the block pair in units of NW rows (the prologue's indices are in units of the item's blocks)
   const int bp = c.bp, bq = c.bq;
   if (threadIdx.x == 0) s_rot = 0;
   int rot = 0;
   auto block_to_lds = [&](int b) {
     const int g = b * NW + wv;
-    const double2* src = c.it.w + (size_t)min(g, n - 1) * m;
-#pragma unroll
-    for (int k = 0; k < E; ++k) {
-      const int e = lane + 64 * k;
-      lds[(size_t)wv * 64 * E + 64 * k + lane] = (g < n && e < m) ? src[e] : make_double2(0.0, 0.0);
-    }
+    RegVec<E> v;
+    rv_load<E>(v, c.it.w + (size_t)min(g, n - 1) * m, g < n, m, lane);
+    rv_to_lds<E>(v, lds + (size_t)wv * 64 * E, lane);
+    const double nn = rv_norm2<E>(v);
+    if (lane == 0) s_nrm[wv] = nn;
   };
   const int gx = bp * NW + wv;
   if (round == 0) {
@@ -718,7 +694,7 @@ __global__ __launch_bounds__(NW * 64, 1) void jacobi_reg_lds_kernel(const JacIte
     // row is held while the other block's pairs take two rows per wave
     block_to_lds(bp);
     __syncthreads();
-    rot += lds_intra_block<E, NW>(lds, bp, n, c.eps, c.floor, wv, lane);
+    rot += lds_intra_block<E, NW>(lds, s_nrm, c.eps, c.floor, wv, lane);
     if (gx < n)
       for (int k = 0; k < E; ++k) {
         const int e = lane + 64 * k;
@@ -728,16 +704,18 @@ __global__ __launch_bounds__(NW * 64, 1) void jacobi_reg_lds_kernel(const JacIte
   }
   block_to_lds(bq);
   __syncthreads();
-  if (round == 0) rot += lds_intra_block<E, NW>(lds, bq, n, c.eps, c.floor, wv, lane);
+  if (round == 0) rot += lds_intra_block<E, NW>(lds, s_nrm, c.eps, c.floor, wv, lane);
   RegVec<E> x;  // resident row wv of block bp
   rv_load<E>(x, c.it.w + (size_t)min(gx, n - 1) * m, gx < n, m, lane);
+  double nx = rv_norm2<E>(x);
   for (int st = 0; st < NW; ++st) {
     const int j = (wv + st) % NW;
-    const int gy = bq * NW + j;
     RegVec<E> y;
     rv_from_lds<E>(y, lds + (size_t)j * 64 * E, lane);
-    if (jacobi_pair_ordered<E>(x, gx < n ? gx : -1, y, gy < n ? gy : -1, c.eps, c.floor)) {
+    double ny = s_nrm[j];
+    if (jacobi_pair_tracked<E>(x, nx, y, ny, c.eps, c.floor, lane)) {
       rv_to_lds<E>(y, lds + (size_t)j * 64 * E, lane);
+      if (lane == 0) s_nrm[j] = ny;
       ++rot;
     }
     __syncthreads();

@@ -77,7 +77,7 @@ __global__ __launch_bounds__(256) void row_norm_kernel(const LqItem* items, int 
   if (row >= it.n) return;
   const double2* w = it.w + (size_t)row * it.m;
   double s = 0.0;
-  for (int e = lane; e < it.m; e += 64) s += w[e].x * w[e].x + w[e].y * w[e].y;
+  for (int e = lane; e < it.m; e += 64) s = norm_acc(w[e], s);
   s = wave_sum(s);
   if (lane == 0) it.norm2[row] = s;
 }
@@ -143,7 +143,7 @@ __global__ __launch_bounds__(NW * 64) void lq_panel_kernel(const LqItem* items, 
         if (a != t / NW) continue;
         double nn = 0.0;
 #pragma unroll
-        for (int k = 0; k < E; ++k) nn += x[a][k].x * x[a][k].x + x[a][k].y * x[a][k].y;
+        for (int k = 0; k < E; ++k) nn = norm_acc(x[a][k], nn);
         nn = wave_sum(nn);
         const double r = sqrt(nn), inv = r > 0.0 ? 1.0 / r : (r == 0.0 ? 0.0 : r);
 #pragma unroll
@@ -177,10 +177,7 @@ __global__ __launch_bounds__(NW * 64) void lq_panel_kernel(const LqItem* items, 
     for (int b = 0; b < RPW; ++b) {
       c[2 * b] = c[2 * b + 1] = 0.0;
 #pragma unroll
-      for (int k = 0; k < E; ++k) {
-        c[2 * b] += q[k].x * x[b][k].x + q[k].y * x[b][k].y;
-        c[2 * b + 1] += q[k].x * x[b][k].y - q[k].y * x[b][k].x;
-      }
+      for (int k = 0; k < E; ++k) dot_acc(q[k], x[b][k], c[2 * b], c[2 * b + 1]);
     }
     wave_sum_scalar<2 * RPW>(c, lane);
 #pragma unroll
@@ -189,10 +186,7 @@ __global__ __launch_bounds__(NW * 64) void lq_panel_kernel(const LqItem* items, 
       if (u <= t || u >= nb) continue;  // done, or padding
       const double cr = c[2 * b], ci = c[2 * b + 1];
 #pragma unroll
-      for (int k = 0; k < E; ++k) {
-        x[b][k].x -= cr * q[k].x - ci * q[k].y;
-        x[b][k].y -= cr * q[k].y + ci * q[k].x;
-      }
+      for (int k = 0; k < E; ++k) sub_mul(x[b][k], cr, ci, q[k]);
       if (it.r && lane == 0) it.r[(size_t)(s0 + t) * it.n + s0 + u] = make_double2(cr, -ci);
     }
   }
@@ -237,23 +231,15 @@ __global__ __launch_bounds__(256, 2) void lq_update_kernel(const LqItem* items, 
       double c[2 * RPW];
 #pragma unroll
       for (int a = 0; a < RPW; ++a) {
-        double re = 0.0, im = 0.0;
+        c[2 * a] = c[2 * a + 1] = 0.0;
 #pragma unroll
-        for (int k = 0; k < E; ++k) {
-          re += q[k].x * x[a][k].x + q[k].y * x[a][k].y;
-          im += q[k].x * x[a][k].y - q[k].y * x[a][k].x;
-        }
-        c[2 * a] = re;
-        c[2 * a + 1] = im;
+        for (int k = 0; k < E; ++k) dot_acc(q[k], x[a][k], c[2 * a], c[2 * a + 1]);
       }
       wave_sum_scalar<2 * RPW>(c, lane);
 #pragma unroll
       for (int a = 0; a < RPW; ++a) {
 #pragma unroll
-        for (int k = 0; k < E; ++k) {
-          x[a][k].x -= c[2 * a] * q[k].x - c[2 * a + 1] * q[k].y;
-          x[a][k].y -= c[2 * a] * q[k].y + c[2 * a + 1] * q[k].x;
-        }
+        for (int k = 0; k < E; ++k) sub_mul(x[a][k], c[2 * a], c[2 * a + 1], q[k]);
         if (it.r && lane == a && i0 + a < n)
           it.r[(size_t)(s0 + t0 + t) * it.n + i0 + a] = make_double2(c[2 * a], -c[2 * a + 1]);
       }

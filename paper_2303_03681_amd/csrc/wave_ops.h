@@ -11,10 +11,12 @@ typedef double __attribute__((ext_vector_type(2))) dvec2;
 typedef __attribute__((address_space(1))) dvec2 gdvec2;
 
 // Lane permutation within rows of 16 lanes (DPP control CTRL) of a double.
+// Every control used stays inside the row, so no lane keeps an old value and
+// none has to be set up.
 template <int CTRL>
 __device__ __forceinline__ double dpp_mov(double x) {
-  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xF, 0xF, false);
-  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xF, 0xF, false);
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(x), CTRL, 0xF, 0xF, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(x), CTRL, 0xF, 0xF, true);
   return __hiloint2double(hi, lo);
 }
 
@@ -68,31 +70,48 @@ __device__ __forceinline__ void wave_sum_n(double (&v)[N]) {
   for (int i = 0; i < N; ++i) v[i] = add_xor32(v[i]);
 }
 
-// Sums of N = 4 or 8 values over the wave, handed back in scalar registers:
-// reduce-scattered over lane bits 3, 2 (and 1 for N = 8), so that every lane
+// acc + conj(a) b in two chains of fused multiply-adds.
+__device__ __forceinline__ void dot_acc(double2 a, double2 b, double& re, double& im) {
+  re = fma(a.y, b.y, fma(a.x, b.x, re));
+  im = fma(-a.y, b.x, fma(a.x, b.y, im));
+}
+
+// x - (cr + i ci) q
+__device__ __forceinline__ void sub_mul(double2& x, double cr, double ci, double2 q) {
+  x.x = fma(ci, q.y, fma(-cr, q.x, x.x));
+  x.y = fma(-ci, q.x, fma(-cr, q.y, x.y));
+}
+
+__device__ __forceinline__ double norm_acc(double2 a, double s) { return fma(a.y, a.y, fma(a.x, a.x, s)); }
+
+// Sums of N = 2, 4 or 8 values over the wave, handed back in scalar registers:
+// reduce-scattered over lane bit 3 (2 for N >= 4, 1 for N = 8), so that every lane
 // carries one sum through the remaining steps, then read from the lane that
 // holds it.  About half the instructions of wave_sum_n for these N.
 template <int N>
 __device__ __forceinline__ void wave_sum_scalar(double (&v)[N], int lane) {
-  static_assert(N == 4 || N == 8, "N sums");
-  double a[N / 2], b[N / 4], x;
+  static_assert(N == 2 || N == 4 || N == 8, "N sums");
+  double a[N / 2], x;
   const bool h3 = (lane >> 3) & 1, h2 = (lane >> 2) & 1, h1 = (lane >> 1) & 1;
 #pragma unroll
   for (int j = 0; j < N / 2; ++j)
     a[j] = (h3 ? v[N / 2 + j] : v[j]) + dpp_mov<0x140>(h3 ? v[j] : v[N / 2 + j]);  // row_mirror
-#pragma unroll
-  for (int j = 0; j < N / 4; ++j)
-    b[j] = (h2 ? a[N / 4 + j] : a[j]) + dpp_mov<0x141>(h2 ? a[j] : a[N / 4 + j]);  // row_half_mirror
-  if constexpr (N == 8) {
-    x = (h1 ? b[1] : b[0]) + dpp_mov<0x4E>(h1 ? b[0] : b[1]);  // quad_perm [2,3,0,1]
+  if constexpr (N == 2) {
+    x = a[0] + dpp_mov<0x141>(a[0]);
+    x += dpp_mov<0x4E>(x);
   } else {
-    x = b[0] + dpp_mov<0x4E>(b[0]);
+    double b[N / 4];
+#pragma unroll
+    for (int j = 0; j < N / 4; ++j)
+      b[j] = (h2 ? a[N / 4 + j] : a[j]) + dpp_mov<0x141>(h2 ? a[j] : a[N / 4 + j]);  // row_half_mirror
+    if constexpr (N == 8) x = (h1 ? b[1] : b[0]) + dpp_mov<0x4E>(h1 ? b[0] : b[1]);  // quad_perm [2,3,0,1]
+    else x = b[0] + dpp_mov<0x4E>(b[0]);
   }
   x += dpp_mov<0xB1>(x);  // quad_perm [1,0,3,2]
   x = add_xor32(add_xor16(x));
 #pragma unroll
   for (int i = 0; i < N; ++i) {
-    const int l = N == 8 ? i << 1 : i << 2;  // lane bits 3.. hold the index of the sum
+    const int l = i * (16 / N);  // lane bits 3.. hold the index of the sum
     v[i] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l),
                             __builtin_amdgcn_readlane(__double2loint(x), l));
   }
