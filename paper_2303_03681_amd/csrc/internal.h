@@ -66,11 +66,12 @@ struct TruncItem {        // Eq. (Bl): out (2Dl x k) = C (2Dl x 2Dr) * conj(V)^T
 };
 
 // ---------------------------------------------------------------- LQ preconditioning
-struct LqItem {           // block modified Gram-Schmidt on the rows of w (n x m)
+struct LqItem {           // block modified Gram-Schmidt on the rows of w (n x m, n <= m)
   double2* w;             // rows, replaced by the orthonormal rows
   const int* order;       // processing order of the rows (null: as stored)
   int* order_out;         // launch_lq_order: that order
-  double2* r;             // factor as L^+, row s (of n entries) for step s; may be null
+  double2* r;             // factor as L^+ (n x n), row s for step s; may be null
+                          // (launch_lq_adjoint: the m x n matrix whose adjoint w becomes)
   double2* out;           // the rows once more as [s][row][r] (m split in halves); may be null
   double* norm2;          // squared row norms (launch_row_norm, launch_lq_order)
   const int* k_dev;       // if not null, the number of rows is min(n, *k_dev)
@@ -216,8 +217,8 @@ hipError_t launch_finalize(const FinItem* items_dev, int items, hipStream_t s);
 hipError_t launch_row_norm(const LqItem* items_dev, int items, int max_rows, hipStream_t s);
 hipError_t launch_lq_order(const LqItem* items_dev, int items, hipStream_t s);
 constexpr int kLqMax = 1024;  // longest side of a matrix the LQ kernels take
-hipError_t launch_lq(const LqItem* items_dev, int items, int max_rows, int max_len, int max_steps,
-                     hipStream_t s);
+hipError_t launch_lq(const LqItem* items_dev, int items, int max_rows, int max_len, hipStream_t s);
+hipError_t launch_lq_adjoint(const LqItem* items_dev, int items, int max_rows, int max_len, hipStream_t s);
 hipError_t launch_lq_rank(const LqFinItem* items_dev, int items, hipStream_t s);
 hipError_t launch_lq_vec(const LqVecItem* items_dev, int items, int max_k, int max_len, hipStream_t s);
 hipError_t launch_trunc(const TruncItem* items_dev, int items, int max_rows, int max_k,

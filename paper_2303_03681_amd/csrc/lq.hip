@@ -10,6 +10,11 @@
 //   P C~ = L1 Q1,   L1^+ = L2 Q2,   Algorithm 1 on the rows of L2^+ :
 //   J L2^+ = Sigma Z,  and  V^+ = Z Q1.
 //
+// A tall C~ (more rows than columns) is first replaced by the triangular
+// factor of its columns, C~^+ = L0 Q0 -> L0^+ (square, the same right vectors),
+// so that every row of every factorisation is a step: the leading rows of a
+// tall matrix need not span its row space.
+//
 // (The rows of L2^+ have the Gram matrix of the columns of L2; X = Z^+ are the
 // left singular vectors of L1^+, that is the right ones of L1.)  Sweeps until
 // no rotation, measured on captured 512 x 512 C~ of a 30-qubit D = 256
@@ -124,10 +129,10 @@ __global__ __launch_bounds__(NW * 64) void lq_panel_kernel(const LqItem* items, 
   constexpr int LQB = NW * RPW;
   __shared__ double2 q_lds[2][64 * E];
   const LqItem it = items[blockIdx.x];
-  const int n = lq_rows(it), m = it.m, steps = min(n, m);
+  const int n = lq_rows(it), m = it.m;
   const int s0 = panel * LQB;
-  if (s0 >= steps) return;
-  const int nb = min(LQB, steps - s0);
+  if (s0 >= n) return;
+  const int nb = min(LQB, n - s0);
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   double2 x[RPW][E];
 #pragma unroll
@@ -201,10 +206,10 @@ __global__ __launch_bounds__(256, 2) void lq_update_kernel(const LqItem* items, 
   __shared__ double2 q_lds[QC][64 * E];
   const int item = blockIdx.x / per_item;
   const LqItem it = items[item];
-  const int n = lq_rows(it), m = it.m, steps = min(n, m);
+  const int n = lq_rows(it), m = it.m;
   const int s0 = panel * LQB;
-  if (s0 >= steps) return;
-  const int nb = min(LQB, steps - s0);
+  if (s0 >= n) return;
+  const int nb = min(LQB, n - s0);
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int first = s0 + nb + (blockIdx.x - item * per_item) * 4 * RPW;
   if (first >= n) return;
@@ -260,13 +265,11 @@ __global__ __launch_bounds__(256, 2) void lq_update_kernel(const LqItem* items, 
 namespace {
 
 template <int E, int NW, int RPW, int URPW>
-hipError_t launch_lq_e(const LqItem* items_dev, int items, int max_rows, int max_steps, hipStream_t s) {
+hipError_t launch_lq_e(const LqItem* items_dev, int items, int max_rows, hipStream_t s) {
   constexpr int LQB = NW * RPW;
-  for (int p = 0; p * LQB < max_steps; ++p) {
+  for (int p = 0; p * LQB < max_rows; ++p) {
     hipLaunchKernelGGL((lq_panel_kernel<E, NW, RPW>), dim3(items), dim3(NW * 64), 0, s, items_dev, p);
-    // rows after the block; a matrix with fewer steps than the longest has a
-    // shorter last block, hence more rows after it than max_rows - (p + 1) LQB
-    const int rest = max_rows - p * LQB - 1;
+    const int rest = max_rows - (p + 1) * LQB;
     if (rest > 0) {
       const int per = cdiv(rest, 4 * URPW);
       hipLaunchKernelGGL((lq_update_kernel<E, LQB, URPW>), dim3(items * per), dim3(256), 0, s, items_dev, p,
@@ -281,14 +284,37 @@ hipError_t launch_lq_e(const LqItem* items_dev, int items, int max_rows, int max
 // LQ factorisation of every matrix (max_rows x max_len the largest): rows
 // become Q in place (in processing order), the factor goes to r as L^+.
 // Blocks of 32 rows, 16 where a row takes 64 registers per lane.
-hipError_t launch_lq(const LqItem* items_dev, int items, int max_rows, int max_len, int max_steps,
-                     hipStream_t s) {
+hipError_t launch_lq(const LqItem* items_dev, int items, int max_rows, int max_len, hipStream_t s) {
   if (items <= 0 || max_rows <= 0 || max_len <= 0) return hipSuccess;
-  if (max_len <= 128) return launch_lq_e<2, 8, 2, 4>(items_dev, items, max_rows, max_steps, s);
-  if (max_len <= 256) return launch_lq_e<4, 8, 2, 4>(items_dev, items, max_rows, max_steps, s);
-  if (max_len <= 512) return launch_lq_e<8, 8, 2, 4>(items_dev, items, max_rows, max_steps, s);
-  if (max_len <= 1024) return launch_lq_e<16, 8, 2, 2>(items_dev, items, max_rows, max_steps, s);
+  if (max_len <= 128) return launch_lq_e<2, 8, 2, 4>(items_dev, items, max_rows, s);
+  if (max_len <= 256) return launch_lq_e<4, 8, 2, 4>(items_dev, items, max_rows, s);
+  if (max_len <= 512) return launch_lq_e<8, 8, 2, 4>(items_dev, items, max_rows, s);
+  if (max_len <= 1024) return launch_lq_e<16, 8, 2, 2>(items_dev, items, max_rows, s);
   return hipErrorInvalidValue;
+}
+
+// w (n x m) = adjoint of r (m x n), 16 x 16 elements per workgroup through LDS.
+__global__ __launch_bounds__(256) void lq_adjoint_kernel(const LqItem* items, int per_item, int tiles_m) {
+  __shared__ double2 t[16][17];
+  const int item = blockIdx.x / per_item;
+  const LqItem it = items[item];
+  const int b = blockIdx.x - item * per_item;
+  const int i0 = (b / tiles_m) * 16, j0 = (b % tiles_m) * 16;  // rows and columns of w
+  const int x = threadIdx.x & 15, y = threadIdx.x >> 4;
+  if (i0 >= it.n || j0 >= it.m) return;
+  if (j0 + y < it.m && i0 + x < it.n) t[y][x] = it.r[(size_t)(j0 + y) * it.n + i0 + x];
+  __syncthreads();
+  if (i0 + y < it.n && j0 + x < it.m) {
+    const double2 v = t[x][y];
+    it.w[(size_t)(i0 + y) * it.m + j0 + x] = make_double2(v.x, -v.y);
+  }
+}
+
+hipError_t launch_lq_adjoint(const LqItem* items_dev, int items, int max_rows, int max_len, hipStream_t s) {
+  if (items <= 0 || max_rows <= 0 || max_len <= 0) return hipSuccess;
+  const int tiles_m = cdiv(max_len, 16), per = cdiv(max_rows, 16) * tiles_m;
+  hipLaunchKernelGGL(lq_adjoint_kernel, dim3(items * per), dim3(256), 0, s, items_dev, per, tiles_m);
+  return hipGetLastError();
 }
 
 // sigma_i = ||a_i|| from the squared norms, stable descending order,

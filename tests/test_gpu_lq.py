@@ -45,13 +45,20 @@ def _run(binding, D, u, sites, sweeps):
     (512, 257, 300, 255, 2),
     (512, 100, 512, 512, 2),
     (512, 512, 64, 100, 2),
+    (64, 64, 30, 16, 2),
+    (64, 9, 40, 30, 1),
+    # the rows of the larger half of lambda all parallel (negative decades)
+    (128, 128, 24, 12, -1),
+    (128, 60, 100, 70, -2),
 ])
 def test_gate_svd_vs_lapack_and_direct(gpu_lib, D, dl, dm, dr, decades):
     from paper_2303_03681_amd import binding
     rng = np.random.default_rng([dl, dm, dr])
-    lam = np.logspace(0, -decades, dl)
+    lam = np.logspace(0, -abs(decades), dl)
     lam /= np.linalg.norm(lam)
     b0, b1 = _site(rng, dl, dm), _site(rng, dm, dr)
+    if decades < 0:
+        b0[:, :dl // 2] = b0[:, :1]
     lam_m = np.ones(dm) / np.sqrt(dm)
     u = np.linalg.qr(rng.standard_normal((4, 4)) + 1j * rng.standard_normal((4, 4)))[0]
     sites = [(b0, lam), (b1, lam_m)]
