@@ -26,6 +26,7 @@
 
 #include "internal.h"
 #include "jacobi_ops.h"
+#include "lq_ops.h"
 #include "wave_ops.h"
 
 namespace mps {
@@ -35,6 +36,7 @@ namespace {
 constexpr int FW = 8;      // waves per workgroup
 constexpr int FB = 8;      // rows per block
 constexpr int FMAXN = 128; // rows (2 D_l) and row length (2 D_r) limit
+constexpr int FPRE = 32 * 32;  // matrices of more elements are LQ-factorised before Algorithm 1
 constexpr int FVS = 65;    // LDS row stride (double2) of the staged V^+ (bank spread)
 
 // ---------------------------------------------------------------------------
@@ -329,26 +331,9 @@ struct FusedShared {
   int ok;
 };
 
-// One two-qubit gate by the whole workgroup; xs is the dynamic LDS (block
-// slots, then the staged V^+).  Every thread returns at the same point.
-template <int E>
-__device__ __forceinline__ void gate_body(const FusedGate& g, double2* xs, FusedShared& sh) {
-  double* s_sig = sh.sig;
-  int* s_perm = sh.perm;
-  int* s_rank = sh.rank;
-  double* s_part = sh.part;
-  int* s_rot = sh.rot;
-  int& s_k = sh.k;
-  double& s_inv = sh.inv;
-  int& s_ok = sh.ok;
-
-  if (g.status[0] != 0) return;  // an earlier gate of this run failed: apply nothing
-  const int Dl = g.dims[g.q], Dm = g.dims[g.q + 1], Dr = g.dims[g.q + 2];
-  const int n = 2 * Dl, m = 2 * Dr;
-  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  double2* C = g.c;
-
-  // ---- Eq. (C): C[(i,a)][(j,r)] = sum_{i'j'} Q[2i+j][2i'+j'] (B_q^{i'} B_{q+1}^{j'})[a][r]
+// Eq. (C): C[(i,a)][(j,r)] = sum_{i'j'} Q[2i+j][2i'+j'] (B_q^{i'} B_{q+1}^{j'})[a][r]
+__device__ __forceinline__ void gate_theta(const FusedGate& g, int Dl, int Dm, int Dr) {
+  const int m = 2 * Dr;
   double2 u[16];
 #pragma unroll
   for (int i = 0; i < 16; ++i) u[i] = g.u[i];
@@ -378,12 +363,60 @@ __device__ __forceinline__ void gate_body(const FusedGate& g, double2* xs, Fused
           acc.x += v.x;
           acc.y += v.y;
         }
-        C[(size_t)(i * Dl + a) * m + j * Dr + r] = acc;
+        g.c[(size_t)(i * Dl + a) * m + j * Dr + r] = acc;
       }
   }
   __syncthreads();
+}
 
-  // ---- Eq. (C~): rows lambda_a C[(i,a)] into registers; ||C~||_F^2 in a fixed order
+// One LQ factorisation by the whole workgroup (rows x len, RPW rows per
+// wave): load(i, e) is element e of row i; the orthonormal rows go to q_out
+// (len each; may be null) and the adjoint factor to f_out (rows x rows).  All
+// rows are in registers before anything is written, so f_out may be where
+// they came from.
+template <int E, int RPW, class Load>
+__device__ __forceinline__ void gate_lq(int rows, int len, double2* xs, double2* q_out, double2* f_out, Load load) {
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double2 x[RPW][E];
+#pragma unroll
+  for (int a = 0; a < RPW; ++a) {
+    const int i = a * FW + wv;
+#pragma unroll
+    for (int k = 0; k < E; ++k) {
+      const int e = lane + 64 * k;
+      x[a][k] = i < rows && e < len ? load(i, e) : make_double2(0.0, 0.0);
+    }
+  }
+  __syncthreads();
+  mgs_rows<E, FW, RPW>(
+      x, rows, xs, [&](int t, double r) { f_out[(size_t)t * rows + t] = make_double2(r, 0.0); },
+      [&](int t, const double2* q) {
+        if (q_out)
+          for (int e = threadIdx.x; e < len; e += FW * 64) q_out[(size_t)t * len + e] = q[e];
+        for (int i = threadIdx.x; i < t; i += FW * 64) f_out[(size_t)t * rows + i] = make_double2(0.0, 0.0);
+      },
+      [&](int t, int u, double re, double im) { f_out[(size_t)t * rows + u] = make_double2(re, -im); });
+  __syncthreads();
+}
+
+// Register layout by size: 64 elements of a row per lane register, 64 rows per
+// 8 rows of a wave.
+template <class Load>
+__device__ __forceinline__ void gate_lq_any(int rows, int len, double2* xs, double2* q_out, double2* f_out,
+                                            Load load) {
+  if (rows <= 64 && len <= 64) gate_lq<1, 8>(rows, len, xs, q_out, f_out, load);
+  else if (rows <= 64) gate_lq<2, 8>(rows, len, xs, q_out, f_out, load);
+  else gate_lq<2, 16>(rows, len, xs, q_out, f_out, load);
+}
+
+// Algorithm 1 on n rows of length m (load(row, e)), then sigma_i = ||row_i||,
+// stable descending order and truncation (sh.sig, perm, rank, k, inv; sh.ok).
+// store(row, rank, e, value / sigma) is called for the kept rows.  False, with
+// the status set, if it did not converge or is not finite.
+template <int E, class Load, class Store>
+__device__ __forceinline__ bool gate_svd(const FusedGate& g, double2* xs, FusedShared& sh, int n, int m, int capk,
+                                         Load load, Store store) {
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int nb = (n + FB - 1) / FB;
   nb = nb < 2 ? 2 : nb + (nb & 1);
   const int nwa = nb / 2;
@@ -398,17 +431,8 @@ __device__ __forceinline__ void gate_body(const FusedGate& g, double2* xs, Fused
         const int e = lane + 64 * k;
         double2 vt = make_double2(0.0, 0.0), vb = make_double2(0.0, 0.0);
         if (wv < nwa && e < m) {
-          const int rt = gt + t, rb = gb + t;
-          if (rt < n) {
-            const double l = g.lam_l[rt % Dl];
-            const double2 cv = C[(size_t)rt * m + e];
-            vt = make_double2(l * cv.x, l * cv.y);
-          }
-          if (rb < n) {
-            const double l = g.lam_l[rb % Dl];
-            const double2 cv = C[(size_t)rb * m + e];
-            vb = make_double2(l * cv.x, l * cv.y);
-          }
+          if (gt + t < n) vt = load(gt + t, e);
+          if (gb + t < n) vb = load(gb + t, e);
         }
         T[t][k] = vt;
         B[t][k] = vb;
@@ -416,102 +440,71 @@ __device__ __forceinline__ void gate_body(const FusedGate& g, double2* xs, Fused
       }
   }
   part = wave_sum(part);
-  if (lane == 0) s_part[wv] = part;
+  if (lane == 0) sh.part[wv] = part;
   if (threadIdx.x == 0) {
-    s_rot[0] = 0;
-    s_rot[1] = 0;
+    sh.rot[0] = 0;
+    sh.rot[1] = 0;
   }
   __syncthreads();
   double fro2 = 0.0;
 #pragma unroll
-  for (int w = 0; w < FW; ++w) fro2 += s_part[w];
+  for (int w = 0; w < FW; ++w) fro2 += sh.part[w];
   if (!isfinite(fro2)) {
     if (threadIdx.x == 0) set_status(g, 1);
-    return;
+    return false;
   }
   const double eps = g.eps_scale * (double)m;
   const double floor = eps * eps * fro2;
-
-  // ---- Algorithm 1
-  const int done = jacobi_sweeps<E>(T, B, xs, s_rot, nb, g.max_sweeps, eps, floor);
+  const int done = jacobi_sweeps<E>(T, B, xs, sh.rot, nb, g.max_sweeps, eps, floor);
   if (!done) {
     if (threadIdx.x == 0) set_status(g, 2);
-    return;
+    return false;
   }
 
-  // ---- sigma_i = ||row_i||, stable descending order, truncation
   {
-    double nrm[2 * FB];
-#pragma unroll
-    for (int t = 0; t < FB; ++t) {
-      double a = 0.0, b = 0.0;
-#pragma unroll
-      for (int k = 0; k < E; ++k) {
-        a += T[t][k].x * T[t][k].x + T[t][k].y * T[t][k].y;
-        b += B[t][k].x * B[t][k].x + B[t][k].y * B[t][k].y;
-      }
-      nrm[t] = a;
-      nrm[FB + t] = b;
-    }
-    wave_sum_n<2 * FB>(nrm);
+    double nt, nbm;
+    row_norms<E>(T, B, nt, nbm, lane);
     if (wv < nwa && lane < 2 * FB) {
-      double v = 0.0;
-#pragma unroll
-      for (int t = 0; t < 2 * FB; ++t)
-        if (lane == t) v = nrm[t];
       const int row = lane < FB ? wv * FB + lane : (nb - 1 - wv) * FB + (lane - FB);
-      if (row < n) s_sig[row] = sqrt(v);
+      if (row < n) sh.sig[row] = sqrt(lane < FB ? nt : nbm);
     }
   }
+  if (threadIdx.x < FMAXN) sh.perm[threadIdx.x] = threadIdx.x;
   __syncthreads();
   for (int i = threadIdx.x; i < n; i += FW * 64) {
-    const double si = s_sig[i];
+    const double si = sh.sig[i];
     int rk = 0;
     for (int j = 0; j < n; ++j) {
-      const double sj = s_sig[j];
+      const double sj = sh.sig[j];
       rk += (sj > si) || (sj == si && j < i);
     }
-    s_perm[rk] = i;
-    s_rank[i] = rk;
+    sh.perm[rk] = i;
+    sh.rank[i] = rk;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double tot = 0.0;
-    bool bad = false;
-    for (int a = 0; a < n; ++a) {
-      const double sv = s_sig[s_perm[a]];
-      if (!isfinite(sv)) bad = true;
-      tot += sv * sv;
-    }
-    const double nrm = sqrt(tot);
-    int k = 0;
-    while (k < n && s_sig[s_perm[k]] > g.cutoff * nrm) ++k;
-    const int capk = min(g.cap_k, min(n, m));
-    if (k < 1) k = 1;
-    if (k > capk) k = capk;
-    double kept2 = 0.0, disc2 = 0.0;
-    for (int a = 0; a < n; ++a) {
-      const double sv = s_sig[s_perm[a]];
-      if (a < k) kept2 += sv * sv;
-      else disc2 += sv * sv;
-    }
+  if (wv == 0) {  // lane l: the l-th and the (l + 64)-th largest
+    const double s0 = lane < n ? sh.sig[sh.perm[lane]] : 0.0;
+    const double s1 = lane + 64 < n ? sh.sig[sh.perm[lane + 64]] : 0.0;
+    const double tot = wave_sum(s0 * s0 + s1 * s1), cut = g.cutoff * sqrt(tot);
+    int k = __popcll(__ballot(lane < n && s0 > cut)) + __popcll(__ballot(lane + 64 < n && s1 > cut));
+    k = min(max(k, 1), capk);
+    const double kept2 = wave_sum((lane < k ? s0 * s0 : 0.0) + (lane + 64 < k ? s1 * s1 : 0.0));
+    const double disc2 = wave_sum((lane < k ? 0.0 : s0 * s0) + (lane + 64 < k ? 0.0 : s1 * s1));
     const double kept = sqrt(kept2);
-    s_ok = !(bad || !(kept > 0.0) || !isfinite(kept));
-    s_inv = s_ok ? 1.0 / kept : 0.0;
-    s_k = k;
-    if (s_ok) {
-      *g.disc += tot > 0.0 ? disc2 / tot : 0.0;
-      *g.sweeps += done;
-    } else {
-      set_status(g, 1);
+    if (lane == 0) {
+      sh.ok = isfinite(tot) && kept > 0.0 && isfinite(kept);
+      sh.inv = sh.ok ? 1.0 / kept : 0.0;
+      sh.k = k;
+      if (sh.ok) {
+        *g.disc += tot > 0.0 ? disc2 / tot : 0.0;
+        *g.sweeps += done;
+      } else {
+        set_status(g, 1);
+      }
     }
   }
   __syncthreads();
-  if (!s_ok) return;
-  const int k = s_k;
-  const double inv = s_inv;
-
-  // ---- Eq. (Bl): B_{q+1} <- V_k^+ as [j][p][r];  lambda_{q+1} <- sigma_k / ||sigma_k||
+  if (!sh.ok) return false;
   if (wv < nwa) {
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -520,23 +513,131 @@ __device__ __forceinline__ void gate_body(const FusedGate& g, double2* xs, Fused
       for (int t = 0; t < FB; ++t) {
         const int row = base + t;
         if (row >= n) continue;
-        const int p = s_rank[row];
-        if (p >= k) continue;
-        const double sv = s_sig[row];
+        const int p = sh.rank[row];
+        if (p >= sh.k) continue;
+        const double sv = sh.sig[row];
         const double is = sv > 0.0 ? 1.0 / sv : 0.0;
 #pragma unroll
         for (int kk = 0; kk < E; ++kk) {
           const int e = lane + 64 * kk;
           if (e < m) {
             const double2 x = h == 0 ? T[t][kk] : B[t][kk];
-            const int j = e >= Dr ? 1 : 0, r = e - j * Dr;
-            g.bq1[((size_t)j * k + p) * Dr + r] = make_double2(x.x * is, x.y * is);
+            store(p, e, make_double2(x.x * is, x.y * is));
           }
         }
       }
     }
   }
-  for (int p = threadIdx.x; p < k; p += FW * 64) g.lam_m[p] = s_sig[s_perm[p]] * inv;
+  return true;
+}
+
+// V^+ (k x m) = Z Q, Z (k x na) and Q (na x m) in memory, its rows then
+// orthonormalised in order (they are to eps sigma_1 / sigma_p) and stored as
+// the right site tensor [j][p][r].
+template <int E, int RPW>
+__device__ __forceinline__ void gate_vec(const FusedGate& g, double2* xs, const double2* z, const double2* q, int k,
+                                         int na, int m, int Dr) {
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  double2 x[RPW][E];
+#pragma unroll
+  for (int a = 0; a < RPW; ++a)
+#pragma unroll
+    for (int c = 0; c < E; ++c) x[a][c] = make_double2(0.0, 0.0);
+  for (int s = 0; s < na; ++s) {
+    double2 v[E];
+#pragma unroll
+    for (int c = 0; c < E; ++c) {
+      const int e = lane + 64 * c;
+      v[c] = q[(size_t)s * m + min(e, m - 1)];
+    }
+#pragma unroll
+    for (int a = 0; a < RPW; ++a) {
+      const double2 w = z[(size_t)min(a * FW + wv, k - 1) * na + s];
+#pragma unroll
+      for (int c = 0; c < E; ++c) sub_mul(x[a][c], -w.x, -w.y, v[c]);
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < RPW; ++a)
+#pragma unroll
+    for (int c = 0; c < E; ++c)
+      if (lane + 64 * c >= m || a * FW + wv >= k) x[a][c] = make_double2(0.0, 0.0);
+  mgs_rows<E, FW, RPW>(
+      x, k, xs, [](int, double) {},
+      [&](int t, const double2* v) {
+        for (int e = threadIdx.x; e < m; e += FW * 64) {
+          const int j = e >= Dr ? 1 : 0;
+          g.bq1[((size_t)j * k + t) * Dr + e - j * Dr] = v[e];
+        }
+      },
+      [](int, int, double, double) {});
+}
+
+// One two-qubit gate by the whole workgroup; xs is the dynamic LDS (block
+// slots, rows in flight, then the staged V^+).  Every thread returns at the
+// same point.
+__device__ __forceinline__ void gate_any(const FusedGate& g, double2* xs, FusedShared& sh) {
+  if (g.status[0] != 0) return;  // an earlier gate of this run failed: apply nothing
+  const int Dl = g.dims[g.q], Dm = g.dims[g.q + 1], Dr = g.dims[g.q + 2];
+  const int n = 2 * Dl, m = 2 * Dr;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const double2* C = g.c;
+  gate_theta(g, Dl, Dm, Dr);
+  const int capk = min(g.cap_k, min(n, m));
+
+  // Eq. (C~) is lambda_a C[(i,a)]; i and a exchanged, its rows are in the order of lambda
+  const bool pre = g.l1 != nullptr && (n * m > FPRE || n > 2 * m);
+  if (pre) {
+    // Two LQ factorisations before Algorithm 1, as for the batched gates: the
+    // sweeps then see a nearly diagonal matrix (UCCSD chains: 14.6 -> 5.6
+    // sweeps on average), and V^+ is their result times the first Q.
+    double2* f = g.l1;   // factors, then Z
+    double2* q1 = g.l2;  // Q of the first factorisation
+    const int na = min(n, m);
+    if (n > m) {  // tall: its m x m triangular factor has the same right vectors
+      gate_lq_any(m, n, xs, nullptr, f, [&](int i, int e) {
+        const double l = g.lam_l[e % Dl];
+        const double2 v = C[(size_t)e * m + i];
+        return make_double2(l * v.x, -l * v.y);
+      });
+      gate_lq_any(m, m, xs, q1, f, [&](int i, int e) { return f[(size_t)i * m + e]; });
+    } else {
+      gate_lq_any(n, m, xs, q1, f, [&](int i, int e) {
+        const int a = i >> 1;
+        const double l = g.lam_l[a];
+        const double2 v = C[(size_t)((i & 1) * Dl + a) * m + e];
+        return make_double2(l * v.x, l * v.y);
+      });
+    }
+    gate_lq_any(na, na, xs, nullptr, f, [&](int i, int e) { return f[(size_t)i * na + e]; });
+    auto load = [&](int i, int e) { return f[(size_t)i * na + e]; };
+    auto store = [&](int p, int e, double2 v) { f[(size_t)p * na + e] = v; };
+    if (!(na <= 64 ? gate_svd<1>(g, xs, sh, na, na, capk, load, store)
+                   : gate_svd<2>(g, xs, sh, na, na, capk, load, store)))
+      return;
+    __syncthreads();
+    if (m <= 64) gate_vec<1, 8>(g, xs, f, q1, sh.k, na, m, Dr);
+    else if (sh.k <= 64) gate_vec<2, 8>(g, xs, f, q1, sh.k, na, m, Dr);
+    else gate_vec<2, 16>(g, xs, f, q1, sh.k, na, m, Dr);
+  } else {
+    auto load = [&](int i, int e) {
+      const double l = g.lam_l[i % Dl];
+      const double2 v = C[(size_t)i * m + e];
+      return make_double2(l * v.x, l * v.y);
+    };
+    auto store = [&](int p, int e, double2 v) {
+      const int j = e >= Dr ? 1 : 0;
+      g.bq1[((size_t)j * sh.k + p) * Dr + e - j * Dr] = v;
+    };
+    if (!(m <= 64 ? gate_svd<1>(g, xs, sh, n, m, capk, load, store)
+                  : gate_svd<2>(g, xs, sh, n, m, capk, load, store)))
+      return;
+  }
+  const int k = sh.k;
+  const double inv = sh.inv;
+
+  // ---- Eq. (Bl): lambda_{q+1} <- sigma_k / ||sigma_k||
+  for (int p = threadIdx.x; p < k; p += FW * 64) g.lam_m[p] = sh.sig[sh.perm[p]] * inv;
 
   // ---- Eq. (Bl): B_q[(i,a)][p] = inv sum_e C[(i,a)][e] conj(V^+[p][e]), 64 columns at a
   // time, V^+ read back from the rows just stored in B_{q+1}
@@ -580,12 +681,6 @@ __device__ __forceinline__ void gate_body(const FusedGate& g, double2* xs, Fused
   if (threadIdx.x == 0) g.dims[g.q + 1] = k;
 }
 
-// Register width from the actual row length 2 D_r.
-__device__ __forceinline__ void gate_any(const FusedGate& g, double2* xs, FusedShared& sh) {
-  if (2 * g.dims[g.q + 2] <= 64) gate_body<1>(g, xs, sh);
-  else gate_body<2>(g, xs, sh);
-}
-
 __global__ __launch_bounds__(FW * 64) void gate2q_fused_kernel(FusedGate g) {
   extern __shared__ double2 xs[];
   __shared__ FusedShared sh;
@@ -616,7 +711,7 @@ __global__ __launch_bounds__(FW * 64) void fused_step_kernel(const FusedRun* run
     }
     return;
   }
-  const FusedGate g{r.sites[q], r.sites[q + 1], r.lam[q], r.lam[q + 1], u, r.dims, r.c, r.status,
+  const FusedGate g{r.sites[q], r.sites[q + 1], r.lam[q], r.lam[q + 1], u, r.dims, r.c, r.l1, r.l2, r.status,
                     r.disc, r.sweeps, q, (int)gi, r.cap[q + 1], r.max_sweeps, r.cutoff, r.eps_scale};
   gate_any(g, xs, sh);
 }

@@ -165,6 +165,8 @@ struct FusedGate {
   const double2* u;     // 4x4 gate, row-major, row index 2 i_q + i_{q+1}
   int* dims;            // bond dimensions (n + 1), dims[q+1] <- k
   double2* c;           // scratch, >= 2 D_l x 2 D_r
+  double2* l1;          // two more of that size for the LQ factors; null: Algorithm 1 on C~ itself
+  double2* l2;
   int* status;          // [0]: 0 ok, 1 non-finite, 2 no convergence; [1]: failing gate
   double* disc;         // += relative discarded weight
   int* sweeps;          // += sweeps used
@@ -182,6 +184,8 @@ struct FusedRun {
   const int* cap;         // bond capacities (n + 1)
   int* dims;
   double2* c;             // scratch, >= 2 cap x 2 cap
+  double2* l1;            // as in FusedGate
+  double2* l2;
   int* status;
   double* disc;
   int* sweeps;

@@ -845,6 +845,8 @@ __global__ __launch_bounds__(1024) void finalize_kernel(const FinItem* items) {
     if (lane == 0) sig[v] = sqrt(acc);
   }
   __syncthreads();
+  for (int i = threadIdx.x; i < n; i += blockDim.x) perm[i] = i;  // (a NaN leaves ranks unset)
+  __syncthreads();
   for (int i = threadIdx.x; i < n; i += blockDim.x) {
     const double si = sig[i];
     int r = 0;
@@ -855,37 +857,34 @@ __global__ __launch_bounds__(1024) void finalize_kernel(const FinItem* items) {
     perm[r] = i;
   }
   __syncthreads();
-  if (threadIdx.x == 0) {
+  // sums over the values: one wave, lane l takes l, l + 64, ...
+  if (threadIdx.x < 64) {
     double tot = 0.0;
-    bool bad = false;
-    for (int a = 0; a < n; ++a) {
-      const double sv = sig[perm[a]];
-      if (!isfinite(sv)) bad = true;
-      tot += sv * sv;
-    }
+    for (int a = lane; a < n; a += 64) tot += sig[a] * sig[a];
+    tot = wave_sum(tot);
     const double nrm = sqrt(tot);
     int k = 0;
-    while (k < n && sig[perm[k]] > it.cutoff * nrm) ++k;
-    if (k < 1) k = 1;
-    if (k > it.cap) k = it.cap;
+    for (int a = lane; a < n; a += 64) k += sig[a] > it.cutoff * nrm ? 1 : 0;
+    k = (int)wave_sum((double)k);
+    k = min(max(k, 1), it.cap);
     double kept2 = 0.0, disc2 = 0.0;
-    for (int a = 0; a < n; ++a) {
+    for (int a = lane; a < n; a += 64) {
       const double sv = sig[perm[a]];
       if (a < k) kept2 += sv * sv;
       else disc2 += sv * sv;
     }
+    kept2 = wave_sum(kept2);
+    disc2 = wave_sum(disc2);
     const double kept = sqrt(kept2);
-    if (bad || !(kept > 0.0) || !isfinite(kept)) {
-      *it.status_out = 1;
-      s_inv = 0.0;
-    } else {
-      *it.status_out = 0;
-      s_inv = 1.0 / kept;
+    const bool bad = !isfinite(tot) || !(kept > 0.0) || !isfinite(kept);
+    if (lane == 0) {
+      *it.status_out = bad ? 1 : 0;
+      s_inv = bad ? 0.0 : 1.0 / kept;
+      *it.k_out = k;
+      *it.scale_out = s_inv;
+      *it.disc_out = tot > 0.0 ? disc2 / tot : 0.0;
+      s_k = k;
     }
-    *it.k_out = k;
-    *it.scale_out = s_inv;
-    *it.disc_out = tot > 0.0 ? disc2 / tot : 0.0;
-    s_k = k;
   }
   __syncthreads();
   const int k = s_k;

@@ -40,6 +40,7 @@
 
 #include "gemm_core.h"
 #include "internal.h"
+#include "lq_ops.h"
 #include "wave_ops.h"
 
 namespace mps {
@@ -118,12 +119,9 @@ hipError_t launch_lq_order(const LqItem* items_dev, int items, hipStream_t s) {
   return hipGetLastError();
 }
 
-// Modified Gram-Schmidt inside block `panel` (LQB rows) of every matrix: one
-// workgroup of NW waves per matrix, row u of the block in registers of wave
-// u % NW.  At step t the owner normalises row t and hands it on through one
-// of two LDS buffers (one barrier per step: a buffer is rewritten two steps
-// later, after every wave has passed the next barrier).  Row s of the factor
-// gets its diagonal and in-block entries, and zeros before the diagonal.
+// Modified Gram-Schmidt inside block `panel` (LQB rows) of every matrix, one
+// workgroup of NW waves per matrix.  Row s of the factor gets its diagonal and
+// in-block entries, and zeros before the diagonal.
 template <int E, int NW, int RPW>
 __global__ __launch_bounds__(NW * 64) void lq_panel_kernel(const LqItem* items, int panel) {
   constexpr int LQB = NW * RPW;
@@ -140,61 +138,29 @@ __global__ __launch_bounds__(NW * 64) void lq_panel_kernel(const LqItem* items, 
     const int u = a * NW + wv;
     load_row<E>(x[a], lq_row(it, s0 + min(u, nb - 1)), u < nb, m, lane);
   }
-  for (int t = 0; t < nb; ++t) {
-    double2* buf = q_lds[t & 1];
-    if (wv == t % NW) {
-#pragma unroll
-      for (int a = 0; a < RPW; ++a) {
-        if (a != t / NW) continue;
-        double nn = 0.0;
-#pragma unroll
-        for (int k = 0; k < E; ++k) nn = norm_acc(x[a][k], nn);
-        nn = wave_sum(nn);
-        const double r = sqrt(nn), inv = r > 0.0 ? 1.0 / r : (r == 0.0 ? 0.0 : r);
-#pragma unroll
-        for (int k = 0; k < E; ++k) buf[lane + 64 * k] = make_double2(x[a][k].x * inv, x[a][k].y * inv);
-        if (it.r && lane == 0) it.r[(size_t)(s0 + t) * it.n + s0 + t] = make_double2(r, 0.0);
-      }
-    }
-    __syncthreads();
-    // the finished row (and the factor's zeros before the diagonal), by all threads
-    {
-      gdvec2* dst = (gdvec2*)lq_row(it, s0 + t);
-      const int half = m / 2;
-      for (int e = threadIdx.x; e < m; e += NW * 64) {
-        const double2 q = buf[e];
-        dst[e] = dvec2{q.x, q.y};
-        if (it.out) {  // [s][row][r], the layout of a right site tensor
-          const int sb = e >= half ? 1 : 0;
-          it.out[((size_t)sb * n + s0 + t) * half + e - sb * half] = q;
+  const int half = m / 2;
+  mgs_rows<E, NW, RPW>(
+      x, nb, &q_lds[0][0],
+      [&](int t, double r) {
+        if (it.r) it.r[(size_t)(s0 + t) * it.n + s0 + t] = make_double2(r, 0.0);
+      },
+      [&](int t, const double2* q) {  // the finished row, and the factor's zeros before the diagonal
+        gdvec2* dst = (gdvec2*)lq_row(it, s0 + t);
+        for (int e = threadIdx.x; e < m; e += NW * 64) {
+          const double2 v = q[e];
+          dst[e] = dvec2{v.x, v.y};
+          if (it.out) {  // [s][row][r], the layout of a right site tensor
+            const int sb = e >= half ? 1 : 0;
+            it.out[((size_t)sb * n + s0 + t) * half + e - sb * half] = v;
+          }
         }
-      }
-      if (it.r)
-        for (int i = threadIdx.x; i < s0 + t; i += NW * 64)
-          it.r[(size_t)(s0 + t) * it.n + i] = make_double2(0.0, 0.0);
-    }
-    if (wv + (RPW - 1) * NW <= t) continue;  // no later row on this wave
-    double2 q[E];
-#pragma unroll
-    for (int k = 0; k < E; ++k) q[k] = buf[lane + 64 * k];
-    double c[2 * RPW];
-#pragma unroll
-    for (int b = 0; b < RPW; ++b) {
-      c[2 * b] = c[2 * b + 1] = 0.0;
-#pragma unroll
-      for (int k = 0; k < E; ++k) dot_acc(q[k], x[b][k], c[2 * b], c[2 * b + 1]);
-    }
-    wave_sum_scalar<2 * RPW>(c, lane);
-#pragma unroll
-    for (int b = 0; b < RPW; ++b) {
-      const int u = b * NW + wv;
-      if (u <= t || u >= nb) continue;  // done, or padding
-      const double cr = c[2 * b], ci = c[2 * b + 1];
-#pragma unroll
-      for (int k = 0; k < E; ++k) sub_mul(x[b][k], cr, ci, q[k]);
-      if (it.r && lane == 0) it.r[(size_t)(s0 + t) * it.n + s0 + u] = make_double2(cr, -ci);
-    }
-  }
+        if (it.r)
+          for (int i = threadIdx.x; i < s0 + t; i += NW * 64)
+            it.r[(size_t)(s0 + t) * it.n + i] = make_double2(0.0, 0.0);
+      },
+      [&](int t, int u, double re, double im) {
+        if (it.r) it.r[(size_t)(s0 + t) * it.n + s0 + u] = make_double2(re, -im);
+      });
 }
 
 // Takes the components along the rows of block `panel` out of every later row
@@ -342,33 +308,34 @@ __global__ __launch_bounds__(1024) void lq_rank_kernel(const LqFinItem* items) {
     perm[r] = i;
   }
   __syncthreads();
-  if (i == 0) {
+  // sums over the ordered values: one wave, lane l takes l, l + 64, ...
+  if (i < 64) {
     double tot = 0.0;
-    bool bad = false;
-    for (int a = 0; a < n; ++a) {
-      const double sv = sig[perm[a]];
-      if (!isfinite(sv)) bad = true;
-      tot += sv * sv;
-    }
+    for (int a = i; a < n; a += 64) tot += sig[a] * sig[a];
+    tot = wave_sum(tot);
     const double nrm = sqrt(tot);
     int k = 0;
-    while (k < n && sig[perm[k]] > it.cutoff * nrm) ++k;
-    if (k < 1) k = 1;
-    if (k > it.cap) k = it.cap;
+    for (int a = i; a < n; a += 64) k += sig[a] > it.cutoff * nrm ? 1 : 0;
+    k = (int)wave_sum((double)k);
+    k = min(max(k, 1), it.cap);
     double kept2 = 0.0, disc2 = 0.0;
-    for (int a = 0; a < n; ++a) {
+    for (int a = i; a < n; a += 64) {
       const double sv = sig[perm[a]];
       if (a < k) kept2 += sv * sv;
       else disc2 += sv * sv;
     }
+    kept2 = wave_sum(kept2);
+    disc2 = wave_sum(disc2);
     const double kept = sqrt(kept2);
-    bad = bad || !isfinite(tot) || !(kept > 0.0) || !isfinite(kept);
-    *it.status_out = bad ? 1 : 0;
-    s_inv = bad ? 0.0 : 1.0 / kept;
-    *it.k_out = k;
-    *it.scale_out = s_inv;
-    *it.disc_out = tot > 0.0 ? disc2 / tot : 0.0;
-    s_k = k;
+    const bool bad = !isfinite(tot) || !(kept > 0.0) || !isfinite(kept);
+    if (i == 0) {
+      *it.status_out = bad ? 1 : 0;
+      s_inv = bad ? 0.0 : 1.0 / kept;
+      *it.k_out = k;
+      *it.scale_out = s_inv;
+      *it.disc_out = tot > 0.0 ? disc2 / tot : 0.0;
+      s_k = k;
+    }
   }
   __syncthreads();
   if (i < s_k) {

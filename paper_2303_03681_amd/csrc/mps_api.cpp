@@ -2180,6 +2180,11 @@ mps_status fused_begin(mps_state* h) {
   if (h->fused_active) return MPS_OK;
   mps_status st = ensure_ws(h, 1);
   if (st != MPS_OK) return st;
+  if (h->max_sweeps >= kDefaultSweeps) {  // scratch for the LQ factors, if there is room
+    h->pre_busy = true;
+    (void)ensure_pre(h, 1);
+    h->pre_busy = false;
+  }
   if ((st = upload(h, h->d_dims, h->dims.data(), sizeof(int) * (h->n + 1))) != MPS_OK) return st;
   HIP_TRY(h, hipMemsetAsync(h->d_fstat, 0, 2 * sizeof(int), h->stream));
   HIP_TRY(h, hipMemsetAsync(h->d_fdisc, 0, sizeof(double), h->stream));
@@ -2222,8 +2227,9 @@ mps_status fused_flush(mps_state* h, int64_t* failed_at, int* code) {
 }
 
 mps_status fused_launch(mps_state* h, int q, const double2* u, int gate) {
+  const bool pre = h->max_sweeps >= kDefaultSweeps;
   FusedGate g{h->cur(q), h->cur(q + 1), h->lcur(q), h->lcur(q + 1), u, h->d_dims, h->ws_c,
-              h->d_fstat, h->d_fdisc, h->d_fsweeps, q, gate, h->cap[q + 1], h->max_sweeps,
+              pre ? h->ws_l1 : nullptr, pre ? h->ws_l2 : nullptr, h->d_fstat, h->d_fdisc, h->d_fsweeps, q, gate, h->cap[q + 1], h->max_sweeps,
               h->cutoff, kEpsScale};
   HIP_TRY(h, launch_gate2q_fused(g, 2 * h->cap[q + 2], h->stream));
   return MPS_OK;
@@ -2586,12 +2592,15 @@ mps_status mps_apply_gates_multi(int32_t n_handles, const mps_handle* hs, const 
   hipStream_t s = stream ? (hipStream_t)stream : hs[0]->stream;
   std::vector<FusedRun> runs(n_handles);
   int64_t steps = 0;
+  mps_state* h0 = hs[0];
+  // before the runs take the handles' scratch, which an allocation may give back
+  mps_status st = ensure_desc(h0, sizeof(FusedRun) * n_handles);
+  if (st != MPS_OK) return st;
   for (int i = 0; i < n_handles; ++i) {
     mps_state* h = hs[i];
     const int64_t ng = n_gates[i];
     steps = std::max(steps, ng);
-    mps_status st = ensure_ws(h, 1);
-    if (st != MPS_OK) return st;
+    if ((st = ensure_ws(h, 1)) != MPS_OK) return st;
     if ((st = sync(h)) != MPS_OK) return st;
     const size_t need = (size_t)std::max<int64_t>(ng, 1);
     if (need * 16 > h->gates_cap) {
@@ -2621,13 +2630,12 @@ mps_status mps_apply_gates_multi(int32_t n_handles, const mps_handle* hs, const 
     HIP_TRY(h, hipMemcpy(h->d_lam_ptrs, lp.data(), sizeof(double*) * (h->n + 1), hipMemcpyHostToDevice));
     if ((st = fused_begin(h)) != MPS_OK) return st;
     if ((st = sync(h)) != MPS_OK) return st;
-    runs[i] = FusedRun{h->d_site_ptrs, h->d_lam_ptrs, h->d_cap, h->d_dims, h->ws_c, h->d_fstat,
+    const bool pre = h->max_sweeps >= kDefaultSweeps;
+    runs[i] = FusedRun{h->d_site_ptrs, h->d_lam_ptrs, h->d_cap, h->d_dims, h->ws_c,
+                       pre ? h->ws_l1 : nullptr, pre ? h->ws_l2 : nullptr, h->d_fstat,
                        h->d_fdisc, h->d_fsweeps, h->d_gq, h->d_gq + ng, (const double2*)h->d_gates,
                        0, ng, h->max_sweeps, h->cutoff, kEpsScale};
   }
-  mps_state* h0 = hs[0];
-  mps_status st = ensure_desc(h0, sizeof(FusedRun) * n_handles);
-  if (st != MPS_OK) return st;
   HIP_TRY(h0, hipMemcpy(h0->d_desc, runs.data(), sizeof(FusedRun) * n_handles, hipMemcpyHostToDevice));
   for (int64_t k = 0; k < steps; ++k)
     HIP_TRY(h0, launch_fused_step((const FusedRun*)h0->d_desc, n_handles, k, s));
