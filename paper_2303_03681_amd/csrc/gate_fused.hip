@@ -24,6 +24,7 @@
 #include <cstdint>
 #include <utility>
 
+#include "gemm_core.h"
 #include "internal.h"
 #include "jacobi_ops.h"
 #include "lq_ops.h"
@@ -37,7 +38,6 @@ constexpr int FW = 8;      // waves per workgroup
 constexpr int FB = 8;      // rows per block
 constexpr int FMAXN = 128; // rows (2 D_l) and row length (2 D_r) limit
 constexpr int FPRE = 32 * 32;  // matrices of more elements are LQ-factorised before Algorithm 1
-constexpr int FVS = 65;    // LDS row stride (double2) of the staged V^+ (bank spread)
 
 // ---------------------------------------------------------------------------
 // Eight pairs at a time.  The 16 per-lane partial sums (Re and Im of x^+y of 8
@@ -53,28 +53,6 @@ constexpr int FVS = 65;    // LDS row stride (double2) of the staged V^+ (bank s
 // registers instead), which keeps the kernel inside the 64 KB instruction
 // cache that two compute units share: with all 15 sub-rounds of both register
 // widths unrolled the code took 169 KB and a 128 x 128 sweep 650 us.
-
-// One reduce-scatter stage: keep the half of v selected by this lane's bit,
-// add the partner's copy of it (the partner keeps the other half).
-template <int H>
-__device__ __forceinline__ double rs_pick(const double (&v)[2 * H], int j, bool hi, bool send) {
-  return (hi != send) ? v[H + j] : v[j];
-}
-
-// The full sum of v[l & 15] on lane l: lane bits 3, 2, 1, 0 by DPP, then full
-// sums over bits 4 and 5 (the same bits in every lane that holds a sum).
-__device__ __forceinline__ double reduce_scatter16(const double (&v)[16], int lane) {
-  double v8[8], v4[4], v2[2];
-  const bool h3 = (lane >> 3) & 1, h2 = (lane >> 2) & 1, h1 = (lane >> 1) & 1, h0 = lane & 1;
-#pragma unroll
-  for (int j = 0; j < 8; ++j) v8[j] = rs_pick<8>(v, j, h3, false) + dpp_mov<0x140>(rs_pick<8>(v, j, h3, true));
-#pragma unroll
-  for (int j = 0; j < 4; ++j) v4[j] = rs_pick<4>(v8, j, h2, false) + dpp_mov<0x141>(rs_pick<4>(v8, j, h2, true));
-#pragma unroll
-  for (int j = 0; j < 2; ++j) v2[j] = rs_pick<2>(v4, j, h1, false) + dpp_mov<0x4E>(rs_pick<2>(v4, j, h1, true));
-  const double x = rs_pick<1>(v2, 0, h0, false) + dpp_mov<0xB1>(rs_pick<1>(v2, 0, h0, true));
-  return add_xor32(add_xor16(x));
-}
 
 // Lane l receives lane (l + S) & 7 of a value that repeats every 8 lanes.
 template <int S>
@@ -107,8 +85,7 @@ __device__ __forceinline__ void partials_one(double2 (&T)[FB][E], double2 (&B)[F
 }
 
 template <int E, class P, int I>
-__device__ __forceinline__ int apply_one(double2 (&T)[FB][E], double2 (&B)[FB][E], uint64_t act, const Rot& mine) {
-  if (!((act >> I) & 1)) return 0;
+__device__ __forceinline__ void apply_one(double2 (&T)[FB][E], double2 (&B)[FB][E], const Rot& mine) {
   Rot rt;  // row x plays a_i: x' = c x + s conj(e) y, y' = c y - s e x
   rt.c = readlane_d(mine.c, I);
   rt.ar = readlane_d(mine.ar, I);
@@ -116,7 +93,10 @@ __device__ __forceinline__ int apply_one(double2 (&T)[FB][E], double2 (&B)[FB][E
   rt.br = -rt.ar;
   rt.bi = rt.ai;
   pair_apply<E>(row<E, P::xr(I)>(T, B), row<E, P::yr(I)>(T, B), rt);
-  return 1;
+}
+template <int E, class P, int I>
+__device__ __forceinline__ void apply_if(double2 (&T)[FB][E], double2 (&B)[FB][E], uint32_t act, const Rot& mine) {
+  if ((act >> I) & 1) apply_one<E, P, I>(T, B, mine);
 }
 
 // Eight disjoint pairs: bxx, byy are the squared norms of lane l's pair
@@ -131,14 +111,26 @@ __device__ __forceinline__ int rot8(double2 (&T)[FB][E], double2 (&B)[FB][E], do
   const bool im_lane = (lane >> 3) & 1;
   const double br = im_lane ? other : x, bi = im_lane ? x : other;
   const bool need = pair_needs_rot(bxx, byy, br, bi, eps, floor);
-  const uint64_t act = __ballot(need) & 0xFFull;
+  const uint32_t act = (uint32_t)__ballot(need) & 0xFFu;
   *d = 0.0;
   if (act == 0) return 0;  // no pair rotates: skip the rotation formula
-  Rot mine{1.0, 0.0, 0.0, 0.0, 0.0};
-  double dn = 0.0;
-  pair_rot_coeffs(bxx, byy, br, bi, true, mine, &dn);
+  Rot mine;
+  double dn;
+  pair_rot_coeffs(bxx, byy, br, bi, mine, &dn);
   *d = need ? dn : 0.0;
-  return (apply_one<E, P, I>(T, B, act, mine) + ...);
+  const int rot = __popc(act);
+  if (E == 1 && rot > 4) {
+    // most pairs rotate: one straight run of all eight, the others by the
+    // identity, instead of a branch per pair (two registers per row leave the
+    // scheduler no room to interleave them)
+    mine.c = need ? mine.c : 1.0;
+    mine.ar = need ? mine.ar : 0.0;
+    mine.ai = need ? mine.ai : 0.0;
+    (apply_one<E, P, I>(T, B, mine), ...);
+  } else {
+    (apply_if<E, P, I>(T, B, act, mine), ...);
+  }
+  return rot;
 }
 
 template <int E, int S>
@@ -331,40 +323,81 @@ struct FusedShared {
   int ok;
 };
 
-// Eq. (C): C[(i,a)][(j,r)] = sum_{i'j'} Q[2i+j][2i'+j'] (B_q^{i'} B_{q+1}^{j'})[a][r]
-__device__ __forceinline__ void gate_theta(const FusedGate& g, int Dl, int Dm, int Dr) {
-  const int m = 2 * Dr;
-  double2 u[16];
+// Products of one wave on FP64 MFMA, operands straight from memory (L1/L2):
+// MT x NT tiles of 16 x 16, la(i, k) and lb(j, k) the complex elements of the
+// lane's row of A tile i and column of B tile j.  16 k at a time are in flight.
+template <int MT, int NT, class LA, class LB>
+__device__ __forceinline__ void wave_gemm(d4_t (&re)[MT][NT], d4_t (&im)[MT][NT], int K, LA la, LB lb) {
+  constexpr int U = 4;
+  const int lk = (threadIdx.x & 63) >> 4;
 #pragma unroll
-  for (int i = 0; i < 16; ++i) u[i] = g.u[i];
-  for (int idx = threadIdx.x; idx < Dl * Dr; idx += FW * 64) {
-    const int a = idx / Dr, r = idx - a * Dr;
-    const double2* x0 = g.bq + (size_t)a * Dm;
-    const double2* x1 = g.bq + (size_t)(Dl + a) * Dm;
-    const double2* y0 = g.bq1 + r;
-    const double2* y1 = g.bq1 + (size_t)Dm * Dr + r;
-    double2 t[4] = {make_double2(0.0, 0.0), make_double2(0.0, 0.0), make_double2(0.0, 0.0),
-                    make_double2(0.0, 0.0)};
-    for (int b = 0; b < Dm; ++b) {
-      const double2 a0 = x0[b], a1 = x1[b], b0 = y0[(size_t)b * Dr], b1 = y1[(size_t)b * Dr];
-      t[0].x += a0.x * b0.x - a0.y * b0.y; t[0].y += a0.x * b0.y + a0.y * b0.x;
-      t[1].x += a0.x * b1.x - a0.y * b1.y; t[1].y += a0.x * b1.y + a0.y * b1.x;
-      t[2].x += a1.x * b0.x - a1.y * b0.y; t[2].y += a1.x * b0.y + a1.y * b0.x;
-      t[3].x += a1.x * b1.x - a1.y * b1.y; t[3].y += a1.x * b1.y + a1.y * b1.x;
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j) re[i][j] = im[i][j] = d4_t{0.0, 0.0, 0.0, 0.0};
+  for (int k0 = 0; k0 < K; k0 += 4 * U) {
+    double2 a[MT][U], b[NT][U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = k0 + 4 * u + lk, kc = min(k, K - 1);
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+        const double2 v = la(i, kc);
+        a[i][u] = make_double2(k < K ? v.x : 0.0, k < K ? v.y : 0.0);
+      }
+#pragma unroll
+      for (int j = 0; j < NT; ++j) {
+        const double2 v = lb(j, kc);
+        b[j][u] = make_double2(k < K ? v.x : 0.0, k < K ? v.y : 0.0);
+      }
     }
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int u = 0; u < U; ++u)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) {
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+          re[i][j] = mfma_16x16x4(a[i][u].x, b[j][u].x, re[i][j]);
+          re[i][j] = mfma_16x16x4(-a[i][u].y, b[j][u].y, re[i][j]);
+          im[i][j] = mfma_16x16x4(a[i][u].x, b[j][u].y, im[i][j]);
+          im[i][j] = mfma_16x16x4(a[i][u].y, b[j][u].x, im[i][j]);
+        }
+  }
+}
+
+// Eq. (C): C[(i,a)][(j,r)] = sum_{i'j'} Q[2i+j][2i'+j'] (B_q^{i'} B_{q+1}^{j'})[a][r]
+// A wave takes 16 a x 16 r of all four (i', j'), so that the gate mixes its
+// accumulators.
+__device__ __forceinline__ void gate_theta(const FusedGate& g, int Dl, int Dm, int Dr) {
+  const int m = 2 * Dr;
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lr = lane & 15, lk = lane >> 4;
+  const int ta = (Dl + 15) / 16, tr = (Dr + 15) / 16;
+  for (int t = wv; t < ta * tr; t += FW) {
+    const int a0 = (t / tr) * 16, r0 = (t % tr) * 16;
+    const double2* pa = g.bq + (size_t)min(a0 + lr, Dl - 1) * Dm;
+    const double2* pb = g.bq1 + min(r0 + lr, Dr - 1);
+    d4_t re[2][2], im[2][2];
+    wave_gemm<2, 2>(
+        re, im, Dm, [&](int i, int k) { return pa[(size_t)i * Dl * Dm + k]; },
+        [&](int j, int k) { return pb[(size_t)j * Dm * Dr + (size_t)k * Dr]; });
+    const int r = r0 + lr;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int a = a0 + acc_row<double>(lk, v);
+      if (a >= Dl || r >= Dr) continue;
+#pragma unroll
+      for (int ij = 0; ij < 4; ++ij) {
         double2 acc = make_double2(0.0, 0.0);
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-          const double2 v = cmul(u[(2 * i + j) * 4 + k], t[k]);
-          acc.x += v.x;
-          acc.y += v.y;
+          const double2 u = g.u[ij * 4 + k];
+          const double tx = re[k >> 1][k & 1][v], ty = im[k >> 1][k & 1][v];
+          acc.x += u.x * tx - u.y * ty;
+          acc.y += u.x * ty + u.y * tx;
         }
-        g.c[(size_t)(i * Dl + a) * m + j * Dr + r] = acc;
+        g.c[(size_t)((ij >> 1) * Dl + a) * m + (ij & 1) * Dr + r] = acc;
       }
+    }
   }
   __syncthreads();
 }
@@ -531,37 +564,45 @@ __device__ __forceinline__ bool gate_svd(const FusedGate& g, double2* xs, FusedS
   return true;
 }
 
-// V^+ (k x m) = Z Q, Z (k x na) and Q (na x m) in memory, its rows then
-// orthonormalised in order (they are to eps sigma_1 / sigma_p) and stored as
-// the right site tensor [j][p][r].
+// V^+ (k x m) = Z Q, Z (k x na) and Q (na x m) in memory, as the right site
+// tensor [j][p][r].
+__device__ __forceinline__ void gate_vec(const FusedGate& g, const double2* z, const double2* q, int k, int na, int m,
+                                         int Dr) {
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lr = lane & 15, lk = lane >> 4;
+  const int tp = (k + 15) / 16, te = (m + 15) / 16;
+  for (int t = wv; t < tp * te; t += FW) {
+    const int p0 = (t / te) * 16, e0 = (t % te) * 16;
+    const double2* pa = z + (size_t)min(p0 + lr, k - 1) * na;
+    const double2* pb = q + min(e0 + lr, m - 1);
+    d4_t re[1][1], im[1][1];
+    wave_gemm<1, 1>(
+        re, im, na, [&](int, int s) { return pa[s]; }, [&](int, int s) { return pb[(size_t)s * m]; });
+    const int e = e0 + lr, j = e >= Dr ? 1 : 0;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int p = p0 + acc_row<double>(lk, v);
+      if (p < k && e < m)
+        g.bq1[((size_t)j * k + p) * Dr + e - j * Dr] = make_double2(re[0][0][v], im[0][0][v]);
+    }
+  }
+  __syncthreads();
+}
+
+// The rows of that V^+ (orthonormal to eps sigma_1 / sigma_p) orthonormalised
+// in order, in place.
 template <int E, int RPW>
-__device__ __forceinline__ void gate_vec(const FusedGate& g, double2* xs, const double2* z, const double2* q, int k,
-                                         int na, int m, int Dr) {
+__device__ __forceinline__ void gate_orth(const FusedGate& g, double2* xs, int k, int m, int Dr) {
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   double2 x[RPW][E];
 #pragma unroll
   for (int a = 0; a < RPW; ++a)
 #pragma unroll
-    for (int c = 0; c < E; ++c) x[a][c] = make_double2(0.0, 0.0);
-  for (int s = 0; s < na; ++s) {
-    double2 v[E];
-#pragma unroll
     for (int c = 0; c < E; ++c) {
-      const int e = lane + 64 * c;
-      v[c] = q[(size_t)s * m + min(e, m - 1)];
+      const int e = lane + 64 * c, p = a * FW + wv, j = e >= Dr ? 1 : 0;
+      x[a][c] = p < k && e < m ? g.bq1[((size_t)j * k + p) * Dr + e - j * Dr] : make_double2(0.0, 0.0);
     }
-#pragma unroll
-    for (int a = 0; a < RPW; ++a) {
-      const double2 w = z[(size_t)min(a * FW + wv, k - 1) * na + s];
-#pragma unroll
-      for (int c = 0; c < E; ++c) sub_mul(x[a][c], -w.x, -w.y, v[c]);
-    }
-  }
-#pragma unroll
-  for (int a = 0; a < RPW; ++a)
-#pragma unroll
-    for (int c = 0; c < E; ++c)
-      if (lane + 64 * c >= m || a * FW + wv >= k) x[a][c] = make_double2(0.0, 0.0);
+  __syncthreads();
   mgs_rows<E, FW, RPW>(
       x, k, xs, [](int, double) {},
       [&](int t, const double2* v) {
@@ -571,16 +612,51 @@ __device__ __forceinline__ void gate_vec(const FusedGate& g, double2* xs, const 
         }
       },
       [](int, int, double, double) {});
+  __syncthreads();
+}
+
+// Eq. (Bl): B_q[(i,a)][p] = inv sum_e C[(i,a)][e] conj(V^+[p][e]), V^+ from the
+// right site tensor [j][p][r]; 2 x 2 tiles per wave where there are enough.
+template <int MT, int NT>
+__device__ __forceinline__ void gate_left(const FusedGate& g, int n, int k, int m, int Dr, double inv) {
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lr = lane & 15, lk = lane >> 4;
+  const int tm = (n + 16 * MT - 1) / (16 * MT), tn = (k + 16 * NT - 1) / (16 * NT);
+  for (int t = wv; t < tm * tn; t += FW) {
+    const int i0 = (t / tn) * 16 * MT, p0 = (t % tn) * 16 * NT;
+    const double2* pa[MT];
+    const double2* pb[NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i) pa[i] = g.c + (size_t)min(i0 + 16 * i + lr, n - 1) * m;
+#pragma unroll
+    for (int j = 0; j < NT; ++j) pb[j] = g.bq1 + (size_t)min(p0 + 16 * j + lr, k - 1) * Dr;
+    const size_t half = (size_t)k * Dr - Dr;  // from element e of block 0 to element e of block 1
+    d4_t re[MT][NT], im[MT][NT];
+    wave_gemm<MT, NT>(
+        re, im, m, [&](int i, int e) { return pa[i][e]; },
+        [&](int j, int e) {
+          const double2 v = pb[j][e >= Dr ? half + e : e];
+          return make_double2(v.x, -v.y);
+        });
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+      for (int j = 0; j < NT; ++j)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+          const int row = i0 + 16 * i + acc_row<double>(lk, v), p = p0 + 16 * j + lr;
+          if (row < n && p < k)
+            g.bq[(size_t)row * k + p] = make_double2(re[i][j][v] * inv, im[i][j][v] * inv);
+        }
+  }
 }
 
 // One two-qubit gate by the whole workgroup; xs is the dynamic LDS (block
-// slots, rows in flight, then the staged V^+).  Every thread returns at the
-// same point.
+// slots, rows in flight).  Every thread returns at the same point.
 __device__ __forceinline__ void gate_any(const FusedGate& g, double2* xs, FusedShared& sh) {
   if (g.status[0] != 0) return;  // an earlier gate of this run failed: apply nothing
   const int Dl = g.dims[g.q], Dm = g.dims[g.q + 1], Dr = g.dims[g.q + 2];
   const int n = 2 * Dl, m = 2 * Dr;
-  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const double2* C = g.c;
   gate_theta(g, Dl, Dm, Dr);
   const int capk = min(g.cap_k, min(n, m));
@@ -616,9 +692,10 @@ __device__ __forceinline__ void gate_any(const FusedGate& g, double2* xs, FusedS
                    : gate_svd<2>(g, xs, sh, na, na, capk, load, store)))
       return;
     __syncthreads();
-    if (m <= 64) gate_vec<1, 8>(g, xs, f, q1, sh.k, na, m, Dr);
-    else if (sh.k <= 64) gate_vec<2, 8>(g, xs, f, q1, sh.k, na, m, Dr);
-    else gate_vec<2, 16>(g, xs, f, q1, sh.k, na, m, Dr);
+    gate_vec(g, f, q1, sh.k, na, m, Dr);
+    if (m <= 64) gate_orth<1, 8>(g, xs, sh.k, m, Dr);
+    else if (sh.k <= 64) gate_orth<2, 8>(g, xs, sh.k, m, Dr);
+    else gate_orth<2, 16>(g, xs, sh.k, m, Dr);
   } else {
     auto load = [&](int i, int e) {
       const double l = g.lam_l[i % Dl];
@@ -639,45 +716,9 @@ __device__ __forceinline__ void gate_any(const FusedGate& g, double2* xs, FusedS
   // ---- Eq. (Bl): lambda_{q+1} <- sigma_k / ||sigma_k||
   for (int p = threadIdx.x; p < k; p += FW * 64) g.lam_m[p] = sh.sig[sh.perm[p]] * inv;
 
-  // ---- Eq. (Bl): B_q[(i,a)][p] = inv sum_e C[(i,a)][e] conj(V^+[p][e]), 64 columns at a
-  // time, V^+ read back from the rows just stored in B_{q+1}
-  for (int p0 = 0; p0 < k; p0 += 64) {
-    __syncthreads();
-    for (int idx = threadIdx.x; idx < m * 64; idx += FW * 64) {
-      const int e = idx >> 6, pp = idx & 63, p = p0 + pp;
-      double2 v = make_double2(0.0, 0.0);
-      if (p < k) {
-        const int j = e >= Dr ? 1 : 0, r = e - j * Dr;
-        const double2 x = g.bq1[((size_t)j * k + p) * Dr + r];
-        v = make_double2(x.x * inv, -x.y * inv);
-      }
-      xs[e * FVS + pp] = v;
-    }
-    __syncthreads();
-    // wave w: rows 16w .. 16w+15 of B_q; lane: column p0 + lane
-    const int r0 = wv * 16;
-    if (r0 < n) {
-      double2 acc[16];
-#pragma unroll
-      for (int rr = 0; rr < 16; ++rr) acc[rr] = make_double2(0.0, 0.0);
-      for (int e = 0; e < m; ++e) {
-        const double2 v = xs[e * FVS + lane];
-#pragma unroll
-        for (int rr = 0; rr < 16; ++rr) {
-          const int row = min(r0 + rr, n - 1);
-          const double2 cv = C[(size_t)row * m + e];
-          acc[rr].x += cv.x * v.x - cv.y * v.y;
-          acc[rr].y += cv.x * v.y + cv.y * v.x;
-        }
-      }
-      const int p = p0 + lane;
-      if (p < k) {
-#pragma unroll
-        for (int rr = 0; rr < 16; ++rr)
-          if (r0 + rr < n) g.bq[(size_t)(r0 + rr) * k + p] = acc[rr];
-      }
-    }
-  }
+  __syncthreads();
+  if (n > 64 || k > 32) gate_left<2, 2>(g, n, k, m, Dr, inv);
+  else gate_left<1, 1>(g, n, k, m, Dr, inv);
   if (threadIdx.x == 0) g.dims[g.q + 1] = k;
 }
 
@@ -785,11 +826,7 @@ __global__ __launch_bounds__(FW * 64) void jacobi_small_kernel(const JacItem* it
   else jacobi_small_body<2>(it, max_sweeps, eps_scale, xs, s_rot);
 }
 
-size_t fused_lds_bytes() {
-  const size_t slots = (size_t)FW * FB * 64 * 2 * sizeof(double2);
-  const size_t vstage = (size_t)FMAXN * FVS * sizeof(double2);
-  return std::max(slots, vstage);
-}
+size_t fused_lds_bytes() { return (size_t)FW * FB * 64 * 2 * sizeof(double2); }
 
 hipError_t configure_fused_lds() {
   hipError_t e = hipFuncSetAttribute((const void*)gate2q_fused_kernel,
@@ -799,7 +836,7 @@ hipError_t configure_fused_lds() {
                           (int)fused_lds_bytes());
   if (e != hipSuccess) return e;
   return hipFuncSetAttribute((const void*)jacobi_small_kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
-                             (int)(FW * FB * 64 * 2 * sizeof(double2)));
+                             (int)fused_lds_bytes());
 }
 
 hipError_t launch_gate2q_fused(const FusedGate& g, int max_len, hipStream_t s) {
@@ -818,8 +855,8 @@ hipError_t launch_fused_step(const FusedRun* runs_dev, int n_runs, int64_t step,
 hipError_t launch_jacobi_small(const JacItem* items_dev, int items, int max_sweeps, double eps_scale,
                                hipStream_t s) {
   if (items <= 0) return hipSuccess;
-  hipLaunchKernelGGL(jacobi_small_kernel, dim3(items), dim3(FW * 64), FW * FB * 64 * 2 * sizeof(double2),
-                     s, items_dev, max_sweeps, eps_scale);
+  hipLaunchKernelGGL(jacobi_small_kernel, dim3(items), dim3(FW * 64), fused_lds_bytes(), s, items_dev,
+                     max_sweeps, eps_scale);
   return hipGetLastError();
 }
 

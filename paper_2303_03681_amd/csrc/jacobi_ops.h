@@ -13,11 +13,6 @@ struct Rot {
   double c, ar, ai, br, bi;  // x' = c x + (ar + i ai) y,  y' = c y + (br + i bi) x
 };
 
-// Algorithm 1's rotation from b_xx = x^+x, b_yy = y^+y and b_xy = x^+y of one
-// pair, in this lane; the row with the lower index plays a_i.  Returns false
-// when the pair is already orthogonal to the tolerance (|b_ij| <= eps
-// sqrt(b_ii b_jj) or <= floor).  *dn receives t |b_ij|, by which b_ii grows
-// and b_jj shrinks under the rotation.
 // Algorithm 1's rotation test: |b_ij| > floor and |b_ij| > eps sqrt(b_ii
 // b_jj), compared in squares (symmetric in the two rows).
 __device__ __forceinline__ bool pair_needs_rot(double bxx, double byy, double br, double bi, double eps,
@@ -26,27 +21,30 @@ __device__ __forceinline__ bool pair_needs_rot(double bxx, double byy, double br
   return mag2 > floor * floor && mag2 > eps * eps * (bxx * byy);
 }
 
-// The rotation itself, for a pair that passed pair_needs_rot.
-__device__ __forceinline__ void pair_rot_coeffs(double bxx, double byy, double br, double bi, bool x_is_i,
-                                                Rot& rt, double* dn) {
-  const double bii = x_is_i ? bxx : byy, bjj = x_is_i ? byy : bxx;
+// Algorithm 1's rotation from b_ii = bxx, b_jj = byy and b_ij of a pair that
+// passed the test, row x playing a_i.  With w = 1 / sqrt(1 + tau^2) the
+// formulas for t, c and s reduce to
+//   c^2 = (1 + |tau| w) / 2,   s = sign(tau) w / (2 c),   t = s / c,
+// three reciprocal square roots (of |b_ij|^2, 1 + tau^2 and c^2) where t and
+// c as written take two, a square root and a division.  |tau| is capped where
+// the rotation no longer changes anything.  *dn receives t |b_ij|, by which
+// b_ii grows and b_jj shrinks.
+__device__ __forceinline__ void pair_rot_coeffs(double bxx, double byy, double br, double bi, Rot& rt, double* dn) {
+  const double delta = bxx - byy;
   const double mag2 = br * br + bi * bi;
-  const double rinv = rsqrt(mag2);  // 1 / |b_ij|
-  const double tau = (bii - bjj) * (0.5 * rinv);
-  const double at = fabs(tau);
-  const double sg = tau >= 0.0 ? 1.0 : -1.0;
-  const double t = at > 1e100 ? sg * (0.5 / at) : sg / (at + sqrt(1.0 + tau * tau));
-  const double c = rsqrt(1.0 + t * t);
-  const double s = t * c;
-  const double er = br * rinv, ei = x_is_i ? bi * rinv : -bi * rinv;
-  // a_i' = c a_i + s conj(e) a_j,  a_j' = c a_j - s e a_i
-  const double pr = s * er, pi = -s * ei, qr = -s * er, qi = -s * ei;
-  rt.c = c;
-  rt.ar = x_is_i ? pr : qr;
-  rt.ai = x_is_i ? pi : qi;
-  rt.br = x_is_i ? qr : pr;
-  rt.bi = x_is_i ? qi : pi;
-  if (dn) *dn = t * (mag2 * rinv);
+  const double rinv = rsqrt_newton(mag2);  // 1 / |b_ij|
+  const double at = fmin(fabs(delta) * (0.5 * rinv), 1e100);
+  const double w = rsqrt_newton(fma(at, at, 1.0));
+  const double c2 = fma(0.5 * at, w, 0.5);
+  const double rc = rsqrt_newton(c2);  // 1 / c
+  const double s = delta >= 0.0 ? 0.5 * w * rc : -0.5 * w * rc;
+  rt.c = c2 * rc;
+  // e = b_ij / |b_ij|;  a_i' = c a_i + s conj(e) a_j,  a_j' = c a_j - s e a_i
+  rt.ar = s * (br * rinv);
+  rt.ai = -s * (bi * rinv);
+  rt.br = -rt.ar;
+  rt.bi = rt.ai;
+  *dn = s * rc * (mag2 * rinv);
 }
 
 // Partial sums of Re and Im of x^+y over this lane's elements.
@@ -67,12 +65,6 @@ __device__ __forceinline__ void pair_apply(double2 (&x)[E], double2 (&y)[E], con
     x[k] = make_double2(rt.c * a.x + (rt.ar * b.x - rt.ai * b.y), rt.c * a.y + (rt.ar * b.y + rt.ai * b.x));
     y[k] = make_double2(rt.c * b.x + (rt.br * a.x - rt.bi * a.y), rt.c * b.y + (rt.br * a.y + rt.bi * a.x));
   }
-}
-
-__device__ __forceinline__ double readlane_d(double x, int l) {
-  const int lo = __builtin_amdgcn_readlane(__double2loint(x), l);
-  const int hi = __builtin_amdgcn_readlane(__double2hiint(x), l);
-  return __hiloint2double(hi, lo);
 }
 
 }  // namespace mps

@@ -343,7 +343,7 @@ __device__ __forceinline__ bool jacobi_pair_tracked(RegVec<E>& x, double& nx, Re
   if (!pair_needs_rot(nx, ny, v[0], v[1], eps, floor)) return false;
   Rot rt;
   double dn;
-  pair_rot_coeffs(nx, ny, v[0], v[1], true, rt, &dn);
+  pair_rot_coeffs(nx, ny, v[0], v[1], rt, &dn);
   rt.c = wave_uniform(rt.c);
   rt.ar = wave_uniform(rt.ar);
   rt.ai = wave_uniform(rt.ai);
@@ -490,7 +490,7 @@ __global__ __launch_bounds__(IW * 64) void jacobi_reg_intra_kernel(const JacItem
 template <int E>
 __device__ __forceinline__ int rot2n(RegVec<E>& x0, RegVec<E>& y0, double& nx0, double& ny0,
                                      RegVec<E>& x1, RegVec<E>& y1, double& nx1, double& ny1,
-                                     bool x_is_i, double eps, double floor, int lane) {
+                                     double eps, double floor, int lane) {
   double v[4];  // v[2c + i]: component c (0 Re, 1 Im) of pair i
   pair_partials_xy<E>(x0.v, y0.v, v[0], v[2]);
   pair_partials_xy<E>(x1.v, y1.v, v[1], v[3]);
@@ -515,27 +515,29 @@ __device__ __forceinline__ int rot2n(RegVec<E>& x0, RegVec<E>& y0, double& nx0, 
   const double br = im_lane ? other : x, bi = im_lane ? x : other;
   const uint64_t act = __ballot(pair_needs_rot(bxx, byy, br, bi, eps, floor));
   if (!(act & 17ull)) return 0;  // neither pair rotates: skip the rotation formula
-  Rot mine{1.0, 0.0, 0.0, 0.0, 0.0};
-  double dn = 0.0;
-  pair_rot_coeffs(bxx, byy, br, bi, x_is_i, mine, &dn);
+  Rot mine;
+  double dn;
+  pair_rot_coeffs(bxx, byy, br, bi, mine, &dn);
   int rot = 0;
   // pair i is held (Re component) by lane 4 i
   if (act & 1ull) {
-    const Rot rt{readlane_d(mine.c, 0), readlane_d(mine.ar, 0), readlane_d(mine.ai, 0),
-                 readlane_d(mine.br, 0), readlane_d(mine.bi, 0)};
+    Rot rt{readlane_d(mine.c, 0), readlane_d(mine.ar, 0), readlane_d(mine.ai, 0), 0.0, 0.0};
+    rt.br = -rt.ar;
+    rt.bi = rt.ai;
     const double d = readlane_d(dn, 0);
     pair_apply<E>(x0.v, y0.v, rt);
-    nx0 += x_is_i ? d : -d;
-    ny0 -= x_is_i ? d : -d;
+    nx0 += d;
+    ny0 -= d;
     ++rot;
   }
   if (act & 16ull) {
-    const Rot rt{readlane_d(mine.c, 4), readlane_d(mine.ar, 4), readlane_d(mine.ai, 4),
-                 readlane_d(mine.br, 4), readlane_d(mine.bi, 4)};
+    Rot rt{readlane_d(mine.c, 4), readlane_d(mine.ar, 4), readlane_d(mine.ai, 4), 0.0, 0.0};
+    rt.br = -rt.ar;
+    rt.bi = rt.ai;
     const double d = readlane_d(dn, 4);
     pair_apply<E>(x1.v, y1.v, rt);
-    nx1 += x_is_i ? d : -d;
-    ny1 -= x_is_i ? d : -d;
+    nx1 += d;
+    ny1 -= d;
     ++rot;
   }
   return rot;
@@ -570,11 +572,10 @@ __global__ __launch_bounds__(CW * 64, 2) void jacobi_reg_cross_kernel(const JacI
     rv_load<E>(t1, c.it.w + (size_t)min(h1, n - 1) * m, h1 < n, m, lane);
   }
   double nr0 = rv_norm2<E>(r0), nr1 = rv_norm2<E>(r1), nt0 = rv_norm2<E>(t0), nt1 = rv_norm2<E>(t1);
-  const bool x_is_i = c.bp < c.bq;
   int rot = 0;
   for (int st = 0; st < CW; ++st) {
-    rot += rot2n<E>(r0, t0, nr0, nt0, r1, t1, nr1, nt1, x_is_i, c.eps, c.floor, lane);
-    rot += rot2n<E>(r0, t1, nr0, nt1, r1, t0, nr1, nt0, x_is_i, c.eps, c.floor, lane);
+    rot += rot2n<E>(r0, t0, nr0, nt0, r1, t1, nr1, nt1, c.eps, c.floor, lane);
+    rot += rot2n<E>(r0, t1, nr0, nt1, r1, t0, nr1, nt0, c.eps, c.floor, lane);
     if (st == CW - 1) break;
     double2* mine = slots + (size_t)wv * 2 * 64 * E;
     rv_to_lds<E>(t0, mine, lane);

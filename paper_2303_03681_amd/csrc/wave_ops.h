@@ -34,6 +34,28 @@ __device__ __forceinline__ double add_xor32(double v) {
   return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
 }
 
+// Barrier of the workgroup that orders LDS accesses only: __syncthreads() also
+// waits until every earlier store to memory has landed (hundreds of cycles in
+// a loop that stores a result per step).
+__device__ __forceinline__ void lds_barrier() {
+  asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+}
+
+// 1 / sqrt(x) for positive normal x: the hardware estimate and two Newton steps.
+__device__ __forceinline__ double rsqrt_newton(double x) {
+  double y = __builtin_amdgcn_rsq(x);
+  double h = 0.5 * x * y;
+  y = fma(y, fma(-h, y, 0.5), y);
+  h = 0.5 * x * y;
+  return fma(y, fma(-h, y, 0.5), y);
+}
+
+__device__ __forceinline__ double readlane_d(double x, int l) {
+  const int lo = __builtin_amdgcn_readlane(__double2loint(x), l);
+  const int hi = __builtin_amdgcn_readlane(__double2hiint(x), l);
+  return __hiloint2double(hi, lo);
+}
+
 // A wave-uniform value moved to scalar registers (it is identical in all lanes).
 __device__ __forceinline__ double wave_uniform(double x) {
   const int lo = __builtin_amdgcn_readfirstlane(__double2loint(x));
@@ -112,9 +134,30 @@ __device__ __forceinline__ void wave_sum_scalar(double (&v)[N], int lane) {
 #pragma unroll
   for (int i = 0; i < N; ++i) {
     const int l = i * (16 / N);  // lane bits 3.. hold the index of the sum
-    v[i] = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(x), l),
-                            __builtin_amdgcn_readlane(__double2loint(x), l));
+    v[i] = readlane_d(x, l);
   }
+}
+
+// One reduce-scatter stage: keep the half of v selected by this lane's bit,
+// add the partner's copy of it (the partner keeps the other half).
+template <int H>
+__device__ __forceinline__ double rs_pick(const double (&v)[2 * H], int j, bool hi, bool send) {
+  return (hi != send) ? v[H + j] : v[j];
+}
+
+// The full sum of v[l & 15] on lane l: lane bits 3, 2, 1, 0 by DPP, then full
+// sums over bits 4 and 5 (the same bits in every lane that holds a sum).
+__device__ __forceinline__ double reduce_scatter16(const double (&v)[16], int lane) {
+  double v8[8], v4[4], v2[2];
+  const bool h3 = (lane >> 3) & 1, h2 = (lane >> 2) & 1, h1 = (lane >> 1) & 1, h0 = lane & 1;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) v8[j] = rs_pick<8>(v, j, h3, false) + dpp_mov<0x140>(rs_pick<8>(v, j, h3, true));
+#pragma unroll
+  for (int j = 0; j < 4; ++j) v4[j] = rs_pick<4>(v8, j, h2, false) + dpp_mov<0x141>(rs_pick<4>(v8, j, h2, true));
+#pragma unroll
+  for (int j = 0; j < 2; ++j) v2[j] = rs_pick<2>(v4, j, h1, false) + dpp_mov<0x4E>(rs_pick<2>(v4, j, h1, true));
+  const double x = rs_pick<1>(v2, 0, h0, false) + dpp_mov<0xB1>(rs_pick<1>(v2, 0, h0, true));
+  return add_xor32(add_xor16(x));
 }
 
 __device__ __forceinline__ double2 cmul(double2 a, double2 b) {
