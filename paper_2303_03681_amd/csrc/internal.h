@@ -151,6 +151,17 @@ struct GramTile {         // one 64x64 block of some bond's G that a string need
   int item, r0, c0;
 };
 
+constexpr int kGramGroup = 4;
+struct GramGroup {        // up to kGramGroup pairs with one left environment
+  const void* l;
+  int first, count;       // their GramPair
+  int kdim;
+};
+struct GramPair {
+  const void* r;
+  double* g;              // out: Re sum_x L[x] R[x]
+};
+
 // ---------------------------------------------------------------- launchers
 hipError_t launch_init_product(double2* const* sites, double* const* lam0, const uint8_t* bits,
                                int n, hipStream_t s);
@@ -278,6 +289,10 @@ hipError_t launch_roots(const double* lam, void* lroot, void* rroot, int d, int 
 int gram_splits(int max_kdim);  // K splits of the closing-trace tiles
 hipError_t launch_gram(const GramItem* items_dev, const GramTile* tiles_dev, int n_tiles, int elem_bytes,
                        double* part, int splits, hipStream_t s);
+// whether a bond's traces are taken pair by pair rather than in 64 x 64 tiles
+bool gram_as_pairs(int64_t pairs, int64_t tiles, int kdim, int elem_bytes);
+hipError_t launch_gram_pairs(const GramGroup* groups_dev, const GramPair* pairs_dev, int groups, int elem_bytes,
+                             hipStream_t s);
 hipError_t launch_rows(const double* per_term, const int64_t* row_ptr, const int64_t* cols, const double* vals,
                        int64_t n_rows, double* out, hipStream_t s);
 hipError_t launch_gather(const double* g, const int64_t* gidx, const double2* nrm, double* per_term,

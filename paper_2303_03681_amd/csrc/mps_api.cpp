@@ -128,9 +128,9 @@ struct ExpectSetup {
   bool graph_chains = false;       // captured with the boundary-environment norm
   void* rows_buf = nullptr;        // CSR of mps_expect_pauli_rows and its output
   size_t rows_bytes = 0;
-  size_t gram_off = 0, tiles_off = 0;
-  int gram_items = 0, gram_tiles = 0;
-  double gram_flops = 0.0;  // dense tile work of the closing traces
+  size_t gram_off = 0, tiles_off = 0, groups_off = 0, pairs_off = 0;
+  int gram_items = 0, gram_tiles = 0, gram_groups = 0;
+  double gram_flops = 0.0;  // work of the closing traces as computed (whole tiles, single pairs)
   double pair_flops = 0.0;  // 4 D^2 per distinct (prefix, suffix) pair
   int64_t n_updates = 0;
 };
@@ -1443,6 +1443,8 @@ mps_status build_expect(mps_state* h, const mps_psum* ps, int prec) {
   for (int64_t k = 0; k < P.n_terms; ++k) by_bond[P.close_bond[k]].push_back(k);
   std::vector<GramItem> gram;
   std::vector<GramTile> tiles;
+  std::vector<GramGroup> groups;
+  std::vector<GramPair> pairs;
   std::vector<int64_t> gidx((size_t)P.n_terms);
   size_t gtot = 0;
   std::vector<std::vector<const void*>> lptrs, rptrs;
@@ -1462,10 +1464,12 @@ mps_status build_expect(mps_state* h, const mps_psum* ps, int prec) {
       pb.push_back(b.first->second);
     }
     const int nl = (int)lref.size(), nr = (int)rref.size();
+    int64_t n_distinct = 0;
     {  // the method's own work: Re Tr(L R) = 4 D^2 FLOPs per distinct pair
       std::unordered_set<int64_t> distinct;
       for (size_t q = 0; q < pa.size(); ++q) distinct.insert((int64_t)pa[q] * nr + pb[q]);
-      ex.pair_flops += 4.0 * (double)distinct.size() * D[c] * D[c];
+      n_distinct = (int64_t)distinct.size();
+      ex.pair_flops += 4.0 * (double)n_distinct * D[c] * D[c];
     }
     std::vector<int> lpos(nl), rpos(nr);
     for (int i = 0; i < nl; ++i) lpos[i] = i;
@@ -1494,21 +1498,43 @@ mps_status build_expect(mps_state* h, const mps_psum* ps, int prec) {
         }
       }
     }
+    const int item = (int)gram.size();
+    const int tcols = (nr + 63) / 64;
+    std::vector<char> used((size_t)((nl + 63) / 64) * tcols, 0);
+    int64_t n_used = 0;
+    for (size_t q = 0; q < pa.size(); ++q) {
+      char& u = used[(size_t)(lpos[pa[q]] / 64) * tcols + rpos[pb[q]] / 64];
+      n_used += !u;
+      u = 1;
+    }
+    // few needed pairs per tile: each pair by itself, the pairs of one prefix together
+    if (gram_as_pairs(n_distinct, n_used, D[c] * D[c], (int)el)) {
+      std::vector<std::pair<int64_t, int64_t>> key(pa.size());  // (pair, string)
+      for (size_t q = 0; q < pa.size(); ++q) key[q] = {(int64_t)pa[q] * nr + pb[q], by_bond[c][q]};
+      std::sort(key.begin(), key.end());
+      for (size_t q = 0; q < key.size(); ++q) {
+        if (q == 0 || key[q].first != key[q - 1].first) {
+          const int a = (int)(key[q].first / nr), b = (int)(key[q].first % nr);
+          const void* l = lref_ptr(lref[a]);
+          if (groups.empty() || groups.back().l != l || groups.back().count == kGramGroup ||
+              groups.back().kdim != D[c] * D[c])
+            groups.push_back(GramGroup{l, (int)pairs.size(), 0, D[c] * D[c]});
+          ++groups.back().count;
+          pairs.push_back(GramPair{rref_ptr(rref[b]), (double*)(uintptr_t)gtot});
+          ex.gram_flops += 4.0 * D[c] * D[c];
+          ++gtot;
+        }
+        gidx[key[q].second] = (int64_t)gtot - 1;
+      }
+      continue;
+    }
     std::vector<const void*> lp(nl), rp(nr);
     for (int i = 0; i < nl; ++i) lp[lpos[i]] = lref_ptr(lref[i]);
     for (int i = 0; i < nr; ++i) rp[rpos[i]] = rref_ptr(rref[i]);
-    const int item = (int)gram.size();
-    std::vector<char> used((size_t)((nl + 63) / 64) * ((nr + 63) / 64), 0);
-    const int tcols = (nr + 63) / 64;
-    for (size_t q = 0; q < pa.size(); ++q) {
-      const int a = lpos[pa[q]], b = rpos[pb[q]];
-      gidx[by_bond[c][q]] = (int64_t)gtot + (int64_t)a * nr + b;
-      char& u = used[(size_t)(a / 64) * tcols + b / 64];
-      if (!u) {
-        u = 1;
-        tiles.push_back(GramTile{item, (a / 64) * 64, (b / 64) * 64});
-      }
-    }
+    for (size_t q = 0; q < pa.size(); ++q)
+      gidx[by_bond[c][q]] = (int64_t)gtot + (int64_t)lpos[pa[q]] * nr + rpos[pb[q]];
+    for (size_t t = 0; t < used.size(); ++t)
+      if (used[t]) tiles.push_back(GramTile{item, (int)(t / tcols) * 64, (int)(t % tcols) * 64});
     GramItem gi{nullptr, nullptr, (double*)(uintptr_t)gtot, nl, nr, D[c] * D[c]};
     gram.push_back(gi);
     lptrs.push_back(std::move(lp));
@@ -1548,6 +1574,10 @@ mps_status build_expect(mps_state* h, const mps_psum* ps, int prec) {
   ex.gram_off = put(nullptr, gram.size() * sizeof(GramItem));
   ex.gram_tiles = (int)tiles.size();
   ex.tiles_off = put(tiles.data(), tiles.size() * sizeof(GramTile));
+  ex.gram_groups = (int)groups.size();
+  for (GramPair& pr : pairs) pr.g = ex.gbuf + (size_t)(uintptr_t)pr.g;
+  ex.groups_off = put(groups.data(), groups.size() * sizeof(GramGroup));
+  ex.pairs_off = put(pairs.data(), pairs.size() * sizeof(GramPair));
   // terms
   const size_t T = (size_t)P.n_terms;
   if (T > ex.terms_cap || !ex.per_term) {
@@ -1805,6 +1835,8 @@ mps_status expect_close(mps_state* h, int el, const double2* nrm, hipStream_t s)
   HIP_TRY(h, launch_gram((const GramItem*)((char*)ex.desc + ex.gram_off),
                          (const GramTile*)((char*)ex.desc + ex.tiles_off), ex.gram_tiles, el, ex.gpart,
                          ex.gram_split, s));
+  HIP_TRY(h, launch_gram_pairs((const GramGroup*)((char*)ex.desc + ex.groups_off),
+                               (const GramPair*)((char*)ex.desc + ex.pairs_off), ex.gram_groups, el, s));
   HIP_TRY(h, launch_gather(ex.gbuf, ex.gidx, nrm, ex.per_term, T, s));
   HIP_TRY(h, launch_energy(ex.per_term, ex.coeffs, T, ex.energy, s));
   return MPS_OK;
@@ -1838,6 +1870,8 @@ mps_status expect_impl(mps_state* h, const mps_psum* ps, int prec, double* energ
                            (const GramTile*)((char*)ex.desc + ex.tiles_off), ex.gram_tiles, el, ex.gpart,
                            ex.gram_split,
                            h->stream));
+    HIP_TRY(h, launch_gram_pairs((const GramGroup*)((char*)ex.desc + ex.groups_off),
+                                 (const GramPair*)((char*)ex.desc + ex.pairs_off), ex.gram_groups, el, h->stream));
     if (timed) {
       HIP_TRY(h, hipEventRecord(e, h->stream));
       h->tm.close_flops += ex.pair_flops;
