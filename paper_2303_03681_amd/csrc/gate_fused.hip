@@ -323,47 +323,6 @@ struct FusedShared {
   int ok;
 };
 
-// Products of one wave on FP64 MFMA, operands straight from memory (L1/L2):
-// MT x NT tiles of 16 x 16, la(i, k) and lb(j, k) the complex elements of the
-// lane's row of A tile i and column of B tile j.  16 k at a time are in flight.
-template <int MT, int NT, class LA, class LB>
-__device__ __forceinline__ void wave_gemm(d4_t (&re)[MT][NT], d4_t (&im)[MT][NT], int K, LA la, LB lb) {
-  constexpr int U = 4;
-  const int lk = (threadIdx.x & 63) >> 4;
-#pragma unroll
-  for (int i = 0; i < MT; ++i)
-#pragma unroll
-    for (int j = 0; j < NT; ++j) re[i][j] = im[i][j] = d4_t{0.0, 0.0, 0.0, 0.0};
-  for (int k0 = 0; k0 < K; k0 += 4 * U) {
-    double2 a[MT][U], b[NT][U];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int k = k0 + 4 * u + lk, kc = min(k, K - 1);
-#pragma unroll
-      for (int i = 0; i < MT; ++i) {
-        const double2 v = la(i, kc);
-        a[i][u] = make_double2(k < K ? v.x : 0.0, k < K ? v.y : 0.0);
-      }
-#pragma unroll
-      for (int j = 0; j < NT; ++j) {
-        const double2 v = lb(j, kc);
-        b[j][u] = make_double2(k < K ? v.x : 0.0, k < K ? v.y : 0.0);
-      }
-    }
-#pragma unroll
-    for (int u = 0; u < U; ++u)
-#pragma unroll
-      for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) {
-          re[i][j] = mfma_16x16x4(a[i][u].x, b[j][u].x, re[i][j]);
-          re[i][j] = mfma_16x16x4(-a[i][u].y, b[j][u].y, re[i][j]);
-          im[i][j] = mfma_16x16x4(a[i][u].x, b[j][u].y, im[i][j]);
-          im[i][j] = mfma_16x16x4(a[i][u].y, b[j][u].x, im[i][j]);
-        }
-  }
-}
-
 // Eq. (C): C[(i,a)][(j,r)] = sum_{i'j'} Q[2i+j][2i'+j'] (B_q^{i'} B_{q+1}^{j'})[a][r]
 // A wave takes 16 a x 16 r of all four (i', j'), so that the gate mixes its
 // accumulators.
@@ -377,7 +336,7 @@ __device__ __forceinline__ void gate_theta(const FusedGate& g, int Dl, int Dm, i
     const double2* pa = g.bq + (size_t)min(a0 + lr, Dl - 1) * Dm;
     const double2* pb = g.bq1 + min(r0 + lr, Dr - 1);
     d4_t re[2][2], im[2][2];
-    wave_gemm<2, 2>(
+    wave_gemm<double, 2, 2>(
         re, im, Dm, [&](int i, int k) { return pa[(size_t)i * Dl * Dm + k]; },
         [&](int j, int k) { return pb[(size_t)j * Dm * Dr + (size_t)k * Dr]; });
     const int r = r0 + lr;
@@ -576,7 +535,7 @@ __device__ __forceinline__ void gate_vec(const FusedGate& g, const double2* z, c
     const double2* pa = z + (size_t)min(p0 + lr, k - 1) * na;
     const double2* pb = q + min(e0 + lr, m - 1);
     d4_t re[1][1], im[1][1];
-    wave_gemm<1, 1>(
+    wave_gemm<double, 1, 1>(
         re, im, na, [&](int, int s) { return pa[s]; }, [&](int, int s) { return pb[(size_t)s * m]; });
     const int e = e0 + lr, j = e >= Dr ? 1 : 0;
 #pragma unroll
@@ -632,7 +591,7 @@ __device__ __forceinline__ void gate_left(const FusedGate& g, int n, int k, int 
     for (int j = 0; j < NT; ++j) pb[j] = g.bq1 + (size_t)min(p0 + 16 * j + lr, k - 1) * Dr;
     const size_t half = (size_t)k * Dr - Dr;  // from element e of block 0 to element e of block 1
     d4_t re[MT][NT], im[MT][NT];
-    wave_gemm<MT, NT>(
+    wave_gemm<double, MT, NT>(
         re, im, m, [&](int i, int e) { return pa[i][e]; },
         [&](int j, int e) {
           const double2 v = pb[j][e >= Dr ? half + e : e];

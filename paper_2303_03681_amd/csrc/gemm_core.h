@@ -245,6 +245,54 @@ __global__ __launch_bounds__(256) void cgemm_kernel(P p, int tiles_m, int tiles_
       }
 }
 
+// Products of one wave on MFMA, operands straight from memory (L1/L2, LDS):
+// MT x NT tiles of 16 x 16, la(i, k) and lb(j, k) the complex elements of the
+// lane's row of A tile i and column of B tile j.  16 k at a time are in
+// flight, and every element accumulates in the order of cgemm_kernel.
+template <typename T, int MT, int NT, class LA, class LB>
+__device__ __forceinline__ void wave_gemm(typename acc_of<T>::type (&re)[MT][NT],
+                                          typename acc_of<T>::type (&im)[MT][NT], int K, LA la, LB lb) {
+  using C2 = typename cplx_of<T>::type;
+  constexpr int U = 4;
+  const int lk = (threadIdx.x & 63) >> 4;
+#pragma unroll
+  for (int i = 0; i < MT; ++i)
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) re[i][j][v] = im[i][j][v] = T(0);
+  for (int k0 = 0; k0 < K; k0 += 4 * U) {
+    C2 a[MT][U], b[NT][U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int k = k0 + 4 * u + lk, kc = min(k, K - 1);
+#pragma unroll
+      for (int i = 0; i < MT; ++i) {
+        const C2 v = la(i, kc);
+        a[i][u].x = k < K ? v.x : T(0);
+        a[i][u].y = k < K ? v.y : T(0);
+      }
+#pragma unroll
+      for (int j = 0; j < NT; ++j) {
+        const C2 v = lb(j, kc);
+        b[j][u].x = k < K ? v.x : T(0);
+        b[j][u].y = k < K ? v.y : T(0);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u)
+#pragma unroll
+      for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+          re[i][j] = mfma_16x16x4(a[i][u].x, b[j][u].x, re[i][j]);
+          re[i][j] = mfma_16x16x4(-a[i][u].y, b[j][u].y, re[i][j]);
+          im[i][j] = mfma_16x16x4(a[i][u].x, b[j][u].y, im[i][j]);
+          im[i][j] = mfma_16x16x4(a[i][u].y, b[j][u].x, im[i][j]);
+        }
+  }
+}
+
 // Host-side launcher: grid = items x tiles, rounded up to a multiple of 8
 // for the XCD remap.
 template <int BM, int BN, int BK, class P>

@@ -139,6 +139,16 @@ struct EnvChild {         // L' = sum_s A^{s+} (ph_s X^{s xor flip})
   int letter;             // 0 I, 1 X, 2 Y, 3 Z
   int dl, dr;
   const C2* site;
+  const C2* l;            // the parent's environment (launch_env_small)
+};
+// A launch over several descriptor lists, each with its own site tensor and
+// dims: items par_end of the segment before .. par_end (chi_end) are this
+// segment's.  trans (launch_env_small only): site is [s][beta][alpha].
+struct EnvSeg {
+  const void* par;        // EnvParent<C2>
+  const void* chi;        // EnvChild<C2>
+  const void* site;
+  int par_end, chi_end, dl, dr, trans;
 };
 
 struct GramItem {         // G[a][b] = Re sum_x L_a[x] R_b[x]  (closing traces at one bond)
@@ -245,6 +255,12 @@ hipError_t launch_canon_carry_left(const CanonCarryLeftItem* items_dev, int item
 hipError_t launch_canon_right(const CanonRightItem* items_dev, int items, int max_dl, int max_r,
                               hipStream_t s);
 hipError_t launch_fro2(const double2* w, int count, double* out, hipStream_t s);
+struct RawCopy {          // one device-to-device copy of `words` doubles
+  const double* src;
+  double* dst;
+  long long words;
+};
+hipError_t launch_copy_list(const RawCopy* items, int count, long long max_words, hipStream_t s);
 hipError_t launch_copy(double2* dst, const double2* src, size_t count, hipStream_t s);
 hipError_t launch_fill_ident(double2* dst, int d, hipStream_t s);
 
@@ -265,6 +281,20 @@ hipError_t launch_env_gemm1_split(const EnvParent<float2>* items, int count, con
                                   int dr, int f16, hipStream_t s);
 hipError_t launch_env_gemm2_split(const EnvChild<float2>* items, int count, const float2* site, int dl,
                                   int dr, int f16, hipStream_t s);
+
+// One merged launch per GEMM half over segments (device array); max_dl, max_dr
+// size the grid.  prec: 0 c128, 1 c64, 2 split bf16, 3 split f16.
+struct EnvMerged {
+  const EnvSeg* segs;
+  int n_segs, n_par, n_chi, max_dl, max_dr;
+  EnvSeg one;             // the segment if there is one only (passed by value)
+};
+hipError_t launch_env_merged(const EnvMerged& m, int prec, hipStream_t s);
+// Both halves of every update of the segments in one launch, one workgroup per
+// child; dims at most kEnvSmall (c128 and c64; bitwise the GEMM launches).
+constexpr int kEnvSmall = 64;
+hipError_t configure_env_small();
+hipError_t launch_env_small(const EnvMerged& m, int prec, hipStream_t s);
 
 hipError_t launch_site_prepare(const double2* site, void* out_fwd, void* out_tr, int dl, int dr,
                                int elem_bytes, hipStream_t s);

@@ -1079,6 +1079,26 @@ hipError_t launch_copy(double2* dst, const double2* src, size_t count, hipStream
   return hipGetLastError();
 }
 
+// Several device-to-device copies in one launch: block row y takes item y,
+// 2048 doubles per block along x.
+__global__ __launch_bounds__(256) void copy_list_kernel(const RawCopy* items) {
+  const RawCopy it = items[blockIdx.y];
+  const long long base = (long long)blockIdx.x * 2048;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const long long i = base + 2 * (u * 256 + (int)threadIdx.x);
+    if (i + 1 < it.words) *(double2*)(it.dst + i) = *(const double2*)(it.src + i);
+    else if (i < it.words) it.dst[i] = it.src[i];
+  }
+}
+
+hipError_t launch_copy_list(const RawCopy* items, int count, long long max_words, hipStream_t s) {
+  if (count <= 0 || max_words <= 0) return hipSuccess;
+  if (count > 65535) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(copy_list_kernel, dim3(cdiv(max_words, 2048), count), dim3(256), 0, s, items);
+  return hipGetLastError();
+}
+
 // =================================================================== fixed scratch
 
 // Device scratch of the entry point that allocates nothing
@@ -1191,7 +1211,14 @@ struct EnvG1P {
   const EnvParent<C2>* items;
   const C2* site;
   int dl, dr;
+  const EnvSeg* segs = nullptr;
   __device__ Ctx context(int i) const {
+    if (segs) {
+      int s = 0, base = 0;
+      while (i >= segs[s].par_end) base = segs[s++].par_end;
+      const EnvParent<C2> e = ((const EnvParent<C2>*)segs[s].par)[i - base];
+      return Ctx{e.l, e.x, (const C2*)segs[s].site, segs[s].dl, segs[s].dr};
+    }
     const EnvParent<C2> e = items[i];
     if (e.site) return Ctx{e.l, e.x, e.site, e.dl, e.dr};
     return Ctx{e.l, e.x, site, dl, dr};
@@ -1248,7 +1275,14 @@ struct EnvG2P {
   const EnvChild<C2>* items;
   const C2* site;
   int dl, dr;
+  const EnvSeg* segs = nullptr;
   __device__ Ctx context(int i) const {
+    if (segs) {
+      int s = 0, base = 0;
+      while (i >= segs[s].chi_end) base = segs[s++].chi_end;
+      const EnvChild<C2> e = ((const EnvChild<C2>*)segs[s].chi)[i - base];
+      return Ctx{e.x, e.out, (const C2*)segs[s].site, segs[s].dl, segs[s].dr, e.letter};
+    }
     const EnvChild<C2> e = items[i];
     if (e.site) return Ctx{e.x, e.out, e.site, e.dl, e.dr, e.letter};
     return Ctx{e.x, e.out, site, dl, dr, e.letter};
@@ -1369,6 +1403,160 @@ hipError_t launch_env_gemm2_split(const EnvChild<float2>* items, int count, cons
   EnvG2P<float> p{items, site, dl, dr};
   return f16 ? launch_cgemm_split<_Float16, 64, 64>(p, count, dr, dr, s)
              : launch_cgemm_split<__bf16, 64, 64>(p, count, dr, dr, s);
+}
+
+// Merged launches: c128 and c64 take the 32 x 32 tile where 64 x 64 ones would
+// leave the chip idle (two per compute unit; at D = 64 and 50 items the two
+// halves take 11 + 21 us in 64 x 64 tiles).
+// A single segment goes by value: looking it up in memory first delays every
+// workgroup by two dependent loads (50 qubits D = 256 split-F16 3% slower).
+template <typename T>
+EnvG1P<T> env_p1(const EnvMerged& m) {
+  using C2 = typename cplx_of<T>::type;
+  if (m.n_segs > 1) return EnvG1P<T>{nullptr, nullptr, 0, 0, m.segs};
+  return EnvG1P<T>{(const EnvParent<C2>*)m.one.par, (const C2*)m.one.site, m.one.dl, m.one.dr};
+}
+template <typename T>
+EnvG2P<T> env_p2(const EnvMerged& m) {
+  using C2 = typename cplx_of<T>::type;
+  if (m.n_segs > 1) return EnvG2P<T>{nullptr, nullptr, 0, 0, m.segs};
+  return EnvG2P<T>{(const EnvChild<C2>*)m.one.chi, (const C2*)m.one.site, m.one.dl, m.one.dr};
+}
+
+template <typename T>
+hipError_t env_merged_t(const EnvMerged& m, hipStream_t s) {
+  const EnvG1P<T> p1 = env_p1<T>(m);
+  const EnvG2P<T> p2 = env_p2<T>(m);
+  const long long t1 = (long long)m.n_par * cdiv(m.max_dl, 64) * cdiv(2 * m.max_dr, 64);
+  const long long t2 = (long long)m.n_chi * cdiv(m.max_dr, 64) * cdiv(m.max_dr, 64);
+  const hipError_t e = launch_env_tile(p1, t1 < 512 ? 1 : 0, m.n_par, m.max_dl, 2 * m.max_dr, s);
+  return e != hipSuccess ? e : launch_env_tile(p2, t2 < 512 ? 1 : 0, m.n_chi, m.max_dr, m.max_dr, s);
+}
+
+template <typename L>
+hipError_t env_merged_split(const EnvMerged& m, hipStream_t s) {
+  const EnvG1P<float> p1 = env_p1<float>(m);
+  const EnvG2P<float> p2 = env_p2<float>(m);
+  const hipError_t e = launch_cgemm_split<L, 64, 64>(p1, m.n_par, m.max_dl, 2 * m.max_dr, s);
+  return e != hipSuccess ? e : launch_cgemm_split<L, 64, 64>(p2, m.n_chi, m.max_dr, m.max_dr, s);
+}
+
+hipError_t launch_env_merged(const EnvMerged& m, int prec, hipStream_t s) {
+  switch (prec) {
+    case 0: return env_merged_t<double>(m, s);
+    case 1: return env_merged_t<float>(m, s);
+    case 2: return env_merged_split<__bf16>(m, s);
+    case 3: return env_merged_split<_Float16>(m, s);
+    default: return hipErrorInvalidValue;
+  }
+}
+
+// A whole update L' = sum_s A^{s+} (phase X^{s^flip}), X = L [A^0 | A^1], of one
+// child per workgroup, X in LDS, operands straight from L2.  Small dims are
+// bound by launches and by the latency of a staged K loop (6 + 12 us for the
+// two GEMMs at D = 32); X is recomputed for every child of a parent, which
+// costs nothing while the launch has fewer children than the chip has
+// compute units.  Per element the same operations in the same order as
+// cgemm_kernel on EnvG1P and EnvG2P.
+template <typename T>
+__global__ __launch_bounds__(256) void env_small_kernel(const EnvSeg* segs) {
+  using C2 = typename cplx_of<T>::type;
+  using Acc = typename acc_of<T>::type;
+  extern __shared__ double2 env_lds[];
+  C2* X = (C2*)env_lds;  // [dl][2 dr + 1]
+  const int item = blockIdx.x;
+  int sg = 0, base = 0;
+  while (item >= segs[sg].chi_end) base = segs[sg++].chi_end;
+  const EnvSeg g = segs[sg];
+  const EnvChild<C2> ch = ((const EnvChild<C2>*)g.chi)[item - base];
+  const int dl = g.dl, dr = g.dr, ldx = 2 * dr + 1;
+  const C2* site = (const C2*)g.site;
+  const int sk = g.trans ? 1 : dr, sj = g.trans ? dl : 1;  // site[s][k][j]
+  const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lr = lane & 15, lk = lane >> 4;
+  const int tl = (dl + 15) / 16, tr = (dr + 15) / 16;
+  for (int t = wv; t < tl * tr; t += 4) {
+    const int i0 = (t / tr) * 16, j0 = (t % tr) * 16;
+    const C2* pa = ch.l + (size_t)min(i0 + lr, dl - 1) * dl;
+    const C2* pb = site + (size_t)min(j0 + lr, dr - 1) * sj;
+    Acc re[1][2], im[1][2];
+    wave_gemm<T, 1, 2>(
+        re, im, dl, [&](int, int k) { return pa[k]; },
+        [&](int s, int k) { return pb[(size_t)s * dl * dr + (size_t)k * sk]; });
+    const int j = j0 + lr;
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int i = i0 + acc_row<T>(lk, v);
+        if (i < dl && j < dr) {
+          C2 o;
+          o.x = re[0][s][v];
+          o.y = im[0][s][v];
+          X[(size_t)i * ldx + s * dr + j] = o;
+        }
+      }
+  }
+  __syncthreads();
+  const int flip = (ch.letter == 1 || ch.letter == 2) ? 1 : 0;
+  for (int t = wv; t < tr * tr; t += 4) {
+    const int i0 = (t / tr) * 16, j0 = (t % tr) * 16;
+    const C2* pa = site + (size_t)min(i0 + lr, dr - 1) * sj;
+    const C2* pb = X + min(j0 + lr, dr - 1);
+    Acc re[1][1], im[1][1];
+    wave_gemm<T, 1, 1>(
+        re, im, 2 * dl,
+        [&](int, int k) {
+          const int s = k >= dl, a = k - s * dl;
+          C2 v = pa[(size_t)s * dl * dr + (size_t)a * sk];
+          v.y = -v.y;
+          return v;
+        },
+        [&](int, int k) {
+          const int s = k >= dl, a = k - s * dl;
+          const C2 v = pb[(size_t)a * ldx + (s ^ flip) * dr];
+          C2 o = v;
+          if (ch.letter == 2) {  // Y: s=0 -> -i X^1, s=1 -> +i X^0
+            o.x = s == 0 ? v.y : -v.y;
+            o.y = s == 0 ? -v.x : v.x;
+          } else if (ch.letter == 3 && s == 1) {
+            o.x = -v.x;
+            o.y = -v.y;
+          }
+          return o;
+        });
+    const int j = j0 + lr;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+      const int i = i0 + acc_row<T>(lk, v);
+      if (i < dr && j < dr) {
+        C2 o;
+        o.x = re[0][0][v];
+        o.y = im[0][0][v];
+        ch.out[(size_t)i * dr + j] = o;
+      }
+    }
+  }
+}
+
+hipError_t configure_env_small() {
+  const int bytes = kEnvSmall * (2 * kEnvSmall + 1) * (int)sizeof(double2);
+  const hipError_t e = hipFuncSetAttribute((const void*)env_small_kernel<double>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+  return e != hipSuccess ? e
+                         : hipFuncSetAttribute((const void*)env_small_kernel<float>,
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, bytes / 2);
+}
+
+hipError_t launch_env_small(const EnvMerged& m, int prec, hipStream_t s) {
+  if (m.n_chi <= 0) return hipSuccess;
+  if (m.max_dl > kEnvSmall || m.max_dr > kEnvSmall || prec > 1) return hipErrorInvalidValue;
+  const size_t el = (size_t)m.max_dl * (2 * m.max_dr + 1);
+  if (prec == 0)
+    hipLaunchKernelGGL(env_small_kernel<double>, dim3(m.n_chi), dim3(256), el * sizeof(double2), s, m.segs);
+  else
+    hipLaunchKernelGGL(env_small_kernel<float>, dim3(m.n_chi), dim3(256), el * sizeof(float2), s, m.segs);
+  return hipGetLastError();
 }
 
 // Site tensor in the environment precision (fwd, may be null) and its

@@ -88,7 +88,6 @@ struct ExpectSetup {
   size_t xbuf_bytes = 0;
   void* desc = nullptr;        // all descriptors
   size_t desc_bytes = 0;
-  std::vector<char> host_desc; // host copy of the descriptors (environment launches of several MPSs)
   int64_t plan_terms = 0;
   double* gbuf = nullptr;      // closing traces
   size_t gbuf_count = 0;
@@ -121,6 +120,7 @@ struct ExpectSetup {
     void* rroot;
   };
   std::vector<RootFill> roots;
+  bool x_apart = false;            // the two passes have GEMM1 outputs of their own
   bool fwd128 = false;             // c128 sites copied to fixed buffers (graph replay)
   // captured device sequence (environment launches, closes, gather, energy)
   hipGraph_t graph = nullptr;
@@ -325,6 +325,7 @@ mps_status ensure_lds(mps_state* h) {
   if (b > 152 * 1024) b = 152 * 1024;
   HIP_TRY(h, configure_jacobi_lds(b));
   HIP_TRY(h, configure_fused_lds());
+  HIP_TRY(h, configure_env_small());
   g_lds_budget = b;
   return MPS_OK;
 }
@@ -1160,6 +1161,8 @@ mps_status ensure_chain_buffers(mps_state* h) {
       lch[q] = Ch{cx, lc + off[q + 1], 0};
       rp[q] = P{rc + off[q + 1], cxr};
       rch[q] = Ch{cxr, rc + off[q], 0};
+      lch[q].l = lp[q].l;
+      rch[q].l = rp[q].l;
     }
     const double2 one = make_double2(1.0, 0.0);
     hipError_t e = hipMemcpy(desc, host.data(), host.size(), hipMemcpyHostToDevice);
@@ -1358,8 +1361,12 @@ mps_status build_expect(mps_state* h, const mps_psum* ps, int prec) {
     }
     return need;
   };
-  const size_t x_elems = std::max<size_t>(1, std::max(x_need(P.left), x_need(P.right)));
-  if ((st = grow(&ex.xbuf, ex.xbuf_bytes, x_elems * el)) != MPS_OK) return st;
+  // the two passes apart, so that their launches can be merged; shared if there is no room
+  const size_t x_left = x_need(P.left), x_right = x_need(P.right);
+  ex.x_apart = grow(&ex.xbuf, ex.xbuf_bytes, std::max<size_t>(1, x_left + x_right) * el) == MPS_OK;
+  if (!ex.x_apart &&
+      (st = grow(&ex.xbuf, ex.xbuf_bytes, std::max<size_t>(1, std::max(x_left, x_right)) * el)) != MPS_OK)
+    return st;
   char* poolp = (char*)ex.pool;
   char* sitep = (char*)ex.sites;
   auto lref_ptr = [&](int32_t ref) -> char* {
@@ -1411,10 +1418,12 @@ mps_status build_expect(mps_state* h, const mps_psum* ps, int prec) {
             if ((int)par.size() == chunk_cap) break;
             last_parent = nodes[b].parent;
             char* pp = left ? lref_ptr(last_parent) : rref_ptr(last_parent);
-            par.push_back({(const double2*)pp, (double2*)((char*)ex.xbuf + par.size() * xper * el)});
+            const size_t x0 = left || !ex.x_apart ? 0 : x_left;
+            par.push_back({(const double2*)pp, (double2*)((char*)ex.xbuf + (x0 + par.size() * xper) * el)});
           }
           chi.push_back({(const double2*)par.back().x, (double2*)(poolp + off[b] * el),
                          (int)nodes[b].letter});
+          chi.back().l = par.back().l;
           ++b;
         }
         ExpectSetup::EnvLaunch L;
@@ -1608,7 +1617,6 @@ mps_status build_expect(mps_state* h, const mps_psum* ps, int prec) {
   }
   if (!gram.empty()) std::memcpy(host.data() + ex.gram_off, gram.data(), gram.size() * sizeof(GramItem));
   HIP_TRY(h, hipMemcpy(ex.desc, host.data(), host.size(), hipMemcpyHostToDevice));
-  ex.host_desc = host;
   ex.plan_terms = T;
   if (T) {
     HIP_TRY(h, hipMemcpy(ex.gidx, gidx.data(), T * sizeof(int64_t), hipMemcpyHostToDevice));
@@ -1787,31 +1795,237 @@ struct RowsSpec {
 
 // pair_out (device, may be null) receives the energy's compensated (sum,
 // error) pair, for sums over several plans added on the device.
+// Descriptor lists of one expectation call (one or several states), laid out in
+// one upload: the sites to prepare, the boundary-chain steps of small states,
+// the roots to copy, and the environment updates of equal depth -- of every
+// state and, where their GEMM1 outputs are apart, of both passes -- as merged
+// launches.
+constexpr int64_t kMergeTiles = 1024;  // 64 x 64 tiles of a launch that fills the chip
+constexpr int kEnvFused = 32;  // updates up to these dims run as one launch (launch_env_small)
+
+struct CallLists {
+  std::vector<char> blob;
+  char* dev = nullptr;
+  std::vector<EnvMerged> chain, env;  // segs: offsets into the blob until placed
+  struct Step {  // chain step of states with larger bonds: transposed sites, then both GEMM halves
+    size_t off;
+    int n, max;
+    EnvMerged gemms;
+  };
+  std::vector<Step> chain_gemms;
+  size_t prep_off = 0, copy_off = 0;
+  int n_prep = 0, prep_max = 0, n_copy = 0;
+  long long copy_max = 0;
+
+  size_t put(const void* src, size_t bytes) {
+    const size_t o = blob.size();
+    blob.resize(o + ((bytes + 255) & ~(size_t)255));
+    if (src && bytes) std::memcpy(blob.data() + o, src, bytes);
+    return o;
+  }
+  EnvMerged put_segs(const std::vector<EnvSeg>& v) {
+    EnvMerged m{};
+    m.n_segs = (int)v.size();
+    m.n_par = v.back().par_end;
+    m.n_chi = v.back().chi_end;
+    m.one = v.front();
+    for (const EnvSeg& g : v) {
+      m.max_dl = std::max(m.max_dl, g.dl);
+      m.max_dr = std::max(m.max_dr, g.dr);
+    }
+    m.segs = (const EnvSeg*)(uintptr_t)put(v.data(), v.size() * sizeof(EnvSeg));
+    return m;
+  }
+  EnvMerged placed(EnvMerged m) const {
+    m.segs = (const EnvSeg*)(dev + (uintptr_t)m.segs);
+    return m;
+  }
+};
+
+bool small_bonds(const mps_state* h) {
+  for (int d : h->dims)
+    if (d > kEnvSmall) return false;
+  return true;
+}
+
+// Lists of `count` states (their plans built): stale[i] says whose boundary
+// chains are to be computed here (1: all bonds small, 2: as GEMMs), rmin[i]
+// down to which bond.
+CallLists call_lists(mps_state* const* hs, int count, const std::vector<int>& stale, const std::vector<int>& rmin) {
+  CallLists c;
+  using P = EnvParent<double2>;
+  using Ch = EnvChild<double2>;
+  std::vector<PrepItem> pv;
+  std::vector<CopyItem> cv;
+  int max_n = 0;
+  for (int i = 0; i < count; ++i) {
+    mps_state* h = hs[i];
+    max_n = std::max(max_n, h->n);
+    for (int q = 0; q < h->n; ++q) {
+      const auto& pr = h->ex.prep[q];
+      pv.push_back(PrepItem{h->cur(q), pr.fwd, pr.tr, pr.dl, pr.dr});
+      c.prep_max = std::max(c.prep_max, 2 * pr.dl * pr.dr);
+    }
+    if (h->canonical) continue;
+    for (const auto& r : h->ex.roots) {
+      const long long cnt = (long long)r.d * r.d;
+      if (r.lroot) cv.push_back(CopyItem{h->d_lchain + h->chain_off[r.bond], r.lroot, cnt});
+      if (r.rroot) cv.push_back(CopyItem{h->d_rchain + h->chain_off[r.bond], r.rroot, cnt});
+      c.copy_max = std::max(c.copy_max, cnt);
+    }
+  }
+  c.n_prep = (int)pv.size();
+  c.prep_off = c.put(pv.data(), pv.size() * sizeof(PrepItem));
+  c.n_copy = (int)cv.size();
+  c.copy_off = c.put(cv.data(), cv.size() * sizeof(CopyItem));
+  auto add = [](std::vector<EnvSeg>& v, const void* par, int n_par, const void* chi, int n_chi, const void* site,
+                int dl, int dr, int trans) {
+    const int p0 = v.empty() ? 0 : v.back().par_end, c0 = v.empty() ? 0 : v.back().chi_end;
+    v.push_back(EnvSeg{par, chi, site, p0 + n_par, c0 + n_chi, dl, dr, trans});
+  };
+  // boundary chains: step t of the left and of the right chains of every state
+  for (int kind = 1; kind <= 2; ++kind)
+    for (int t = 0; t < max_n; ++t) {
+      std::vector<EnvSeg> v;
+      std::vector<PrepItem> tv;
+      int most = 0;
+      for (int i = 0; i < count; ++i) {
+        mps_state* h = hs[i];
+        if (stale[i] != kind || t >= h->n) continue;
+        const P* lp = (const P*)h->d_chaindesc;
+        const Ch* lch = (const Ch*)(lp + h->n);
+        const P* rp = (const P*)(lch + h->n);
+        const Ch* rch = (const Ch*)(rp + h->n);
+        const int q = h->n - 1 - t;
+        add(v, lp + t, 1, lch + t, 1, h->cur(t), h->dims[t], h->dims[t + 1], 0);
+        if (q < rmin[i]) continue;
+        add(v, rp + q, 1, rch + q, 1, kind == 1 ? h->cur(q) : h->d_chaintr, h->dims[q + 1], h->dims[q], kind == 1);
+        if (kind == 2) {
+          tv.push_back(PrepItem{h->cur(q), nullptr, h->d_chaintr, h->dims[q], h->dims[q + 1]});
+          most = std::max(most, 2 * h->dims[q] * h->dims[q + 1]);
+        }
+      }
+      if (v.empty()) continue;
+      if (kind == 1) {
+        c.chain.push_back(c.put_segs(v));
+      } else {
+        const size_t off = c.put(tv.data(), tv.size() * sizeof(PrepItem));
+        c.chain_gemms.push_back({off, (int)tv.size(), most, c.put_segs(v)});
+      }
+    }
+  // environment updates
+  bool apart = true;
+  for (int i = 0; i < count; ++i) apart = apart && hs[i]->ex.x_apart;
+  for (int pass = 0; pass < (apart ? 1 : 2); ++pass) {
+    size_t depth = 0;
+    for (int i = 0; i < count; ++i) {
+      if (apart || pass == 0) depth = std::max(depth, hs[i]->ex.left_launches.size());
+      if (apart || pass == 1) depth = std::max(depth, hs[i]->ex.right_launches.size());
+    }
+    for (size_t t = 0; t < depth; ++t) {
+      std::vector<EnvSeg> v;
+      // launches that fill the chip by themselves stay apart (merged, the two
+      // passes compete for the caches: 28 qubits D = 512 layer 219 -> 227 ms)
+      int64_t tiles[2] = {0, 0};
+      for (int i = 0; i < count; ++i)
+        for (int side = 0; side < 2; ++side) {
+          const auto& ls = side == 0 ? hs[i]->ex.left_launches : hs[i]->ex.right_launches;
+          if (t < ls.size()) tiles[side] += (int64_t)ls[t].n_children * ((ls[t].dr + 63) / 64) * ((ls[t].dr + 63) / 64);
+        }
+      const bool alone = apart && std::max(tiles[0], tiles[1]) > kMergeTiles;
+      for (int side = 0; side < 2; ++side) {
+        if (!apart && side != pass) continue;
+        for (int i = 0; i < count; ++i) {
+          mps_state* h = hs[i];
+          const char* db = (const char*)h->ex.desc;
+          const auto& ls = side == 0 ? h->ex.left_launches : h->ex.right_launches;
+          if (t >= ls.size()) continue;
+          const ExpectSetup::EnvLaunch& L = ls[t];
+          const void* site = !L.left ? h->ex.prep[L.site].tr
+                                     : (h->ex.prep[L.site].fwd ? h->ex.prep[L.site].fwd : (const void*)h->cur(L.site));
+          add(v, db + L.parents_off, L.n_parents, db + L.children_off, L.n_children, site, L.dl, L.dr, 0);
+        }
+        if (alone && !v.empty()) {
+          c.env.push_back(c.put_segs(v));
+          v.clear();
+        }
+      }
+      if (!v.empty()) c.env.push_back(c.put_segs(v));
+    }
+  }
+  return c;
+}
+
+// Site preparation, boundary chains and roots of the lists' states on s.
+mps_status run_set_up(mps_state* drv, const CallLists& c, mps_state* const* hs, int count, int el, hipStream_t s) {
+  HIP_TRY(drv, launch_site_prepare_list((const PrepItem*)(c.dev + c.prep_off), c.n_prep, c.prep_max, el, s));
+  for (const EnvMerged& m : c.chain) HIP_TRY(drv, launch_env_small(c.placed(m), MPS_PREC_C128, s));
+  for (const CallLists::Step& t : c.chain_gemms) {
+    HIP_TRY(drv, launch_site_prepare_list((const PrepItem*)(c.dev + t.off), t.n, t.max, 16, s));
+    HIP_TRY(drv, launch_env_merged(c.placed(t.gemms), MPS_PREC_C128, s));
+  }
+  HIP_TRY(drv, launch_root_copy_list((const CopyItem*)(c.dev + c.copy_off), c.n_copy, c.copy_max, el, s));
+  for (int i = 0; i < count; ++i)
+    if (hs[i]->canonical)
+      for (const auto& r : hs[i]->ex.roots)
+        HIP_TRY(drv, launch_roots(hs[i]->lcur(r.bond), r.lroot, r.rroot, r.d, el, s));
+  return MPS_OK;
+}
+
+// One merged depth: fused updates while the dims are small (c128 and c64), else
+// one launch per GEMM half.
+hipError_t run_env_merged(const EnvMerged& m, int prec, hipStream_t s) {
+  if (prec <= MPS_PREC_C64 && m.max_dl <= kEnvFused && m.max_dr <= kEnvFused) return launch_env_small(m, prec, s);
+  return launch_env_merged(m, prec, s);
+}
+
 // The expectation's set-up on h's stream: the plan's device layout, the site
 // tensors in environment precision (and transposed), the trie roots.  *nrm:
 // the device value <psi|psi> to divide by (boundary environments), or null in
-// exact canonical form.
-mps_status expect_open(mps_state* h, const mps_psum* ps, int prec, const double2** nrm_out) {
+// exact canonical form.  *lists: the call's merged launches (env empty when
+// the launches are to run one by one: tuned or forced tiles, graph capture, no
+// room for the lists).
+mps_status expect_open(mps_state* h, const mps_psum* ps, int prec, const double2** nrm_out, CallLists* lists) {
   mps_status st;
   if ((st = build_expect(h, ps, prec)) != MPS_OK) return st;
   ExpectSetup& ex = h->ex;
   const int el = prec == MPS_PREC_C128 ? 16 : 8;
-  // layer 0: site tensors in environment precision and transposed; trie roots
-  for (int q = 0; q < h->n; ++q)
-    HIP_TRY(h, launch_site_prepare(h->cur(q), ex.prep[q].fwd, ex.prep[q].tr, ex.prep[q].dl,
-                                   ex.prep[q].dr, el, h->stream));
   // Exact canonical form: diag(lambda^2) and identity roots, unit norm.  After
   // gates (truncated Hastings updates leave the sites only nearly
   // right-orthonormal and the norm near 1): identity environments from both
   // boundaries and division by <psi|psi>, the same values without a sweep.
   const bool chains = !h->canonical;
-  const double2* nrm = nullptr;
+  int rmin = h->n;
+  bool stale = false;
   if (chains) {
-    int rmin = h->n;
+    if ((st = ensure_chain_buffers(h)) != MPS_OK) return st;
     for (const auto& r : ex.roots)
       if (r.rroot) rmin = std::min(rmin, r.bond);
+    stale = !(h->chain_version == h->version && h->chain_rmin <= rmin);
+  }
+  *nrm_out = chains ? h->d_lchain + h->chain_off[h->n] : nullptr;
+  const bool merged = !h->autotune && h->forced_tile < 0 && !h->graphs;
+  const bool small = stale && small_bonds(h);
+  *lists = call_lists(&h, 1, {small ? 1 : 0}, {rmin});
+  if (!merged) lists->env.clear();
+  if (ensure_desc(h, lists->blob.size()) == MPS_OK) {
+    lists->dev = (char*)h->d_desc;
+    if ((st = upload(h, lists->dev, lists->blob.data(), lists->blob.size())) != MPS_OK) return st;
+    if (stale && !small && (st = identity_chains(h, rmin)) != MPS_OK) return st;
+    if ((st = run_set_up(h, *lists, &h, 1, el, h->stream)) != MPS_OK) return st;
+    if (small) {
+      h->chain_version = h->version;
+      h->chain_rmin = rmin;
+    }
+    return MPS_OK;
+  }
+  // one launch per site and root
+  lists->env.clear();
+  for (int q = 0; q < h->n; ++q)
+    HIP_TRY(h, launch_site_prepare(h->cur(q), ex.prep[q].fwd, ex.prep[q].tr, ex.prep[q].dl,
+                                   ex.prep[q].dr, el, h->stream));
+  if (chains) {
     if ((st = identity_chains(h, rmin)) != MPS_OK) return st;
-    nrm = h->d_lchain + h->chain_off[h->n];
     for (const auto& r : ex.roots) {
       const size_t cnt = (size_t)r.d * r.d;
       if (r.lroot)
@@ -1823,7 +2037,6 @@ mps_status expect_open(mps_state* h, const mps_psum* ps, int prec, const double2
     for (const auto& r : ex.roots)
       HIP_TRY(h, launch_roots(h->lcur(r.bond), r.lroot, r.rroot, r.d, el, h->stream));
   }
-  *nrm_out = nrm;
   return MPS_OK;
 }
 
@@ -1847,7 +2060,8 @@ mps_status expect_impl(mps_state* h, const mps_psum* ps, int prec, double* energ
   mps_status st;
   const double t0 = now_ms();
   const double2* nrm = nullptr;
-  if ((st = expect_open(h, ps, prec, &nrm)) != MPS_OK) return st;
+  CallLists lists;
+  if ((st = expect_open(h, ps, prec, &nrm, &lists)) != MPS_OK) return st;
   ExpectSetup& ex = h->ex;
   const int el = prec == MPS_PREC_C128 ? 16 : 8;
   const bool chains = nrm != nullptr;
@@ -1859,12 +2073,24 @@ mps_status expect_impl(mps_state* h, const mps_psum* ps, int prec, double* energ
   // are captured once per (plan, precision, bond dims, root kind) and replayed.
   auto device_sequence = [&](bool capturing) -> mps_status {
     mps_status s2;
-    for (const auto& L : ex.left_launches)
-      if ((s2 = run_env_launch(h, L, prec, capturing ? nullptr : &pending, capturing)) != MPS_OK) return s2;
-    for (const auto& L : ex.right_launches)
-      if ((s2 = run_env_launch(h, L, prec, capturing ? nullptr : &pending, capturing)) != MPS_OK) return s2;
     hipEvent_t b = nullptr, e = nullptr;
     const bool timed = h->timing && !capturing;
+    for (const EnvMerged& m : lists.env) {
+      if (timed && (s2 = timed_begin(h, h->ev_env, h->ev_env_used, b, e)) != MPS_OK) return s2;
+      HIP_TRY(h, run_env_merged(lists.placed(m), prec, h->stream));
+      if (timed) {
+        HIP_TRY(h, hipEventRecord(e, h->stream));
+        h->tm.env_launches += 2;
+      }
+    }
+    for (int pass = 0; pass < 2; ++pass)
+      for (const auto& L : pass == 0 ? ex.left_launches : ex.right_launches) {
+        if (!lists.env.empty()) {
+          if (timed) h->tm.env_flops += L.flops;
+        } else if ((s2 = run_env_launch(h, L, prec, capturing ? nullptr : &pending, capturing)) != MPS_OK) {
+          return s2;
+        }
+      }
     if (timed && (s2 = timed_begin(h, h->ev_close, h->ev_close_used, b, e)) != MPS_OK) return s2;
     HIP_TRY(h, launch_gram((const GramItem*)((char*)ex.desc + ex.gram_off),
                            (const GramTile*)((char*)ex.desc + ex.tiles_off), ex.gram_tiles, el, ex.gpart,
@@ -1982,12 +2208,10 @@ mps_status expect_multi_impl(mps_state* const* hs, const mps_psum* const* ps, in
   mps_status st;
   std::vector<const double2*> nrm(count, nullptr);
   std::vector<int> rmin(count, 0), stale(count, 0);
-  int max_n = 0;
   for (int i = 0; i < count; ++i) {
     mps_state* h = hs[i];
     if ((st = build_expect(h, ps[i], prec)) != MPS_OK) return st;
     if (h->stream != drv->stream && (st = sync(h)) != MPS_OK) return st;  // h's earlier work done
-    max_n = std::max(max_n, h->n);
     if (h->canonical) continue;
     if ((st = ensure_chain_buffers(h)) != MPS_OK) return st;
     rmin[i] = h->n;
@@ -1996,182 +2220,21 @@ mps_status expect_multi_impl(mps_state* const* hs, const mps_psum* const* ps, in
     stale[i] = !(h->chain_version == h->version && h->chain_rmin <= rmin[i]);
     nrm[i] = h->d_lchain + h->chain_off[h->n];
   }
-  using P = EnvParent<double2>;  // pointer layout shared by every precision
-  using Ch = EnvChild<double2>;
-  std::vector<char> blob;
-  auto put = [&](const void* src, size_t bytes) {
-    const size_t o = blob.size();
-    blob.resize(o + ((bytes + 255) & ~(size_t)255));
-    if (src && bytes) std::memcpy(blob.data() + o, src, bytes);
-    return o;
-  };
-  struct Gemms {  // one merged launch per GEMM half
-    size_t par_off = 0, chi_off = 0;
-    int n_par = 0, n_chi = 0, max_dl = 0, max_dr = 0;
-  };
-  struct Preps {
-    size_t off = 0;
-    int n = 0, max_elems = 0;
-  };
-  auto put_preps = [&](const std::vector<PrepItem>& v) {
-    Preps r;
-    r.n = (int)v.size();
-    for (const PrepItem& it : v) r.max_elems = std::max(r.max_elems, 2 * it.dl * it.dr);
-    r.off = put(v.data(), v.size() * sizeof(PrepItem));
-    return r;
-  };
-  auto put_gemms = [&](const std::vector<P>& par, const std::vector<Ch>& chi) {
-    Gemms g;
-    g.n_par = (int)par.size();
-    g.n_chi = (int)chi.size();
-    for (const P& x : par) {
-      g.max_dl = std::max(g.max_dl, x.dl);
-      g.max_dr = std::max(g.max_dr, x.dr);
-    }
-    g.par_off = put(par.data(), par.size() * sizeof(P));
-    g.chi_off = put(chi.data(), chi.size() * sizeof(Ch));
-    return g;
-  };
-  // (1) every state's sites in environment precision (and transposed)
-  std::vector<PrepItem> pv;
   for (int i = 0; i < count; ++i)
-    for (int q = 0; q < hs[i]->n; ++q) {
-      const auto& pr = hs[i]->ex.prep[q];
-      pv.push_back(PrepItem{hs[i]->cur(q), pr.fwd, pr.tr, pr.dl, pr.dr});
-    }
-  const Preps site_preps = put_preps(pv);
-  // (2) boundary-environment chains of the stale states, depth by depth
-  std::vector<Gemms> left_chain;
-  for (int q = 0; q < max_n; ++q) {
-    std::vector<P> par;
-    std::vector<Ch> chi;
-    for (int i = 0; i < count; ++i) {
-      mps_state* h = hs[i];
-      if (!stale[i] || q >= h->n) continue;
-      const int dl = h->dims[q], dr = h->dims[q + 1];
-      double2* lc = h->d_lchain;
-      par.push_back(P{lc + h->chain_off[q], h->d_chainx, h->cur(q), dl, dr});
-      chi.push_back(Ch{h->d_chainx, lc + h->chain_off[q + 1], 0, dl, dr, h->cur(q)});
-    }
-    if (!par.empty()) left_chain.push_back(put_gemms(par, chi));
-  }
-  std::vector<std::pair<Preps, Gemms>> right_chain;
-  for (int t = 0; t < max_n; ++t) {
-    std::vector<PrepItem> tv;
-    std::vector<P> par;
-    std::vector<Ch> chi;
-    for (int i = 0; i < count; ++i) {
-      mps_state* h = hs[i];
-      const int q = h->n - 1 - t;
-      if (!stale[i] || q < rmin[i] || q < 0) continue;
-      const int dl = h->dims[q + 1], dr = h->dims[q];  // transposed form
-      double2* rc = h->d_rchain;
-      tv.push_back(PrepItem{h->cur(q), nullptr, h->d_chaintr, h->dims[q], h->dims[q + 1]});
-      par.push_back(P{rc + h->chain_off[q + 1], h->d_chainxr, h->d_chaintr, dl, dr});
-      chi.push_back(Ch{h->d_chainxr, rc + h->chain_off[q], 0, dl, dr, h->d_chaintr});
-    }
-    if (!par.empty()) right_chain.push_back({put_preps(tv), put_gemms(par, chi)});
-  }
-  // (3) roots from the chains
-  std::vector<CopyItem> cv;
-  long long copy_max = 0;
-  for (int i = 0; i < count; ++i) {
-    mps_state* h = hs[i];
-    if (h->canonical) continue;
-    for (const auto& r : h->ex.roots) {
-      const long long cnt = (long long)r.d * r.d;
-      if (r.lroot) cv.push_back(CopyItem{h->d_lchain + h->chain_off[r.bond], r.lroot, cnt});
-      if (r.rroot) cv.push_back(CopyItem{h->d_rchain + h->chain_off[r.bond], r.rroot, cnt});
-      copy_max = std::max(copy_max, cnt);
-    }
-  }
-  const size_t copy_off = put(cv.data(), cv.size() * sizeof(CopyItem));
-  // (4) environment updates of equal trie depth: [left depth 0, 1, ...][right depth 0, 1, ...]
-  std::vector<Gemms> env;
-  for (int pass = 0; pass < 2; ++pass) {
-    size_t depth = 0;
-    for (int i = 0; i < count; ++i) {
-      const auto& ls = pass == 0 ? hs[i]->ex.left_launches : hs[i]->ex.right_launches;
-      depth = std::max(depth, ls.size());
-    }
-    for (size_t t = 0; t < depth; ++t) {
-      std::vector<P> par;
-      std::vector<Ch> chi;
-      for (int i = 0; i < count; ++i) {
-        mps_state* h = hs[i];
-        const auto& ls = pass == 0 ? h->ex.left_launches : h->ex.right_launches;
-        if (t >= ls.size()) continue;
-        const ExpectSetup::EnvLaunch& L = ls[t];
-        // the site tensor the single-state launch would take (run_env_launch)
-        const void* site = L.left ? (h->ex.prep[L.site].fwd ? h->ex.prep[L.site].fwd
-                                                            : (const void*)h->cur(L.site))
-                                  : h->ex.prep[L.site].tr;
-        const P* sp = (const P*)(h->ex.host_desc.data() + L.parents_off);
-        const Ch* sc = (const Ch*)(h->ex.host_desc.data() + L.children_off);
-        for (int k = 0; k < L.n_parents; ++k) {
-          P x = sp[k];
-          x.site = (const double2*)site;
-          x.dl = L.dl;
-          x.dr = L.dr;
-          par.push_back(x);
-        }
-        for (int k = 0; k < L.n_children; ++k) {
-          Ch x = sc[k];
-          x.site = (const double2*)site;
-          x.dl = L.dl;
-          x.dr = L.dr;
-          chi.push_back(x);
-        }
-      }
-      env.push_back(put_gemms(par, chi));
-    }
-  }
-  if ((st = ensure_desc(drv, blob.size() + 256)) != MPS_OK) return st;
-  char* d = (char*)drv->d_desc;
-  if ((st = upload(drv, d, blob.data(), blob.size())) != MPS_OK) return st;
+    if (stale[i] && !small_bonds(hs[i])) stale[i] = 2;
+  CallLists lists = call_lists(hs, count, stale, rmin);
+  if ((st = ensure_desc(drv, lists.blob.size() + 256)) != MPS_OK) return st;
+  lists.dev = (char*)drv->d_desc;
+  if ((st = upload(drv, lists.dev, lists.blob.data(), lists.blob.size())) != MPS_OK) return st;
   hipStream_t s = drv->stream;
-  auto run_preps = [&](const Preps& p, int elem) -> hipError_t {
-    return launch_site_prepare_list((const PrepItem*)(d + p.off), p.n, p.max_elems, elem, s);
-  };
-  // launch-level site null: every item names its own; the dims size the grid
-  auto run_gemms = [&](const Gemms& g, int pr) -> hipError_t {
-    const P* dp = (const P*)(d + g.par_off);
-    const Ch* dc = (const Ch*)(d + g.chi_off);
-    hipError_t e;
-    if (pr == MPS_PREC_C128) {
-      e = launch_env_gemm1_c128(dp, g.n_par, nullptr, g.max_dl, g.max_dr, s, 0);
-      return e != hipSuccess ? e : launch_env_gemm2_c128(dc, g.n_chi, nullptr, g.max_dl, g.max_dr, s, 0);
-    }
-    if (pr == MPS_PREC_C64) {
-      e = launch_env_gemm1_c64((const EnvParent<float2>*)dp, g.n_par, nullptr, g.max_dl, g.max_dr, s, 0);
-      return e != hipSuccess ? e
-                             : launch_env_gemm2_c64((const EnvChild<float2>*)dc, g.n_chi, nullptr, g.max_dl,
-                                                    g.max_dr, s, 0);
-    }
-    const int f16 = pr == MPS_PREC_SPLIT_F16;
-    e = launch_env_gemm1_split((const EnvParent<float2>*)dp, g.n_par, nullptr, g.max_dl, g.max_dr, f16, s);
-    return e != hipSuccess ? e
-                           : launch_env_gemm2_split((const EnvChild<float2>*)dc, g.n_chi, nullptr, g.max_dl,
-                                                    g.max_dr, f16, s);
-  };
-  HIP_TRY(drv, run_preps(site_preps, el));
-  for (const Gemms& g : left_chain) HIP_TRY(drv, run_gemms(g, MPS_PREC_C128));
-  for (const auto& rl : right_chain) {
-    HIP_TRY(drv, run_preps(rl.first, 16));
-    HIP_TRY(drv, run_gemms(rl.second, MPS_PREC_C128));
-  }
-  HIP_TRY(drv, launch_root_copy_list((const CopyItem*)(d + copy_off), (int)cv.size(), copy_max, el, s));
-  for (int i = 0; i < count; ++i)
-    if (hs[i]->canonical)
-      for (const auto& r : hs[i]->ex.roots)
-        HIP_TRY(drv, launch_roots(hs[i]->lcur(r.bond), r.lroot, r.rroot, r.d, el, s));
-  for (const Gemms& g : env) HIP_TRY(drv, run_gemms(g, prec));
+  if ((st = run_set_up(drv, lists, hs, count, el, s)) != MPS_OK) return st;
+  for (const EnvMerged& m : lists.env) HIP_TRY(drv, run_env_merged(lists.placed(m), prec, s));
   for (int i = 0; i < count; ++i)
     if (stale[i]) {
       hs[i]->chain_version = hs[i]->version;
       hs[i]->chain_rmin = rmin[i];
     }
-  if (drv->timing) drv->tm.env_launches += 2 * (int64_t)env.size();
+  if (drv->timing) drv->tm.env_launches += 2 * (int64_t)lists.env.size();
   std::vector<double> e2(2 * (size_t)count, 0.0);
   std::vector<double2> nn(count, make_double2(1.0, 0.0));
   for (int i = 0; i < count; ++i) {
@@ -3147,13 +3210,20 @@ mps_status mps_copy(mps_handle dst, mps_handle src) {
     return fail(MPS_ERR_ARG, "mps_copy needs equal qubit counts and bond capacities");
   if ((st = sync(src)) != MPS_OK) return st;  // src's last gates have landed
   const int n = src->n;
+  std::vector<RawCopy> items;
+  long long most = 0;
   for (int q = 0; q < n; ++q)
-    HIP_TRY(dst, hipMemcpyAsync(dst->cur(q), src->cur(q),
-                                sizeof(double2) * 2 * (size_t)src->dims[q] * src->dims[q + 1],
-                                hipMemcpyDeviceToDevice, dst->stream));
-  for (int b = 0; b <= n; ++b)
-    HIP_TRY(dst, hipMemcpyAsync(dst->lcur(b), src->lcur(b), sizeof(double) * (size_t)src->dims[b],
-                                hipMemcpyDeviceToDevice, dst->stream));
+    items.push_back(RawCopy{(const double*)src->cur(q), (double*)dst->cur(q),
+                            4 * (long long)src->dims[q] * src->dims[q + 1]});
+  for (int b = 0; b <= n; ++b) items.push_back(RawCopy{src->lcur(b), dst->lcur(b), src->dims[b]});
+  for (const RawCopy& it : items) most = std::max(most, it.words);
+  if (dst->device == src->device && ensure_desc(dst, items.size() * sizeof(RawCopy)) == MPS_OK) {  // one launch
+    if ((st = upload(dst, dst->d_desc, items.data(), items.size() * sizeof(RawCopy))) != MPS_OK) return st;
+    HIP_TRY(dst, launch_copy_list((const RawCopy*)dst->d_desc, (int)items.size(), most, dst->stream));
+  } else {
+    for (const RawCopy& it : items)
+      HIP_TRY(dst, hipMemcpyAsync(it.dst, it.src, sizeof(double) * it.words, hipMemcpyDeviceToDevice, dst->stream));
+  }
   // complete before returning: src's next gates may overwrite its buffers in place
   if ((st = sync(dst)) != MPS_OK) return st;
   dst->dims = src->dims;
