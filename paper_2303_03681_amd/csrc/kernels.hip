@@ -1195,6 +1195,25 @@ hipError_t launch_fill_ident(double2* dst, int d, hipStream_t s) {
 
 // =================================================================== Eq. (expec2)
 
+// The segment that holds item i, by all lanes of a wave together: every step
+// tests 64 ends at once (one load for up to 64 segments; END: par_end or
+// chi_end).  first: the segment's first item.
+template <int EnvSeg::*END>
+__device__ __forceinline__ int find_segment(const EnvSeg* segs, int n, int i, int& first) {
+  const int lane = threadIdx.x & 63;
+  int lo = 0, len = n;
+  while (len > 1) {
+    const int step = (len + 63) / 64, p = lo + (lane + 1) * step - 1;
+    const bool before = p < lo + len && segs[p].*END <= i;
+    const int skip = __popcll(__ballot(before)) * step;
+    lo += skip;
+    len = min(step, len - skip);
+  }
+  lo = __builtin_amdgcn_readfirstlane(lo);
+  first = lo ? segs[lo - 1].*END : 0;
+  return lo;
+}
+
 // X = L [A^0 | A^1]: (Dl x Dl)(Dl x 2Dr); one item per parent, the site A and
 // the dims the launch's or (items of several MPSs in one launch) the item's.
 template <typename TT>
@@ -1212,10 +1231,11 @@ struct EnvG1P {
   const C2* site;
   int dl, dr;
   const EnvSeg* segs = nullptr;
+  int n_segs = 0;
   __device__ Ctx context(int i) const {
     if (segs) {
-      int s = 0, base = 0;
-      while (i >= segs[s].par_end) base = segs[s++].par_end;
+      int base;
+      const int s = find_segment<&EnvSeg::par_end>(segs, n_segs, i, base);
       const EnvParent<C2> e = ((const EnvParent<C2>*)segs[s].par)[i - base];
       return Ctx{e.l, e.x, (const C2*)segs[s].site, segs[s].dl, segs[s].dr};
     }
@@ -1276,10 +1296,11 @@ struct EnvG2P {
   const C2* site;
   int dl, dr;
   const EnvSeg* segs = nullptr;
+  int n_segs = 0;
   __device__ Ctx context(int i) const {
     if (segs) {
-      int s = 0, base = 0;
-      while (i >= segs[s].chi_end) base = segs[s++].chi_end;
+      int base;
+      const int s = find_segment<&EnvSeg::chi_end>(segs, n_segs, i, base);
       const EnvChild<C2> e = ((const EnvChild<C2>*)segs[s].chi)[i - base];
       return Ctx{e.x, e.out, (const C2*)segs[s].site, segs[s].dl, segs[s].dr, e.letter};
     }
@@ -1413,13 +1434,13 @@ hipError_t launch_env_gemm2_split(const EnvChild<float2>* items, int count, cons
 template <typename T>
 EnvG1P<T> env_p1(const EnvMerged& m) {
   using C2 = typename cplx_of<T>::type;
-  if (m.n_segs > 1) return EnvG1P<T>{nullptr, nullptr, 0, 0, m.segs};
+  if (m.n_segs > 1) return EnvG1P<T>{nullptr, nullptr, 0, 0, m.segs, m.n_segs};
   return EnvG1P<T>{(const EnvParent<C2>*)m.one.par, (const C2*)m.one.site, m.one.dl, m.one.dr};
 }
 template <typename T>
 EnvG2P<T> env_p2(const EnvMerged& m) {
   using C2 = typename cplx_of<T>::type;
-  if (m.n_segs > 1) return EnvG2P<T>{nullptr, nullptr, 0, 0, m.segs};
+  if (m.n_segs > 1) return EnvG2P<T>{nullptr, nullptr, 0, 0, m.segs, m.n_segs};
   return EnvG2P<T>{(const EnvChild<C2>*)m.one.chi, (const C2*)m.one.site, m.one.dl, m.one.dr};
 }
 
@@ -1459,15 +1480,14 @@ hipError_t launch_env_merged(const EnvMerged& m, int prec, hipStream_t s) {
 // compute units.  Per element the same operations in the same order as
 // cgemm_kernel on EnvG1P and EnvG2P.
 template <typename T>
-__global__ __launch_bounds__(256) void env_small_kernel(const EnvSeg* segs) {
+__global__ __launch_bounds__(256) void env_small_kernel(const EnvSeg* segs, int n_segs) {
   using C2 = typename cplx_of<T>::type;
   using Acc = typename acc_of<T>::type;
   extern __shared__ double2 env_lds[];
   C2* X = (C2*)env_lds;  // [dl][2 dr + 1]
   const int item = blockIdx.x;
-  int sg = 0, base = 0;
-  while (item >= segs[sg].chi_end) base = segs[sg++].chi_end;
-  const EnvSeg g = segs[sg];
+  int base;
+  const EnvSeg g = segs[find_segment<&EnvSeg::chi_end>(segs, n_segs, item, base)];
   const EnvChild<C2> ch = ((const EnvChild<C2>*)g.chi)[item - base];
   const int dl = g.dl, dr = g.dr, ldx = 2 * dr + 1;
   const C2* site = (const C2*)g.site;
@@ -1553,9 +1573,9 @@ hipError_t launch_env_small(const EnvMerged& m, int prec, hipStream_t s) {
   if (m.max_dl > kEnvSmall || m.max_dr > kEnvSmall || prec > 1) return hipErrorInvalidValue;
   const size_t el = (size_t)m.max_dl * (2 * m.max_dr + 1);
   if (prec == 0)
-    hipLaunchKernelGGL(env_small_kernel<double>, dim3(m.n_chi), dim3(256), el * sizeof(double2), s, m.segs);
+    hipLaunchKernelGGL(env_small_kernel<double>, dim3(m.n_chi), dim3(256), el * sizeof(double2), s, m.segs, m.n_segs);
   else
-    hipLaunchKernelGGL(env_small_kernel<float>, dim3(m.n_chi), dim3(256), el * sizeof(float2), s, m.segs);
+    hipLaunchKernelGGL(env_small_kernel<float>, dim3(m.n_chi), dim3(256), el * sizeof(float2), s, m.segs, m.n_segs);
   return hipGetLastError();
 }
 

@@ -379,7 +379,11 @@ mps_status ensure_desc(mps_state* h, size_t bytes) {
   return MPS_OK;
 }
 
-// Gate workspaces for up to `items` two-qubit gates at the handle's largest size.
+// Room for optional descriptor lists: with an HBM budget only what is there.
+bool room_for_lists(mps_state* h, size_t bytes) {
+  return bytes <= h->desc_bytes || (h->budget == 0 && ensure_desc(h, bytes) == MPS_OK);
+}
+
 // Per-item counters of a batched SVD (the rotation counters laid out
 // [sweep][item]) for up to `items` gates.
 mps_status ensure_counters(mps_state* h, int items) {
@@ -1271,7 +1275,7 @@ void drop_graph(ExpectSetup& ex) {
   ex.graph = nullptr;
 }
 
-mps_status build_expect(mps_state* h, const mps_psum* ps, int prec) {
+mps_status build_expect_with(mps_state* h, const mps_psum* ps, int prec, bool apart) {
   ExpectSetup& ex = h->ex;
   const PauliPlan& P = ps->plan;
   const int n = h->n;
@@ -1282,6 +1286,7 @@ mps_status build_expect(mps_state* h, const mps_psum* ps, int prec) {
   mps_status st = sync(h);
   if (st != MPS_OK) return st;
   drop_graph(ex);
+  ex.plan_serial = 0;  // no plan until this one is complete
   const size_t el = prec == MPS_PREC_C128 ? sizeof(double2) : sizeof(float2);
   const std::vector<int>& D = h->dims;
   // ---- environment pool layout
@@ -1361,12 +1366,10 @@ mps_status build_expect(mps_state* h, const mps_psum* ps, int prec) {
     }
     return need;
   };
-  // the two passes apart, so that their launches can be merged; shared if there is no room
   const size_t x_left = x_need(P.left), x_right = x_need(P.right);
-  ex.x_apart = grow(&ex.xbuf, ex.xbuf_bytes, std::max<size_t>(1, x_left + x_right) * el) == MPS_OK;
-  if (!ex.x_apart &&
-      (st = grow(&ex.xbuf, ex.xbuf_bytes, std::max<size_t>(1, std::max(x_left, x_right)) * el)) != MPS_OK)
-    return st;
+  const size_t x_elems = apart ? x_left + x_right : std::max(x_left, x_right);
+  ex.x_apart = apart;
+  if ((st = grow(&ex.xbuf, ex.xbuf_bytes, std::max<size_t>(1, x_elems) * el)) != MPS_OK) return st;
   char* poolp = (char*)ex.pool;
   char* sitep = (char*)ex.sites;
   auto lref_ptr = [&](int32_t ref) -> char* {
@@ -1627,6 +1630,21 @@ mps_status build_expect(mps_state* h, const mps_psum* ps, int prec) {
   ex.dims = D;
   ex.fwd128 = fwd128;
   return MPS_OK;
+}
+
+// The two passes get GEMM1 outputs of their own, so that their launches can be
+// merged, unless the handle has an HBM budget (what fits a budget depends on
+// the sum of all its workspaces) or the device has no room for both.
+mps_status build_expect(mps_state* h, const mps_psum* ps, int prec) {
+  const bool apart = h->budget == 0;
+  mps_status st = build_expect_with(h, ps, prec, apart);
+  if (apart && st == MPS_ERR_OOM) {
+    dfree(h, h->ex.xbuf);
+    h->ex.xbuf = nullptr;
+    h->ex.xbuf_bytes = 0;
+    st = build_expect_with(h, ps, prec, false);
+  }
+  return st;
 }
 
 // ----------------------------------------------------------------------------
@@ -2008,7 +2026,7 @@ mps_status expect_open(mps_state* h, const mps_psum* ps, int prec, const double2
   const bool small = stale && small_bonds(h);
   *lists = call_lists(&h, 1, {small ? 1 : 0}, {rmin});
   if (!merged) lists->env.clear();
-  if (ensure_desc(h, lists->blob.size()) == MPS_OK) {
+  if (room_for_lists(h, lists->blob.size())) {
     lists->dev = (char*)h->d_desc;
     if ((st = upload(h, lists->dev, lists->blob.data(), lists->blob.size())) != MPS_OK) return st;
     if (stale && !small && (st = identity_chains(h, rmin)) != MPS_OK) return st;
@@ -3217,7 +3235,7 @@ mps_status mps_copy(mps_handle dst, mps_handle src) {
                             4 * (long long)src->dims[q] * src->dims[q + 1]});
   for (int b = 0; b <= n; ++b) items.push_back(RawCopy{src->lcur(b), dst->lcur(b), src->dims[b]});
   for (const RawCopy& it : items) most = std::max(most, it.words);
-  if (dst->device == src->device && ensure_desc(dst, items.size() * sizeof(RawCopy)) == MPS_OK) {  // one launch
+  if (dst->device == src->device && room_for_lists(dst, items.size() * sizeof(RawCopy))) {  // one launch
     if ((st = upload(dst, dst->d_desc, items.data(), items.size() * sizeof(RawCopy))) != MPS_OK) return st;
     HIP_TRY(dst, launch_copy_list((const RawCopy*)dst->d_desc, (int)items.size(), most, dst->stream));
   } else {
