@@ -1215,7 +1215,7 @@ __device__ __forceinline__ int find_segment(const EnvSeg* segs, int n, int i, in
 }
 
 // X = L [A^0 | A^1]: (Dl x Dl)(Dl x 2Dr); one item per parent, the site A and
-// the dims the launch's or (items of several MPSs in one launch) the item's.
+// the dims the launch's or (merged launches) the segment's.
 template <typename TT>
 struct EnvG1P {
   using T = TT;
@@ -1240,7 +1240,6 @@ struct EnvG1P {
       return Ctx{e.l, e.x, (const C2*)segs[s].site, segs[s].dl, segs[s].dr};
     }
     const EnvParent<C2> e = items[i];
-    if (e.site) return Ctx{e.l, e.x, e.site, e.dl, e.dr};
     return Ctx{e.l, e.x, site, dl, dr};
   }
   __device__ static void dims(const Ctx& c, int& M, int& N, int& K) {
@@ -1305,7 +1304,6 @@ struct EnvG2P {
       return Ctx{e.x, e.out, (const C2*)segs[s].site, segs[s].dl, segs[s].dr, e.letter};
     }
     const EnvChild<C2> e = items[i];
-    if (e.site) return Ctx{e.x, e.out, e.site, e.dl, e.dr, e.letter};
     return Ctx{e.x, e.out, site, dl, dr, e.letter};
   }
   __device__ static void dims(const Ctx& c, int& M, int& N, int& K) {
@@ -1375,10 +1373,262 @@ struct EnvG2P {
 // One environment GEMM with tile shape kEnvTileShape[tile] (all shapes give
 // bitwise-identical results: every output element accumulates its K range in
 // the same order of 16x16x4 steps whatever the tile).
+// The address of a wave's operand as a scalar; load_g reads from memory at it.
+__device__ __forceinline__ size_t uniform_addr(const void* p) {
+  const size_t v = (size_t)p;
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)v), hi = __builtin_amdgcn_readfirstlane((unsigned)(v >> 32));
+  return (size_t)hi << 32 | lo;
+}
+template <typename T>
+__device__ __forceinline__ typename cplx_of<T>::type load_g(size_t base, size_t off) {
+  typedef T vec __attribute__((ext_vector_type(2)));
+  const vec v = *(const __attribute__((address_space(1))) vec*)((const __attribute__((address_space(1))) char*)base + off);
+  typename cplx_of<T>::type o;
+  o.x = v.x;
+  o.y = v.y;
+  return o;
+}
+__device__ __forceinline__ double flip_sign(double v, unsigned mask) {
+  return __hiloint2double(__double2hiint(v) ^ (int)mask, __double2loint(v));
+}
+__device__ __forceinline__ float flip_sign(float v, unsigned mask) { return __uint_as_float(__float_as_uint(v) ^ mask); }
+
+// The environment GEMMs (c128, c64): bound by the matrix cores once the loop
+// has little else in it.  cgemm_kernel's loads carry the letter's phase, the s
+// boundary and the edges as branches per element, and a branch around a load
+// makes the loop wait for it; here a wave loads whole rows of both operands, so
+// the row's s, phase and sign are scalars, rows past the edge are clamped
+// (their products are never stored) and only a last partial chunk is masked.
+// Two LDS buffers and one barrier per chunk, complex elements interleaved (one
+// read per fragment).  Same products in the same order as cgemm_kernel.  50
+// qubits D = 256 c128: 225 -> 205 ms (57 -> 64 TFLOP/s of the 73 a large FP64
+// matrix product reaches); 28 qubits D = 512 c64: 74 -> 63 ms of updates (105
+// -> 124 TFLOP/s of 151).
+template <class P, int HALF, int BM, int BN, int BK>
+__global__ __launch_bounds__(256, 2) void env_gemm_kernel(P p, int tiles_m, int tiles_n, int total, int g8) {
+  using T = typename P::T;
+  using C2 = typename cplx_of<T>::type;
+  using Acc = typename acc_of<T>::type;
+  constexpr int RA = BM / 64, RB = BN / 64, EK = BK / 4;  // loads per row, rows per wave and chunk
+  constexpr int FM = BM / 32, FN = BN / 32;
+  __shared__ C2 As[2][BK][BM + 1];
+  __shared__ C2 Bs[2][BK][BN + 1];
+
+  const int logical = xcd_remap(blockIdx.x, g8);
+  if (logical >= total) return;
+  const int per_item = tiles_m * tiles_n;
+  const int item = logical / per_item;
+  const int t = logical - item * per_item;
+  const int tm = t / tiles_n;
+  const int m0 = tm * BM, n0 = (t - tm * tiles_n) * BN;
+  const typename P::Ctx ctx = p.context(item);
+  const int dl = __builtin_amdgcn_readfirstlane(ctx.dl), dr = __builtin_amdgcn_readfirstlane(ctx.dr);
+  constexpr size_t EL = sizeof(C2);
+  const size_t site = uniform_addr(ctx.site);
+  size_t env;  // HALF 1: L, HALF 2: X
+  int M, N, K, letter = 0;
+  C2* out;
+  if constexpr (HALF == 1) {
+    env = uniform_addr(ctx.l);
+    out = ctx.x;
+    M = K = dl;
+    N = 2 * dr;
+  } else {
+    env = uniform_addr(ctx.x);
+    letter = __builtin_amdgcn_readfirstlane(ctx.letter);
+    out = ctx.out;
+    M = N = dr;
+    K = 2 * dl;
+  }
+  if (m0 >= M || n0 >= N) return;
+
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = (wave >> 1) * (BM / 2), wn = (wave & 1) * (BN / 2);
+  const int lr = lane & 15, lk = lane >> 4;
+  const int flip = (letter == 1 || letter == 2) ? 1 : 0;
+  const bool swap = letter == 2;
+
+  // Per-lane offsets in bytes.  HALF 1 loads A with k along the lanes (k is
+  // contiguous in memory: k = tid % BK, rows tid / BK + ...); every other load
+  // takes a row of 64 at k = wave + 4 e.
+  constexpr int AK = 256 / BK;
+  const int ak = tid % BK, ai = tid / BK;
+  unsigned oa[HALF == 1 ? EK * RA : RA];
+  if constexpr (HALF == 1) {
+#pragma unroll
+    for (int e = 0; e < EK * RA; ++e)
+      oa[e] = ((unsigned)min(ai + e * AK, M - 1 - m0) * dl + ak) * (unsigned)EL;
+    env += (size_t)m0 * dl * EL;
+  } else {
+#pragma unroll
+    for (int h = 0; h < RA; ++h) oa[h] = (unsigned)min(m0 + lane + 64 * h, M - 1) * (unsigned)EL;
+  }
+  size_t ob[RB];
+#pragma unroll
+  for (int h = 0; h < RB; ++h) {
+    const int j = min(n0 + lane + 64 * h, N - 1), s = HALF == 1 && j >= dr;
+    ob[h] = HALF == 1 ? (s ? (size_t)dl * dr + (j - dr) : (size_t)j) * EL : (unsigned)j * (unsigned)EL;
+  }
+
+  // Loads and LDS stores of the chunk at k0; loads past K take the last k,
+  // which put() replaces by zeros (MASK: the chunk reaches past K).
+  C2 ra[EK * RA], rb[EK * RB];
+  auto load = [&](int k0) {
+    if constexpr (HALF == 1) {
+      const unsigned back = (unsigned)max(k0 + ak - (K - 1), 0) * (unsigned)EL;
+#pragma unroll
+      for (int e = 0; e < EK * RA; ++e) ra[e] = load_g<T>(env, (size_t)k0 * EL + oa[e] - back);
+    }
+#pragma unroll
+    for (int e = 0; e < EK; ++e) {
+      const int k = min(k0 + wave + 4 * e, K - 1);
+      const size_t srow = site + (size_t)k * dr * EL;
+      if constexpr (HALF == 1) {
+#pragma unroll
+        for (int h = 0; h < RB; ++h) rb[e * RB + h] = load_g<T>(srow, ob[h]);
+      } else {
+        const int s = k >= dl ? 1 : 0, row = 2 * (k - s * dl) + (flip ? 1 - s : s);
+        const size_t xrow = env + (size_t)row * dr * EL;
+#pragma unroll
+        for (int h = 0; h < RA; ++h) ra[e * RA + h] = load_g<T>(srow, oa[h]);
+#pragma unroll
+        for (int h = 0; h < RB; ++h) rb[e * RB + h] = load_g<T>(xrow, ob[h]);
+      }
+    }
+  };
+  auto put = [&](int b, int k0, auto mask) {
+    constexpr bool MASK = decltype(mask)::value;
+    auto keep = [](C2 v, bool in) {
+      if (MASK) {
+        v.x = in ? v.x : T(0);
+        v.y = in ? v.y : T(0);
+      }
+      return v;
+    };
+    if constexpr (HALF == 1) {
+#pragma unroll
+      for (int e = 0; e < EK * RA; ++e) As[b][ak][ai + e * AK] = keep(ra[e], k0 + ak < K);
+    }
+#pragma unroll
+    for (int e = 0; e < EK; ++e) {
+      const int kk = wave + 4 * e;
+      const bool in = k0 + kk < K, s1 = k0 + kk >= dl;
+      if constexpr (HALF == 2) {
+#pragma unroll
+        for (int h = 0; h < RA; ++h) {
+          C2 v = keep(ra[e * RA + h], in);
+          v.y = -v.y;
+          As[b][kk][lane + 64 * h] = v;
+        }
+      }
+      // Y: s=0 -> -i X^1, s=1 -> +i X^0;  Z: s=1 -> -X^1
+      const unsigned nx = s1 && letter >= 2 ? 0x80000000u : 0u;
+      const unsigned ny = (letter == 2 && !s1) || (letter == 3 && s1) ? 0x80000000u : 0u;
+#pragma unroll
+      for (int h = 0; h < RB; ++h) {
+        C2 v = keep(rb[e * RB + h], in);
+        if constexpr (HALF == 2) {
+          const T re = swap ? v.y : v.x, im = swap ? v.x : v.y;
+          v.x = flip_sign(re, nx);
+          v.y = flip_sign(im, ny);
+        }
+        Bs[b][kk][lane + 64 * h] = v;
+      }
+    }
+  };
+  auto stage = [&](int b, int k0) {
+    if (k0 + BK <= K) put(b, k0, std::false_type{});
+    else put(b, k0, std::true_type{});
+  };
+
+  Acc acc_r[FM][FN], acc_i[FM][FN];
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) acc_r[i][j][v] = acc_i[i][j][v] = T(0);
+
+  load(0);
+  stage(0, 0);
+  load(BK);
+  lds_barrier();
+  int b = 0;
+  for (int k0 = 0; k0 < K; k0 += BK, b ^= 1) {
+    if (k0 + BK < K) stage(b ^ 1, k0 + BK);  // its readers passed the last barrier
+    load(k0 + 2 * BK);  // unconditional (past K: clamped): a branch here makes the loop wait for it
+#pragma unroll
+    for (int kk = 0; kk < BK; kk += 4) {
+      C2 a[FM], c[FN];
+#pragma unroll
+      for (int i = 0; i < FM; ++i) a[i] = As[b][kk + lk][wm + i * 16 + lr];
+#pragma unroll
+      for (int j = 0; j < FN; ++j) c[j] = Bs[b][kk + lk][wn + j * 16 + lr];
+      // the two products of one accumulator are kept apart: the second waits for the first
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+          acc_r[i][j] = mfma_16x16x4(a[i].x, c[j].x, acc_r[i][j]);
+          acc_i[i][j] = mfma_16x16x4(a[i].x, c[j].y, acc_i[i][j]);
+        }
+#pragma unroll
+      for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+          acc_r[i][j] = mfma_16x16x4(-a[i].y, c[j].y, acc_r[i][j]);
+          acc_i[i][j] = mfma_16x16x4(a[i].y, c[j].x, acc_i[i][j]);
+        }
+    }
+    lds_barrier();
+  }
+
+#pragma unroll
+  for (int i = 0; i < FM; ++i)
+#pragma unroll
+    for (int j = 0; j < FN; ++j)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int row = m0 + wm + i * 16 + acc_row<T>(lk, v);
+        const int col = n0 + wn + j * 16 + lr;
+        if (row < M && col < N) {
+          C2 o;
+          o.x = acc_r[i][j][v];
+          o.y = acc_i[i][j][v];
+          out[(size_t)row * N + col] = o;
+        }
+      }
+}
+
+template <int BM, int BN, int BK, class P>
+hipError_t launch_env_gemm(const P& p, int count, int m, int n, hipStream_t s) {
+  if (count <= 0 || m <= 0 || n <= 0) return hipSuccess;
+  constexpr int HALF = P::A_CONTIG_K ? 1 : 2;
+  const int tm = cdiv(m, BM), tn = cdiv(n, BN);
+  const long long total = (long long)count * tm * tn;
+  if (total > 0x7fffff00LL) return hipErrorInvalidValue;
+  const int g8 = (int)((total + 7) / 8 * 8);
+  hipLaunchKernelGGL((env_gemm_kernel<P, HALF, BM, BN, BK>), dim3(g8), dim3(256), 0, s, p, tm, tn, (int)total, g8);
+  return hipGetLastError();
+}
+
+// FP64: 64 x 64 x 8, four workgroups per compute unit (50 qubits D = 256:
+// 205 ms; 64 x 64 x 16 with two 212, 128 x 64 x 8 with two 208).  FP32: 128 x 64
+// where that pads no further rows and still gives four workgroups per compute
+// unit (28 qubits D = 512: 63 ms of updates per call, 66 in 64 x 64 tiles).
+template <class P>
+hipError_t launch_env_64(const P& p, int count, int m, int n, hipStream_t s) {
+  if constexpr (sizeof(typename P::T) == 8) return launch_env_gemm<64, 64, 8>(p, count, m, n, s);
+  else if (cdiv(m, 64) % 2 == 0 && (long long)count * cdiv(m, 128) * cdiv(n, 64) >= 1024)
+    return launch_env_gemm<128, 64, 8>(p, count, m, n, s);
+  else return launch_env_gemm<64, 64, 16>(p, count, m, n, s);
+}
+
 template <class P>
 hipError_t launch_env_tile(const P& p, int tile, int count, int m, int n, hipStream_t s) {
   switch (tile) {
-    case 0: return launch_cgemm<64, 64, 16>(p, count, m, n, s);
+    case 0: return launch_env_64(p, count, m, n, s);
     case 1: return launch_cgemm<32, 32, 16>(p, count, m, n, s);
     case 2: return launch_cgemm<128, 64, 16>(p, count, m, n, s);
     case 3: return launch_cgemm<64, 128, 16>(p, count, m, n, s);

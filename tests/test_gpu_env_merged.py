@@ -86,3 +86,24 @@ def test_many_states(gpu_lib, count):
     for m, _, p in base:
         m.close()
         p.close()
+
+
+# updates in the 64 x 64 and 128 x 64 tiles against the 32 x 32 ones: bonds at
+# their edges, K not a multiple of the chunk, enough strings for 1024 tiles
+@pytest.mark.parametrize("n,D,count", [(13, 7, 40), (14, 63, 60), (14, 64, 3000), (15, 65, 60), (16, 127, 300),
+                                       (16, 128, 1500), (16, 129, 300), (17, 200, 200)])
+def test_tiles_agree(gpu_lib, n, D, count):
+    from paper_2303_03681_amd import binding
+    rng = np.random.default_rng([n, D, count])
+    m = _state(binding, n, D, rng)
+    plan = _plan(binding, n, count, rng)
+    for prec in ("c128", "c64"):
+        out = []
+        for tile in (-1, 0, 1):
+            m.set_env_tile(tile)
+            out.append(m.expect(plan, prec, per_term=True))
+        print(f"n={n} D={D} {prec}: bonds up to {m.bond_dims().max()}, E {out[0][0]:.12f}", flush=True)
+        for e, p in out[:2]:
+            assert e == out[2][0] and np.array_equal(p, out[2][1])
+    m.close()
+    plan.close()
