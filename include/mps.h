@@ -395,12 +395,13 @@ typedef struct {
                              * env and close figures above cover eager launches */
   int64_t jacobi_batch_sweeps; /* sweeps launched for multi-launch Jacobi batches *
                                 * (a batch runs until its slowest item converges) */
-  int64_t jacobi_multi_items;  /* SVDs that ran as multi-launch rounds (rows of    *
-                                * 129..1024 elements, more than 64 x 64 entries)   */
+  int64_t jacobi_multi_items;  /* SVDs that ran as multi-launch rounds (more than  *
+                                * 64 x 64 entries, rows of at most 1024 elements)  */
   int64_t jacobi_wide_items;   /* of those, SVDs with rows of 513..1024 elements   */
   int64_t jacobi_split_batches; /* batches whose rounds ran in >= 2 item groups    */
-  double close_tile_flops;     /* FLOPs of the 64 x 64 Gram tiles the closing    *
-                                * launches compute (every pair of a needed tile)  */
+  double close_tile_flops;     /* FLOPs the closing launches compute: every pair  *
+                                * of a 64 x 64 Gram tile, or the needed pairs alone *
+                                * where they fill their tiles sparsely            */
 } mps_timing;
 
 mps_status mps_set_timing(mps_handle h, int32_t enabled); /* also resets counters */

@@ -5,6 +5,7 @@
 //
 //   Eq. (C)   C = sum_{i'j'} Q B_q^{i'} B_{q+1}^{j'}          -> scratch (L2-resident)
 //   Eq. (C~)  rows of lambda C, held in registers
+//   LQ        larger ones: two LQ factorisations first (lq.hip says why)
 //   Alg. 1    one-sided Jacobi on those rows until a sweep makes no rotation
 //   Eq. (svd) sigma = row norms, stable descending order, truncation rank k
 //   Eq. (Bl)  B_{q+1} <- V_k^+,  B_q <- C V_k / ||sigma_1..k||,  lambda <- sigma_k / ||sigma_1..k||

@@ -9,8 +9,9 @@
 //                    normalised vectors -> B~_{q+1} = V (Eq. Bl) or canonical tensors
 //   trunc            Eq. (Bl): B~_q = C V^+, an MFMA GEMM
 //   canon_*          the GEMMs of the two canonicalisation sweeps
-//   env_gemm1/2      Eq. (expec2) transfer update L' = sum sigma A^{s+} L A^{s'}
-//   gram             closing traces Tr(L R) for all (prefix, suffix) pairs at a bond
+//   env_gemm, env_small  Eq. (expec2) transfer update L' = sum sigma A^{s+} L A^{s'}
+//   gram, gram_pairs closing traces Tr(L R): tiles of (prefix, suffix) pairs at a
+//                    bond, or the needed pairs alone
 //   energy           compensated FP64 sum_k c_k <P_k> in string order
 #include <hip/hip_runtime.h>
 
