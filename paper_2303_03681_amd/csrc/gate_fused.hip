@@ -382,7 +382,7 @@ __device__ __forceinline__ void gate_lq(int rows, int len, double2* xs, double2*
   }
   __syncthreads();
   mgs_rows<E, FW, RPW>(
-      x, rows, xs, [&](int t, double r) { f_out[(size_t)t * rows + t] = make_double2(r, 0.0); },
+      x, rows, xs, 0.0, [&](int t, double r) { f_out[(size_t)t * rows + t] = make_double2(r, 0.0); },
       [&](int t, const double2* q) {
         if (q_out)
           for (int e = threadIdx.x; e < len; e += FW * 64) q_out[(size_t)t * len + e] = q[e];
@@ -564,7 +564,7 @@ __device__ __forceinline__ void gate_orth(const FusedGate& g, double2* xs, int k
     }
   __syncthreads();
   mgs_rows<E, FW, RPW>(
-      x, k, xs, [](int, double) {},
+      x, k, xs, kDependent, [](int, double) {},
       [&](int t, const double2* v) {
         for (int e = threadIdx.x; e < m; e += FW * 64) {
           const int j = e >= Dr ? 1 : 0;

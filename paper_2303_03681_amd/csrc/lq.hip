@@ -27,7 +27,8 @@
 // block's components out of all later rows.  The rows of Z Q1 are orthonormal
 // to eps sigma_1 / sigma_p only (the loss of MGS in Q1), so they go through
 // the same two kernels once more in descending order of sigma, which leaves
-// the leading directions untouched.
+// the leading directions untouched and leaves nothing of a row that depends on
+// earlier ones to rounding (kDependent).
 //
 // What bounds it: the panel is a serial chain of LQB steps (norm, broadcast
 // through LDS, dot products, update) on one workgroup per matrix; the update
@@ -140,7 +141,7 @@ __global__ __launch_bounds__(NW * 64) void lq_panel_kernel(const LqItem* items, 
   }
   const int half = m / 2;
   mgs_rows<E, NW, RPW>(
-      x, nb, &q_lds[0][0],
+      x, nb, &q_lds[0][0], it.out ? kDependent : 0.0,
       [&](int t, double r) {
         if (it.r) it.r[(size_t)(s0 + t) * it.n + s0 + t] = make_double2(r, 0.0);
       },

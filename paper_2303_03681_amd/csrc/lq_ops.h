@@ -8,6 +8,14 @@
 
 namespace mps {
 
+// `least` of the pass that orthonormalises V^+.  Its rows have unit norm and
+// overlap with the rows before by eps sigma_1 / sigma_p, so one of which less
+// than 1e-4 is left has a sigma_p that is round-off (kept where the cutoff is
+// below it).  Normalised, what is left is the rounding of the subtraction --
+// parallel to an earlier row where the rows have one element, which would count
+// that direction twice.
+constexpr double kDependent = 1e-8;
+
 // Row u of `rows` sits on wave u % NW in slot u / NW, lane + 64 k holding
 // element k.  Row t is normalised at step t and taken out of the later rows.
 // buf: 2 x 64 E elements of shared memory; diag(t, r) is called by one lane
@@ -23,8 +31,8 @@ namespace mps {
 // wave issue; handing the next row on ahead of the others (look-ahead) took
 // 1.26 us.
 template <int E, int NW, int RPW, class Diag, class Done, class Coef>
-__device__ __forceinline__ void mgs_rows(double2 (&x)[RPW][E], int rows, double2* buf, Diag diag, Done done,
-                                         Coef coef) {
+__device__ __forceinline__ void mgs_rows(double2 (&x)[RPW][E], int rows, double2* buf, double least, Diag diag,
+                                         Done done, Coef coef) {
   constexpr int G = RPW < 4 ? RPW : 4;  // rows whose products are reduced together
   static_assert(RPW % G == 0, "whole groups");
   const int lane = threadIdx.x & 63, wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -38,7 +46,7 @@ __device__ __forceinline__ void mgs_rows(double2 (&x)[RPW][E], int rows, double2
 #pragma unroll
         for (int k = 0; k < E; ++k) nn = norm_acc(x[a][k], nn);
         nn = wave_sum(nn);
-        const double inv = nn > 0.0 ? rsqrt_newton(nn) : (nn == 0.0 ? 0.0 : nn);  // NaN stays NaN
+        const double inv = nn > least ? rsqrt_newton(nn) : (nn <= least ? 0.0 : nn);  // NaN stays NaN
 #pragma unroll
         for (int k = 0; k < E; ++k) b[lane + 64 * k] = make_double2(x[a][k].x * inv, x[a][k].y * inv);
         if (lane == 0) diag(t, nn * inv);
