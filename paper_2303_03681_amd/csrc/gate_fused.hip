@@ -320,7 +320,7 @@ struct FusedShared {
   double part[FW];
   int rot[2];
   int k;
-  double inv;
+  double inv, least;
   int ok;
 };
 
@@ -488,6 +488,7 @@ __device__ __forceinline__ bool gate_svd(const FusedGate& g, double2* xs, FusedS
       sh.ok = isfinite(tot) && kept > 0.0 && isfinite(kept);
       sh.inv = sh.ok ? 1.0 / kept : 0.0;
       sh.k = k;
+      sh.least = 0x1p-53 * sqrt(tot);  // no vector for round-off (finalize_kernel says why)
       if (sh.ok) {
         *g.disc += tot > 0.0 ? disc2 / tot : 0.0;
         *g.sweeps += done;
@@ -509,7 +510,7 @@ __device__ __forceinline__ bool gate_svd(const FusedGate& g, double2* xs, FusedS
         const int p = sh.rank[row];
         if (p >= sh.k) continue;
         const double sv = sh.sig[row];
-        const double is = sv > 0.0 ? 1.0 / sv : 0.0;
+        const double is = sv > sh.least ? 1.0 / sv : 0.0;
 #pragma unroll
         for (int kk = 0; kk < E; ++kk) {
           const int e = lane + 64 * kk;

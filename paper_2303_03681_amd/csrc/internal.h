@@ -40,13 +40,13 @@ struct JacItem {          // one-sided Jacobi on the n row vectors (length m) of
   int rot_stride;
 };
 
-enum FinalizeMode { FIN_GATE = 0, FIN_LEFT = 1, FIN_RIGHT = 2 };
+enum FinalizeMode { FIN_GATE = 0, FIN_LEFT = 1, FIN_RIGHT = 2, FIN_SVD = 3 };
 
 struct FinItem {          // norms, stable descending sort, truncation, output tensors
   const double2* w;       // converged vectors (n x m)
-  double2* vec_out;       // FIN_GATE/FIN_RIGHT: [s][a][r] (k x m split at m/2);
+  double2* vec_out;       // FIN_GATE/FIN_RIGHT/FIN_SVD: [s][a][r] (k x m split at m/2);
                           // FIN_LEFT: [e][a] (m x k)
-  double* lam_out;        // FIN_GATE/FIN_RIGHT: normalised singular values (k)
+  double* lam_out;        // FIN_GATE/FIN_RIGHT/FIN_SVD: normalised singular values (k)
   int* k_out;             // number kept
   double* scale_out;      // 1 / ||sigma_1..k||
   double* disc_out;       // relative discarded weight

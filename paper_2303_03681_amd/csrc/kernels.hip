@@ -831,11 +831,16 @@ hipError_t launch_jacobi_single(const JacItem* items_dev, int items, int max_swe
 
 // sigma_i = ||a_i||, stable descending sort, k = min(cap, #{sigma > cutoff ||sigma||}) >= 1,
 // normalised output vectors (Algorithm 1's final loop and sort; truncation of Eq. svd).
+// FIN_GATE: no vector (zero) for a sigma that is round-off.  Algorithm 1 leaves
+// pairs below eps^2 ||A||_F^2 as they are, so the vectors of sigma_i and sigma_1
+// overlap by up to that over sigma_1 sigma_i: 1e-12 at 2^-53 ||sigma||, but any
+// angle further down, where a normalised vector would count sigma_1's direction
+// once more.
 __global__ __launch_bounds__(1024) void finalize_kernel(const FinItem* items) {
   __shared__ double sig[1024];
   __shared__ int perm[1024];
   __shared__ int s_k;
-  __shared__ double s_inv;
+  __shared__ double s_inv, s_least;
   const FinItem it = items[blockIdx.x];
   const int n = it.n, m = it.m;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -888,6 +893,7 @@ __global__ __launch_bounds__(1024) void finalize_kernel(const FinItem* items) {
       *it.scale_out = s_inv;
       *it.disc_out = tot > 0.0 ? disc2 / tot : 0.0;
       s_k = k;
+      s_least = it.mode == FIN_GATE ? 0x1p-53 * nrm : 0.0;
     }
   }
   __syncthreads();
@@ -909,7 +915,7 @@ __global__ __launch_bounds__(1024) void finalize_kernel(const FinItem* items) {
       const double sv = sig[perm[a]];
       const double2 x = it.w[(size_t)perm[a] * m + e];
       it.vec_out[((size_t)s * k + a) * half + r] =
-          sv > 0.0 ? make_double2(x.x / sv, x.y / sv) : make_double2(0.0, 0.0);
+          sv > s_least ? make_double2(x.x / sv, x.y / sv) : make_double2(0.0, 0.0);
     }
   }
 }

@@ -3068,7 +3068,7 @@ mps_status mps_jacobi_svd(int32_t n_vec, int32_t vec_len, const double* vectors,
   double2 *w = nullptr, *out = nullptr;
   double *fro2 = nullptr, *lam = nullptr, *scale = nullptr, *disc = nullptr;
   int *rot = nullptr, *sw = nullptr, *k = nullptr, *status = nullptr;
-  // FIN_GATE writes vec_out as [s][a][r] with m split in halves; with an odd
+  // FIN_SVD writes vec_out as [s][a][r] with m split in halves; with an odd
   // length use FIN_LEFT-free path: pad the length to even.
   const int m = vec_len + (vec_len & 1);
   if ((st = dalloc_t(h, &w, (size_t)n_vec * m)) != MPS_OK) return st;
@@ -3095,7 +3095,7 @@ mps_status mps_jacobi_svd(int32_t n_vec, int32_t vec_len, const double* vectors,
   std::vector<JacItem> jc{JacItem{w, fro2, rot, sw, n_vec, m, 0, 0, 1}};
   if ((st = run_jacobi(h, jc, 0, swp)) != MPS_OK) return st;
   if (swp[0] < 0) return fail(MPS_ERR_NOCONV, "Jacobi SVD did not converge");
-  FinItem fi{w, out, lam, k, scale, disc, status, n_vec, m, n_vec, 0.0, FIN_GATE};
+  FinItem fi{w, out, lam, k, scale, disc, status, n_vec, m, n_vec, 0.0, FIN_SVD};
   if ((st = ensure_desc(h, 4096)) != MPS_OK) return st;
   if ((st = upload(h, h->d_desc, &fi, sizeof(fi))) != MPS_OK) return st;
   HIP_TRY(h, launch_finalize((const FinItem*)h->d_desc, 1, h->stream));
@@ -3172,7 +3172,7 @@ mps_status mps_jacobi_svd_noalloc(int32_t n_vec, int32_t vec_len, const double* 
   std::vector<JacItem> jc{JacItem{w, fro2, rot, sw, n_vec, m, 0, 0, 1}};
   if ((st = run_jacobi(h, jc, 0, swp)) != MPS_OK) return st;
   if (swp[0] < 0) return fail(MPS_ERR_NOCONV, "Jacobi SVD did not converge");
-  FinItem fi{w, out, lam, k, scale, disc, status, n_vec, m, n_vec, 0.0, FIN_GATE};
+  FinItem fi{w, out, lam, k, scale, disc, status, n_vec, m, n_vec, 0.0, FIN_SVD};
   if ((st = upload(h, h->d_desc, &fi, sizeof(fi))) != MPS_OK) return st;
   HIP_TRY(h, launch_finalize((const FinItem*)h->d_desc, 1, h->stream));
   int kk = 0, stt = 0;
