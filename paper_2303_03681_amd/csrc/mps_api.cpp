@@ -57,6 +57,10 @@ double now_ms() {
       .count();
 }
 
+// device allocations given back so far, by any handle: what was refused for lack
+// of device memory is tried again after the next one
+std::atomic<uint64_t> g_releases{0};
+
 size_t g_lds_budget = 0;  // dynamic LDS the Jacobi kernels may use (set once per process)
 std::mutex g_lds_mutex;
 
@@ -172,19 +176,25 @@ struct mps_state {
   // gate workspaces
   int ws_items = 0;
   int ctr_items = 0;  // per-item SVD counters allocated (fro2, rot, sweeps, k, scale, disc, status)
-  size_t ws_stride = 0;  // complex elements per item
+  size_t ws_stride = 0;  // complex elements per item: ws_side squared
+  size_t ws_side = 0;    // longest side of a two-site matrix, 2 max(cap)
   double2* ws_c = nullptr;
   double2* ws_w = nullptr;
-  // LQ preconditioning of the batched SVDs: the two factors of each gate (the
-  // first one's space then takes V^+).  Optional: given back when the budget
-  // or the device has no room for something else.
+  // LQ preconditioning of the gate SVDs: the two factors of each gate (the
+  // first one's space then takes V^+), row norms, orders and 1 / sigma.
+  // Optional: given back when the budget or the device has no room for
+  // something else.
   int pre_items = 0;
   bool pre_busy = false;
+  void* pre_ws = nullptr;    // one allocation, the four arrays below
   double2* ws_l1 = nullptr;
   double2* ws_l2 = nullptr;
-  int lq_items = 0;          // per-item row norms, orders and 1 / sigma
-  double* d_lqval = nullptr; // [item][2][kLqMax]: squared norms, 1 / sigma
-  int* d_lqidx = nullptr;    // [item][2][kLqMax]: row order, singular value order
+  double* d_lqval = nullptr; // [item][2][ws_side]: squared norms, 1 / sigma
+  int* d_lqidx = nullptr;    // [item][2][ws_side]: row order, singular value order
+  void* d_lqdesc = nullptr;  // descriptors of a preconditioned batch this handle drives
+  size_t lqdesc_bytes = 0;
+  int pre_refused = 0;       // as many items as the device had no room for ...
+  uint64_t pre_refused_at = 0;  // ... at this count of releases (g_releases)
   double* d_fro2 = nullptr;
   int* d_rot = nullptr;
   int* d_sweeps = nullptr;
@@ -282,20 +292,29 @@ void dfree(mps_state* h, void* p) {
       h->held -= h->allocs[i].second;
       h->allocs.erase(h->allocs.begin() + i);
       (void)hipFree(p);
+      g_releases.fetch_add(1);
       return;
     }
+}
+
+void free_pre_items(mps_state* h) {
+  dfree(h, h->pre_ws);
+  h->pre_ws = nullptr;
+  h->ws_l1 = h->ws_l2 = nullptr;
+  h->d_lqval = nullptr;
+  h->d_lqidx = nullptr;
+  h->pre_items = 0;
 }
 
 // Gives the preconditioning workspace back; false if there is none (or a
 // batch is using it).
 bool drop_pre(mps_state* h) {
-  if (h->pre_busy || (!h->ws_l1 && !h->ws_l2 && !h->d_lqval && !h->d_lqidx)) return false;
+  if (h->pre_busy || (!h->pre_ws && !h->d_lqdesc)) return false;
   (void)hipStreamSynchronize(h->stream);
-  for (void* p : {(void*)h->ws_l1, (void*)h->ws_l2, (void*)h->d_lqval, (void*)h->d_lqidx}) dfree(h, p);
-  h->ws_l1 = h->ws_l2 = nullptr;
-  h->d_lqval = nullptr;
-  h->d_lqidx = nullptr;
-  h->pre_items = h->lq_items = 0;
+  free_pre_items(h);
+  dfree(h, h->d_lqdesc);
+  h->d_lqdesc = nullptr;
+  h->lqdesc_bytes = 0;
   return true;
 }
 
@@ -418,7 +437,8 @@ mps_status ensure_ws(mps_state* h, int items) {
   h->ws_c = h->ws_w = nullptr;
   int dmax = 1;
   for (int b = 0; b <= h->n; ++b) dmax = std::max(dmax, h->cap[b]);
-  h->ws_stride = (size_t)(2 * dmax) * (2 * dmax);
+  h->ws_side = 2 * (size_t)dmax;
+  h->ws_stride = h->ws_side * h->ws_side;
   h->ws_items = 0;
   if ((st = dalloc_t(h, &h->ws_c, h->ws_stride * items)) != MPS_OK) return st;
   if ((st = dalloc_t(h, &h->ws_w, h->ws_stride * items)) != MPS_OK) return st;
@@ -430,42 +450,45 @@ mps_status ensure_ws(mps_state* h, int items) {
   return MPS_OK;
 }
 
-// Preconditioning workspace of h for `items` gates (the factors), and of the
-// driver (per-item vectors); false, without any, when there is no room.  The
-// caller has marked it busy, so that an allocation does not give it back.
-bool ensure_pre(mps_state* h, int items) {
+// Preconditioning workspace of h for `items` gates (ensure_ws came before);
+// false, and nothing changed, when the budget has no room for it and for `more`
+// bytes beside it.  The device's refusal is remembered, so that a handle without
+// room pays for the attempt once, not in every batch.  The caller has marked the
+// workspace busy.
+bool ensure_pre(mps_state* h, int items, size_t more) {
   if (items <= h->pre_items) return true;
+  const size_t per_item = 2 * h->ws_stride * sizeof(double2) + 2 * h->ws_side * (sizeof(double) + sizeof(int));
+  const size_t others = h->held - (size_t)h->pre_items * per_item;
+  if (h->budget && others + (size_t)items * per_item + more > h->budget) return false;
+  if (h->pre_refused && items >= h->pre_refused && h->pre_refused_at == g_releases.load()) return false;
   if (sync(h) != MPS_OK) return false;
-  dfree(h, h->ws_l1);
-  dfree(h, h->ws_l2);
-  h->ws_l1 = h->ws_l2 = nullptr;
-  h->pre_items = 0;
-  if (dalloc_t(h, &h->ws_l1, h->ws_stride * items) != MPS_OK ||
-      dalloc_t(h, &h->ws_l2, h->ws_stride * items) != MPS_OK) {
-    dfree(h, h->ws_l1);
-    h->ws_l1 = h->ws_l2 = nullptr;
+  free_pre_items(h);
+  if (dalloc(h, &h->pre_ws, (size_t)items * per_item) != MPS_OK) {
+    h->pre_refused = items;
+    h->pre_refused_at = g_releases.load();
     return false;
   }
+  h->ws_l1 = (double2*)h->pre_ws;
+  h->ws_l2 = h->ws_l1 + h->ws_stride * items;
+  h->d_lqval = (double*)(h->ws_l2 + h->ws_stride * items);
+  h->d_lqidx = (int*)(h->d_lqval + 2 * h->ws_side * items);
   h->pre_items = items;
+  h->pre_refused = 0;
   return true;
 }
 
-bool ensure_lq_vectors(mps_state* drv, int items) {
-  if (items <= drv->lq_items) return true;
-  if (sync(drv) != MPS_OK) return false;
-  dfree(drv, drv->d_lqval);
-  dfree(drv, drv->d_lqidx);
-  drv->d_lqval = nullptr;
-  drv->d_lqidx = nullptr;
-  drv->lq_items = 0;
-  if (dalloc_t(drv, &drv->d_lqval, (size_t)2 * kLqMax * items) != MPS_OK ||
-      dalloc_t(drv, &drv->d_lqidx, (size_t)2 * kLqMax * items) != MPS_OK) {
-    dfree(drv, drv->d_lqval);
-    drv->d_lqval = nullptr;
-    drv->d_lqidx = nullptr;
-    return false;
-  }
-  drv->lq_items = items;
+bool lqdesc_room(const mps_state* h, size_t bytes) {
+  return bytes <= h->lqdesc_bytes || !h->budget || h->held - h->lqdesc_bytes + bytes <= h->budget;
+}
+
+bool ensure_lqdesc(mps_state* h, size_t bytes) {
+  if (bytes <= h->lqdesc_bytes) return true;
+  if (!lqdesc_room(h, bytes) || sync(h) != MPS_OK) return false;
+  dfree(h, h->d_lqdesc);
+  h->d_lqdesc = nullptr;
+  h->lqdesc_bytes = 0;
+  if (dalloc(h, &h->d_lqdesc, bytes) != MPS_OK) return false;
+  h->lqdesc_bytes = bytes;
   return true;
 }
 
@@ -834,27 +857,41 @@ mps_status apply_2q_refs(mps_state* drv, const std::vector<GateRef>& g, bool all
     ~PreBusy() { release(); }
   } busy;
   // descriptors of the launches: 256-byte aligned blocks
-  const size_t desc_direct = (sizeof(ThetaItem) + sizeof(MixItem) + sizeof(FinItem) + sizeof(TruncItem) +
-                              3 * sizeof(JacItem)) * items + 8 * 256;
-  const size_t desc_pre = desc_direct + (5 * sizeof(LqItem) + sizeof(LqFinItem) + sizeof(LqVecItem)) * items +
-                          8 * 256;
+  auto block = [](size_t bytes) { return (bytes + 255) & ~(size_t)255; };
+  const size_t desc_direct = block(sizeof(ThetaItem) * items) + block(sizeof(MixItem) * items) +
+                             block(sizeof(FinItem) * items) + block(sizeof(TruncItem) * items) +
+                             3 * sizeof(JacItem) * items + 512;
+  const size_t desc_pre = desc_direct + 5 * block(sizeof(LqItem) * items) + block(sizeof(LqFinItem) * items) +
+                          block(sizeof(LqVecItem) * items);
+  if ((st = ensure_desc(drv, desc_direct)) != MPS_OK) return st;
+  // Whether there is room is each handle's own matter: its gates are
+  // preconditioned or not whatever shares the batch.  The batch's descriptors
+  // go to the first handle that has room for them.
+  mps_state* home = nullptr;
   if (n_pre > 0) {
-    busy.take(drv);
-    bool room = ensure_desc(drv, desc_pre) == MPS_OK && ensure_lq_vectors(drv, items);
-    for (int b = 0; b < items && room; ++b) {
+    std::unordered_map<mps_state*, int> need;
+    for (int b = 0; b < items; ++b)
+      if (pre[b]) need[g[b].h] = std::max(need[g[b].h], slot[b] + 1);
+    const bool alone = need.size() == 1 && need.begin()->first == drv;
+    n_pre = 0;
+    for (int b = 0; b < items; ++b) {
       if (!pre[b]) continue;
-      if (!g[b].h->pre_busy) busy.take(g[b].h);
-      room = ensure_pre(g[b].h, slot[b] + 1);
+      mps_state* h = g[b].h;
+      if (!h->pre_busy) busy.take(h);
+      pre[b] = ensure_pre(h, need[h], alone ? desc_pre : 0);
+      n_pre += pre[b];
     }
-    if (!room) {  // the direct iteration needs none of it
-      const std::vector<mps_state*> hs = busy.hs;
-      busy.release();
-      for (mps_state* h : hs) drop_pre(h);
-      std::fill(pre.begin(), pre.end(), 0);
-      n_pre = 0;
+    if (n_pre > 0) {
+      if (!drv->pre_busy) busy.take(drv);
+      if (ensure_lqdesc(drv, desc_pre)) home = drv;
+      for (int b = 0; b < items && !home; ++b)
+        if (pre[b] && ensure_lqdesc(g[b].h, desc_pre)) home = g[b].h;
+      if (!home) {
+        std::fill(pre.begin(), pre.end(), 0);
+        n_pre = 0;
+      }
     }
   }
-  if ((st = ensure_desc(drv, n_pre > 0 ? desc_pre : desc_direct)) != MPS_OK) return st;
   std::vector<ThetaItem> th(items);
   std::vector<MixItem> mx(items);
   std::vector<JacItem> jc(items);
@@ -886,10 +923,11 @@ mps_status apply_2q_refs(mps_state* drv, const std::vector<GateRef>& g, bool all
       const int rows = 2 * dl, m = 2 * dr, n = std::min(rows, m), n1 = n;
       double2* f1 = h->ws_l1 + (size_t)slot[b] * h->ws_stride;
       double2* f2 = h->ws_l2 + (size_t)slot[b] * h->ws_stride;
-      double* norm2 = drv->d_lqval + (size_t)b * 2 * kLqMax;
-      double* inv = norm2 + kLqMax;
-      int* order = drv->d_lqidx + (size_t)b * 2 * kLqMax;
-      int* perm = order + kLqMax;
+      const size_t side = h->ws_side;
+      double* norm2 = h->d_lqval + (size_t)slot[b] * 2 * side;
+      double* inv = norm2 + side;
+      int* order = h->d_lqidx + (size_t)slot[b] * 2 * side;
+      int* perm = order + side;
       if (rows > m) {
         l0.push_back(LqItem{f2, nullptr, nullptr, w, nullptr, nullptr, nullptr, m, rows});
         tall_m = std::max(tall_m, m);
@@ -935,9 +973,12 @@ mps_status apply_2q_refs(mps_state* drv, const std::vector<GateRef>& g, bool all
   const size_t o_lf = place(lf.data(), sizeof(LqFinItem) * n_pre);
   const size_t o_lv = place(lv.data(), sizeof(LqVecItem) * n_pre);
   const size_t o_tr = place(tr.data(), sizeof(TruncItem) * items);
-  const size_t o_jac = blob.size();
-  if (o_jac + sizeof(JacItem) * items > drv->desc_bytes) return fail(MPS_ERR_STATE, "internal: descriptors");
-  char* d = (char*)drv->d_desc;
+  // the Jacobi descriptors follow, at the head of the driver's own if these are elsewhere
+  const size_t o_jac = n_pre > 0 ? 0 : blob.size();
+  if (blob.size() > (n_pre > 0 ? home->lqdesc_bytes : drv->desc_bytes) ||
+      o_jac + sizeof(JacItem) * items > drv->desc_bytes)
+    return fail(MPS_ERR_STATE, "internal: descriptors");
+  char* d = (char*)(n_pre > 0 ? home->d_lqdesc : drv->d_desc);
   if ((st = upload(drv, d, blob.data(), blob.size())) != MPS_OK) return st;
   HIP_TRY(drv, hipMemsetAsync(drv->d_fro2, 0, sizeof(double) * items, drv->stream));
   HIP_TRY(drv, hipMemsetAsync(drv->d_rot, 0, sizeof(int) * items * drv->max_sweeps, drv->stream));
@@ -2297,7 +2338,7 @@ mps_status fused_begin(mps_state* h) {
   if (st != MPS_OK) return st;
   if (h->max_sweeps >= kDefaultSweeps) {  // scratch for the LQ factors, if there is room
     h->pre_busy = true;
-    (void)ensure_pre(h, 1);
+    (void)ensure_pre(h, 1, 0);
     h->pre_busy = false;
   }
   if ((st = upload(h, h->d_dims, h->dims.data(), sizeof(int) * (h->n + 1))) != MPS_OK) return st;
@@ -2441,6 +2482,7 @@ mps_status mps_destroy(mps_handle h) {
     if (js) (void)hipStreamSynchronize(js);
   drop_graph(h->ex);
   for (auto& a : h->allocs) (void)hipFree(a.first);
+  g_releases.fetch_add(1);
   for (hipEvent_t e : h->ev_env) (void)hipEventDestroy(e);
   for (hipEvent_t e : h->ev_tune) (void)hipEventDestroy(e);
   for (hipEvent_t e : h->ev_close) (void)hipEventDestroy(e);

@@ -1,0 +1,129 @@
+"""Host orchestration against a stand-in for the HIP runtime (fake_hip.cpp):
+which workspaces are allocated, when, and what happens without room for the
+optional ones.  Each test runs in a process of its own, so that the stand-in
+never meets the real runtime."""
+
+import json
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+
+PRELUDE = """
+import ctypes, json, sys
+sys.modules["torch"] = None
+fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
+for f in ("fake_mallocs", "fake_frees", "fake_blocks"):
+    getattr(fake, f).restype = ctypes.c_longlong
+fake.fake_used.restype = ctypes.c_size_t
+fake.fake_set_capacity.argtypes = [ctypes.c_size_t]
+import numpy as np
+from paper_2303_03681_amd import binding
+
+def layers(n, count):
+    q0 = [q for _ in range(count) for s in (0, 1) for q in range(s, n - 1, 2)]
+    u = np.zeros((len(q0), 16, 2))
+    u[:, :, 0] = np.eye(4).ravel()
+    return np.array(q0), np.array(q0) + 1, u
+
+def preconditioned():
+    return fake.fake_blocks(b"14lq_rank_kernel")
+
+def direct():
+    return fake.fake_blocks(b"15finalize_kernel")
+"""
+
+
+@pytest.fixture(scope="module")
+def fake(tmp_path_factory):
+    out = tmp_path_factory.mktemp("fake") / "fake_hip.so"
+    subprocess.run(["g++", "-O1", "-std=c++17", "-shared", "-fPIC", "-I/opt/rocm/include",
+                    "-I" + os.path.join(ROOT, "paper_2303_03681_amd", "csrc"),
+                    os.path.join(ROOT, "tests", "fake_hip.cpp"), "-o", str(out)], check=True)
+
+    def run(script):
+        res = subprocess.run([sys.executable, "-c", PRELUDE + script, str(out)], capture_output=True, text=True,
+                             cwd=ROOT, timeout=120)
+        assert res.returncode == 0, res.stdout + res.stderr
+        return json.loads(res.stdout.splitlines()[-1])
+
+    return run
+
+
+SOLO = """
+n, D = 16, 80
+g, one = layers(n, 6), layers(n, 1)
+m = binding.Mps(n, D, 1e-14, max_jacobi_sweeps=59)
+m.set_fused_gates(False)
+m.apply_gates(*g)
+held = m.device_bytes() + 4 * (n // 2)  # the 60th sweep's rotation counters
+m.close()
+"""
+
+
+@pytest.mark.parametrize("fused", [False, True])
+def test_no_room_costs_no_allocations(fake, fused):
+    """A budget (or a device) that fits the direct iteration and part of the
+    factors: once the workspaces stand, a layer of gates allocates nothing."""
+    r = fake(SOLO + f"""
+out = []
+side = 2 * 80
+per = 2 * side * side * 16
+for extra in (0, per // 2, per + per // 2, 3 * per, 7 * per + 4000):
+    m = binding.Mps(n, D, 1e-14, hbm_budget_bytes=held + extra)
+    m.set_fused_gates({fused})
+    m.apply_gates(*g)
+    a, f = fake.fake_mallocs(), fake.fake_frees()
+    for _ in range(4):
+        m.apply_gates(*one)
+    out.append((fake.fake_mallocs() - a, fake.fake_frees() - f))
+    m.close()
+m = binding.Mps(n, D, 1e-14)
+m.set_fused_gates({fused})
+fake.fake_set_capacity(fake.fake_used() - m.device_bytes() + held + 3 * per)
+m.apply_gates(*g)
+a, f = fake.fake_mallocs(), fake.fake_frees()
+for _ in range(4):
+    m.apply_gates(*one)
+out.append((fake.fake_mallocs() - a, fake.fake_frees() - f))
+print(json.dumps(out))
+""")
+    # without a budget the device refuses: one attempt per batch size (7 or 8 gates) at the most
+    assert r[:-1] == [[0, 0]] * 5
+    assert r[-1][0] <= 2 and r[-1][1] == 0
+
+
+def test_a_budget_is_its_own_handles_matter(fake):
+    """One handle of a batch has no room for the factors: its gate is iterated
+    directly, the others' are preconditioned as they are alone."""
+    r = fake("""
+n, D = 16, 80
+g, one = layers(n, 6), layers(n, 1)
+held = {}
+def batch(budgets):
+    ms = [binding.Mps(n, D, 1e-14, hbm_budget_bytes=b) for b in budgets]
+    binding.apply_gates_multi(ms, [g] * len(ms))
+    p, d = preconditioned(), direct()
+    binding.apply_gates_multi(ms, [one] * len(ms))
+    out = (preconditioned() - p, direct() - d)
+    held[len(ms)] = [m.device_bytes() for m in ms]
+    for m in ms:
+        m.close()
+    return out
+alone = batch([0])
+pair = batch([0, 0])
+m = binding.Mps(n, D, 1e-14, max_jacobi_sweeps=59)
+binding.apply_gates_multi([m], [g])
+tight = m.device_bytes() + 8192  # a batch of three has its counters at the first handle
+m.close()
+print(json.dumps([alone, pair, batch([tight]), batch([0, tight]), batch([tight, 0]), batch([0, tight, 0])]))
+""")
+    alone, pair, tight, *mixed = r
+    gates = sum(alone)
+    assert alone[0] > 0 and pair == [2 * alone[0], 2 * alone[1]]
+    assert tight == [0, gates]
+    for m, k in zip(mixed, (1, 1, 2)):
+        assert m == [k * alone[0], k * alone[1] + gates]
