@@ -407,7 +407,9 @@ typedef struct {
 mps_status mps_set_timing(mps_handle h, int32_t enabled); /* also resets counters */
 mps_status mps_get_timing(mps_handle h, mps_timing* out);
 
-/* Device bytes currently held by the handle. */
+/* Device bytes currently held by the handle.  Optional workspaces of an idle
+ * handle (the factors of its preconditioned gates, GEMM1 outputs of its own per
+ * pass) are given back when an allocation, of any handle, finds the device full. */
 mps_status mps_device_bytes(mps_handle h, size_t* bytes);
 
 /* Layout self-check of the matrix-core instructions used by the dense

@@ -221,7 +221,9 @@ struct mps_state {
   double* d_pairs = nullptr;  // compensated energy pairs of mps_expect_pauli_sums
   size_t pairs_cap = 0;
   std::vector<std::pair<void*, size_t>> allocs;
+  std::mutex alloc_mutex;  // allocs and held: another handle may reclaim optional ones (reclaim)
   ExpectSetup ex;
+  bool ex_busy = false;    // an expectation uses ex
   // timing
   bool timing = false;
   bool autotune = false;               // choose environment GEMM tiles by measurement
@@ -261,32 +263,16 @@ mps_status dev_fail(mps_state* h, const char* what, hipError_t e) {
     if (e_ != hipSuccess) return dev_fail((h), #expr, e_); \
   } while (0)
 
-bool drop_pre(mps_state* h);
-
-mps_status dalloc(mps_state* h, void** p, size_t bytes) {
-  *p = nullptr;
-  if (bytes == 0) bytes = 256;
-  if (h->budget && h->held + bytes > h->budget) drop_pre(h);
-  if (h->budget && h->held + bytes > h->budget)
-    return fail(MPS_ERR_BUDGET, "HBM budget exceeded: need " + std::to_string(h->held + bytes) +
-                                    " bytes, budget " + std::to_string(h->budget));
-  hipError_t e = hipMalloc(p, bytes);
-  if (e != hipSuccess && drop_pre(h)) {
-    (void)hipGetLastError();
-    e = hipMalloc(p, bytes);
-  }
-  if (e != hipSuccess) {
-    (void)hipGetLastError();
-    *p = nullptr;
-    return fail(MPS_ERR_OOM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
-  }
-  h->held += bytes;
-  h->allocs.emplace_back(*p, bytes);
-  return MPS_OK;
-}
+// Every handle, and what may be taken from an idle one when the device is full:
+// the preconditioning workspace and the GEMM1 outputs kept apart per pass.
+// g_opt_mutex guards the list, the handles' pre_busy, fused_active and ex_busy
+// as seen by other threads, and the taking.
+std::mutex g_opt_mutex;
+std::vector<mps_state*>& g_handles = *new std::vector<mps_state*>();  // outlives every handle
 
 void dfree(mps_state* h, void* p) {
   if (!p) return;
+  std::lock_guard<std::mutex> lock(h->alloc_mutex);
   for (size_t i = 0; i < h->allocs.size(); ++i)
     if (h->allocs[i].first == p) {
       h->held -= h->allocs[i].second;
@@ -306,17 +292,93 @@ void free_pre_items(mps_state* h) {
   h->pre_items = 0;
 }
 
-// Gives the preconditioning workspace back; false if there is none (or a
-// batch is using it).
-bool drop_pre(mps_state* h) {
-  if (h->pre_busy || (!h->pre_ws && !h->d_lqdesc)) return false;
-  (void)hipStreamSynchronize(h->stream);
+// Give h's preconditioning workspace, or its GEMM1 outputs, back (g_opt_mutex
+// held); false if there is none or it is in use.  Idle means that no queued work
+// uses it either: a batch, a fused run and an expectation end with a
+// synchronisation.
+bool release_pre(mps_state* h) {
+  if (h->pre_busy || h->fused_active || (!h->pre_ws && !h->d_lqdesc)) return false;
   free_pre_items(h);
   dfree(h, h->d_lqdesc);
   h->d_lqdesc = nullptr;
   h->lqdesc_bytes = 0;
   return true;
 }
+
+bool release_x(mps_state* h) {
+  ExpectSetup& ex = h->ex;
+  if (h->ex_busy || !ex.x_apart || !ex.xbuf) return false;
+  dfree(h, ex.xbuf);
+  ex.xbuf = nullptr;
+  ex.xbuf_bytes = 0;
+  ex.x_apart = false;
+  ex.plan_serial = 0;  // the next expectation lays its plan out again
+  return true;
+}
+
+void drop_pre(mps_state* h) {
+  std::lock_guard<std::mutex> lock(g_opt_mutex);
+  (void)release_pre(h);
+}
+
+// hipMalloc once more after each release of an optional workspace on h's device,
+// its own first.
+hipError_t reclaim(mps_state* h, void** p, size_t bytes) {
+  std::lock_guard<std::mutex> lock(g_opt_mutex);
+  std::vector<mps_state*> from{h};
+  for (mps_state* o : g_handles)
+    if (o != h && o->device == h->device) from.push_back(o);
+  for (mps_state* o : from)
+    for (bool (*release)(mps_state*) : {release_pre, release_x}) {
+      if (!release(o)) continue;
+      if (hipMalloc(p, bytes) == hipSuccess) return hipSuccess;
+      (void)hipGetLastError();
+    }
+  return hipErrorOutOfMemory;
+}
+
+// optional: a workspace that its user can do without, so nothing is taken back for it.
+mps_status dalloc(mps_state* h, void** p, size_t bytes, bool optional = false) {
+  *p = nullptr;
+  if (bytes == 0) bytes = 256;
+  if (h->budget) {
+    if (h->held + bytes > h->budget) drop_pre(h);
+    if (h->held + bytes > h->budget)
+      return fail(MPS_ERR_BUDGET, "HBM budget exceeded: need " + std::to_string(h->held + bytes) +
+                                      " bytes, budget " + std::to_string(h->budget));
+  }
+  hipError_t e = hipMalloc(p, bytes);
+  if (e != hipSuccess) {
+    (void)hipGetLastError();
+    if (!optional) e = reclaim(h, p, bytes);
+  }
+  if (e != hipSuccess) {
+    *p = nullptr;
+    return fail(MPS_ERR_OOM, "hipMalloc of " + std::to_string(bytes) + " bytes failed");
+  }
+  std::lock_guard<std::mutex> lock(h->alloc_mutex);
+  h->held += bytes;
+  h->allocs.emplace_back(*p, bytes);
+  return MPS_OK;
+}
+
+// Marks in-use workspaces of handles until the end of a scope.
+struct Busy {
+  bool mps_state::*flag;
+  std::vector<mps_state*> hs;
+  explicit Busy(bool mps_state::*f) : flag(f) {}
+  Busy(bool mps_state::*f, mps_state* h) : flag(f) { take(h); }
+  void take(mps_state* h) {
+    std::lock_guard<std::mutex> lock(g_opt_mutex);
+    if (h->*flag) return;
+    h->*flag = true;
+    hs.push_back(h);
+  }
+  ~Busy() {
+    std::lock_guard<std::mutex> lock(g_opt_mutex);
+    for (mps_state* h : hs) h->*flag = false;
+  }
+};
 
 template <typename T>
 mps_status dalloc_t(mps_state* h, T** p, size_t count) {
@@ -398,9 +460,17 @@ mps_status ensure_desc(mps_state* h, size_t bytes) {
   return MPS_OK;
 }
 
-// Room for optional descriptor lists: with an HBM budget only what is there.
+// Room for optional descriptor lists: with an HBM budget, or a full device, only
+// what is there.
 bool room_for_lists(mps_state* h, size_t bytes) {
-  return bytes <= h->desc_bytes || (h->budget == 0 && ensure_desc(h, bytes) == MPS_OK);
+  if (bytes <= h->desc_bytes) return true;
+  void* p = nullptr;
+  const size_t want = std::max(bytes, (size_t)1 << 16);
+  if (h->budget || sync(h) != MPS_OK || dalloc(h, &p, want, true) != MPS_OK) return false;
+  dfree(h, h->d_desc);
+  h->d_desc = p;
+  h->desc_bytes = want;
+  return true;
 }
 
 // Per-item counters of a batched SVD (the rotation counters laid out
@@ -463,7 +533,7 @@ bool ensure_pre(mps_state* h, int items, size_t more) {
   if (h->pre_refused && items >= h->pre_refused && h->pre_refused_at == g_releases.load()) return false;
   if (sync(h) != MPS_OK) return false;
   free_pre_items(h);
-  if (dalloc(h, &h->pre_ws, (size_t)items * per_item) != MPS_OK) {
+  if (dalloc(h, &h->pre_ws, (size_t)items * per_item, true) != MPS_OK) {
     h->pre_refused = items;
     h->pre_refused_at = g_releases.load();
     return false;
@@ -487,7 +557,7 @@ bool ensure_lqdesc(mps_state* h, size_t bytes) {
   dfree(h, h->d_lqdesc);
   h->d_lqdesc = nullptr;
   h->lqdesc_bytes = 0;
-  if (dalloc(h, &h->d_lqdesc, bytes) != MPS_OK) return false;
+  if (dalloc(h, &h->d_lqdesc, bytes, true) != MPS_OK) return false;
   h->lqdesc_bytes = bytes;
   return true;
 }
@@ -844,18 +914,7 @@ mps_status apply_2q_refs(mps_state* drv, const std::vector<GateRef>& g, bool all
     pre[b] = h->max_sweeps >= kDefaultSweeps && n * m > kPreMin && std::max(n, m) <= kLqMax;
     n_pre += pre[b];
   }
-  struct PreBusy {  // the workspace stays while this batch uses it
-    std::vector<mps_state*> hs;
-    void take(mps_state* h) {
-      h->pre_busy = true;
-      hs.push_back(h);
-    }
-    void release() {
-      for (mps_state* h : hs) h->pre_busy = false;
-      hs.clear();
-    }
-    ~PreBusy() { release(); }
-  } busy;
+  Busy busy(&mps_state::pre_busy);  // the workspaces stay while this batch uses them
   // descriptors of the launches: 256-byte aligned blocks
   auto block = [](size_t bytes) { return (bytes + 255) & ~(size_t)255; };
   const size_t desc_direct = block(sizeof(ThetaItem) * items) + block(sizeof(MixItem) * items) +
@@ -877,12 +936,12 @@ mps_status apply_2q_refs(mps_state* drv, const std::vector<GateRef>& g, bool all
     for (int b = 0; b < items; ++b) {
       if (!pre[b]) continue;
       mps_state* h = g[b].h;
-      if (!h->pre_busy) busy.take(h);
+      busy.take(h);
       pre[b] = ensure_pre(h, need[h], alone ? desc_pre : 0);
       n_pre += pre[b];
     }
     if (n_pre > 0) {
-      if (!drv->pre_busy) busy.take(drv);
+      busy.take(drv);
       if (ensure_lqdesc(drv, desc_pre)) home = drv;
       for (int b = 0; b < items && !home; ++b)
         if (pre[b] && ensure_lqdesc(g[b].h, desc_pre)) home = g[b].h;
@@ -1377,12 +1436,12 @@ mps_status build_expect_with(mps_state* h, const mps_psum* ps, int prec, bool ap
   const size_t x_budget_elems = std::max(xmax_per, ((size_t)1 << 30) / el);  // ~1 GiB
   const int chunk_cap = (int)std::max<size_t>(1, x_budget_elems / xmax_per);
   // ---- allocate (re-use when large enough)
-  auto grow = [&](void** p, size_t& have, size_t want) -> mps_status {
+  auto grow = [&](void** p, size_t& have, size_t want, bool optional = false) -> mps_status {
     if (want <= have && *p) return MPS_OK;
     dfree(h, *p);
     *p = nullptr;
     have = 0;
-    mps_status s2 = dalloc(h, p, want);
+    mps_status s2 = dalloc(h, p, want, optional);
     if (s2 == MPS_OK) have = want;
     return s2;
   };
@@ -1410,7 +1469,7 @@ mps_status build_expect_with(mps_state* h, const mps_psum* ps, int prec, bool ap
   const size_t x_left = x_need(P.left), x_right = x_need(P.right);
   const size_t x_elems = apart ? x_left + x_right : std::max(x_left, x_right);
   ex.x_apart = apart;
-  if ((st = grow(&ex.xbuf, ex.xbuf_bytes, std::max<size_t>(1, x_elems) * el)) != MPS_OK) return st;
+  if ((st = grow(&ex.xbuf, ex.xbuf_bytes, std::max<size_t>(1, x_elems) * el, apart)) != MPS_OK) return st;
   char* poolp = (char*)ex.pool;
   char* sitep = (char*)ex.sites;
   auto lref_ptr = [&](int32_t ref) -> char* {
@@ -2119,6 +2178,7 @@ mps_status expect_impl(mps_state* h, const mps_psum* ps, int prec, double* energ
   mps_status st;
   const double t0 = now_ms();
   const double2* nrm = nullptr;
+  Busy busy(&mps_state::ex_busy, h);
   CallLists lists;
   if ((st = expect_open(h, ps, prec, &nrm, &lists)) != MPS_OK) return st;
   ExpectSetup& ex = h->ex;
@@ -2265,6 +2325,8 @@ mps_status expect_multi_impl(mps_state* const* hs, const mps_psum* const* ps, in
   const int el = prec == MPS_PREC_C128 ? 16 : 8;
   const double t0 = now_ms();
   mps_status st;
+  Busy busy(&mps_state::ex_busy);
+  for (int i = 0; i < count; ++i) busy.take(hs[i]);
   std::vector<const double2*> nrm(count, nullptr);
   std::vector<int> rmin(count, 0), stale(count, 0);
   for (int i = 0; i < count; ++i) {
@@ -2336,16 +2398,14 @@ mps_status fused_begin(mps_state* h) {
   if (h->fused_active) return MPS_OK;
   mps_status st = ensure_ws(h, 1);
   if (st != MPS_OK) return st;
-  if (h->max_sweeps >= kDefaultSweeps) {  // scratch for the LQ factors, if there is room
-    h->pre_busy = true;
-    (void)ensure_pre(h, 1, 0);
-    h->pre_busy = false;
-  }
+  Busy busy(&mps_state::pre_busy, h);
+  if (h->max_sweeps >= kDefaultSweeps) (void)ensure_pre(h, 1, 0);  // scratch for the LQ factors, if there is room
   if ((st = upload(h, h->d_dims, h->dims.data(), sizeof(int) * (h->n + 1))) != MPS_OK) return st;
   HIP_TRY(h, hipMemsetAsync(h->d_fstat, 0, 2 * sizeof(int), h->stream));
   HIP_TRY(h, hipMemsetAsync(h->d_fdisc, 0, sizeof(double), h->stream));
   HIP_TRY(h, hipMemsetAsync(h->d_fsweeps, 0, sizeof(int), h->stream));
-  h->fused_active = true;
+  std::lock_guard<std::mutex> lock(g_opt_mutex);
+  h->fused_active = true;  // the workspace stays until fused_flush
   return MPS_OK;
 }
 
@@ -2366,7 +2426,10 @@ mps_status fused_flush(mps_state* h, int64_t* failed_at, int* code) {
   HIP_TRY(h, hipMemcpyAsync(&sweeps, h->d_fsweeps, sizeof(int), hipMemcpyDeviceToHost, h->stream));
   mps_status st = sync(h);
   if (st != MPS_OK) return st;
-  h->fused_active = false;
+  {
+    std::lock_guard<std::mutex> lock(g_opt_mutex);
+    h->fused_active = false;
+  }
   for (int b = 0; b <= h->n; ++b)
     if (dims[b] < 1 || dims[b] > h->cap[b]) {
       h->poisoned = true;
@@ -2470,12 +2533,18 @@ mps_status mps_create(const mps_config* cfg, mps_handle* out) {
   const double one = 1.0;
   HIP_TRY(h.get(), hipMemcpy(h->d_one, &one, sizeof(double), hipMemcpyHostToDevice));
   if ((st = mps_reset(h.get(), cfg->init_bits)) != MPS_OK) return st;
+  std::lock_guard<std::mutex> lock(g_opt_mutex);
+  g_handles.push_back(h.get());
   *out = h.release();
   return MPS_OK;
 }
 
 mps_status mps_destroy(mps_handle h) {
   if (!h) return MPS_OK;
+  {
+    std::lock_guard<std::mutex> lock(g_opt_mutex);
+    g_handles.erase(std::remove(g_handles.begin(), g_handles.end(), h), g_handles.end());
+  }
   if (h->stream) (void)hipStreamSynchronize(h->stream);
   if (h->side) (void)hipStreamSynchronize(h->side);
   for (hipStream_t js : h->jside)
@@ -3091,6 +3160,7 @@ mps_status mps_jacobi_svd(int32_t n_vec, int32_t vec_len, const double* vectors,
     return fail(MPS_ERR_NONFINITE, "non-finite input");
   mps_state tmp;
   tmp.n = 1;
+  HIP_TRY(nullptr, hipGetDevice(&tmp.device));
   HIP_TRY(nullptr, hipStreamCreateWithFlags(&tmp.stream, hipStreamNonBlocking));
   tmp.own_stream = true;
   struct Guard {
@@ -3377,6 +3447,7 @@ mps_status mps_device_bytes(mps_handle h, size_t* bytes) {
   mps_status st = check_handle(h);
   if (st != MPS_OK) return st;
   if (!bytes) return fail(MPS_ERR_ARG, "NULL output");
+  std::lock_guard<std::mutex> lock(h->alloc_mutex);
   *bytes = h->held;
   return MPS_OK;
 }

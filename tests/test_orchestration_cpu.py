@@ -127,3 +127,129 @@ print(json.dumps([alone, pair, batch([tight]), batch([0, tight]), batch([tight, 
     assert tight == [0, gates]
     for m, k in zip(mixed, (1, 1, 2)):
         assert m == [k * alone[0], k * alone[1] + gates]
+
+
+FULL = """
+def state(n, D, **kw):
+    m = binding.Mps(n, D, 1e-14, **kw)
+    m.set_fused_gates(False)
+    m.apply_gates(*layers(n, 8))
+    return m
+
+def strings(n, count):
+    codes = np.unique(np.random.default_rng(n).integers(0, 4, size=(count, n)).astype(np.uint8), axis=0)
+    return binding.PauliSum(codes, np.ones(len(codes)))
+
+def room(extra):
+    fake.fake_set_capacity(fake.fake_used() + extra)
+
+n, D = 16, 80
+m = state(n, D, max_jacobi_sweeps=59)
+need = m.device_bytes()
+m.close()
+"""
+
+
+def test_idle_handles_give_optional_workspaces_back(fake):
+    """A handle that fitted beside another one without its optional workspaces
+    (the factors, the second pass' GEMM1 outputs) fits beside one with them."""
+    r = fake(FULL + """
+a = state(n, D)
+bare = need + 4 * (n // 2)                 # the 60th sweep's rotation counters
+pre = a.device_bytes() - bare
+room(need - pre // 2)
+b = state(n, D, max_jacobi_sweeps=59)      # takes the factors back
+out = [pre, a.device_bytes() - bare]
+room(1 << 30)
+p = preconditioned()
+a.apply_gates(*layers(n, 1))
+out += [a.device_bytes() - bare - pre, preconditioned() - p]
+a.canonicalize()
+plan = strings(n, 400)
+a.expect(plan, "c128")
+held = a.device_bytes()
+b.close()
+room(need - pre - (1 << 20))               # the factors alone would not do
+b = state(n, D, max_jacobi_sweeps=59)
+out += [held - a.device_bytes() - pre]
+b.close()
+room(held)
+out += [a.expect(plan, "c128"), held - a.device_bytes()]
+a.close()
+out += [fake.fake_used()]
+print(json.dumps(out))
+""")
+    pre, left, back, again, more, e, missing, used = r
+    assert pre > 1 << 20 and left == 0
+    assert back == 0 and again > 0
+    assert more > 1 << 20
+    assert e == 0.0 and missing == pre  # the GEMM1 outputs are back, the factors wait for gates
+    assert used == 0
+
+
+def test_full_device_shares_gemm1_outputs(fake):
+    """No room for GEMM1 outputs per pass: the expectation runs with shared ones,
+    as under a budget, and repeats without allocating."""
+    r = fake(FULL + """
+plan = strings(n, 400)
+held = []
+for kw in ({"hbm_budget_bytes": 1 << 34}, {}):
+    m = state(n, D, **kw)
+    m.canonicalize()
+    before = m.device_bytes()
+    m.expect(plan, "c128")
+    held.append(m.device_bytes() - before)
+    m.close()
+m = state(n, D, max_jacobi_sweeps=59)
+m.canonicalize()
+before = m.device_bytes()
+room((held[0] + held[1]) // 2)
+m.expect(plan, "c128")
+held.append(m.device_bytes() - before)
+a = fake.fake_mallocs()
+m.expect(plan, "c128")
+binding.expect_multi([m], [plan], "c128")
+print(json.dumps(held + [fake.fake_mallocs() - a]))
+""")
+    shared, apart, full, again = r
+    assert apart > shared + (1 << 20)
+    assert full == shared and again == 0
+
+
+def test_threads_on_a_full_device(fake):
+    """Handles of several threads take each other's optional workspaces back:
+    every call succeeds or reports no memory, and the books balance."""
+    r = fake(FULL + """
+import threading
+plan = strings(n, 200)
+ms = [state(n, D) for _ in range(4)]
+for m in ms:
+    m.canonicalize()
+room(500 << 20)
+bad, done = [], [0] * 4
+def work(i):
+    rng = np.random.default_rng(i)
+    for k in range(60):
+        try:
+            if rng.random() < 0.5:
+                ms[i].apply_gates(*layers(n, 1))
+                ms[i].canonicalize()
+            elif rng.random() < 0.7:
+                assert ms[i].expect(plan, "c128") == 0.0
+            else:
+                x = state(n, D)
+                x.close()
+            done[i] += 1
+        except binding.MpsError as e:
+            if e.name != "MPS_ERR_OOM":
+                bad.append(str(e))
+t = [threading.Thread(target=work, args=(i,)) for i in range(4)]
+[x.start() for x in t]
+[x.join() for x in t]
+held = sum(m.device_bytes() for m in ms) - fake.fake_used()
+[m.close() for m in ms]
+print(json.dumps([bad, done, held, fake.fake_used()]))
+""")
+    bad, done, held, used = r
+    assert bad == [] and min(done) > 0
+    assert held == 0 and used == 0
