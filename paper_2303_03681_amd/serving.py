@@ -105,16 +105,19 @@ class Request:
         return self.finish - self.arrival
 
 
-def estimate_bytes(n_qubits: int, max_bond: int, n_env_updates: int, prec_bytes: int = 8) -> int:
+def estimate_bytes(n_qubits: int, max_bond: int, n_env_updates: int, prec_bytes: int = 8,
+                   x_parents: int = 128) -> int:
     """Upper estimate of one fragment's device memory: two site and lambda
-    buffers, the gate workspaces, the environment pool and its scratch."""
+    buffers, the gate workspaces with the two factors of a preconditioned SVD,
+    the environment pool and the GEMM1 outputs of both passes (`x_parents`
+    parents held at once, up to 1 GiB a pass)."""
     caps = [min(max_bond, 2 ** min(b, n_qubits - b)) for b in range(n_qubits + 1)]
     sites = sum(2 * 2 * caps[q] * caps[q + 1] * 16 for q in range(n_qubits))
     dmax = max(caps)
-    ws = 2 * (2 * dmax) ** 2 * 16 + 2 * dmax * dmax * 16
+    ws = 4 * (2 * dmax) ** 2 * 16 + 2 * dmax * dmax * 16
     pool = (n_env_updates + 2 * (n_qubits + 1)) * dmax * dmax * prec_bytes
     prepared = 2 * sites
-    scratch = 64 * dmax * 2 * dmax * prec_bytes
+    scratch = min(x_parents * dmax * 2 * dmax * prec_bytes, 2 << 30)
     return int(sites + ws + pool + prepared + scratch + (8 << 20))
 
 
@@ -148,6 +151,16 @@ class GpuBackend:
     def plan_updates(self, frag: Fragment) -> int:
         st = self._plan(frag).stats()
         return int(st["left_updates"] + st["right_updates"])
+
+    def plan_parents(self, frag: Fragment) -> int:
+        """Parents whose GEMM1 outputs are held at once: the most distinct ones
+        at a site, of the left and of the right pass."""
+        plan = self._plan(frag).export()
+        total = 0
+        for parent, site, _ in (plan["left"], plan["right"]):
+            pairs = np.unique(np.stack([site, parent], axis=1), axis=0)
+            total += int(np.unique(pairs[:, 0], return_counts=True)[1].max(initial=0))
+        return total
 
     def reset(self, handle, frag: Fragment):
         handle.reset(frag.bits)
@@ -261,8 +274,10 @@ class Server:
         if frag.fid in self.resident:
             return 0
         if not frag.est_bytes:
+            parents = getattr(self.backend, "plan_parents", None)
+            kw = {} if parents is None else {"x_parents": parents(frag)}
             frag.est_bytes = estimate_bytes(frag.n_qubits, frag.max_bond,
-                                            self.backend.plan_updates(frag))
+                                            self.backend.plan_updates(frag), **kw)
         return frag.est_bytes
 
     def _used(self) -> int:

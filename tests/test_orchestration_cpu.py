@@ -253,3 +253,30 @@ print(json.dumps([bad, done, held, fake.fake_used()]))
     bad, done, held, used = r
     assert bad == [] and min(done) > 0
     assert held == 0 and used == 0
+
+
+@pytest.mark.parametrize("qubits,bond,strings", [(12, 32, 2000), (16, 64, 4000), (24, 64, 6000), (32, 128, 8000),
+                                                 (40, 128, 8000)])
+def test_serving_estimate_is_an_upper_one(fake, qubits, bond, strings):
+    """Device memory of a served fragment whose bonds are all at their cap."""
+    r = fake(f"""
+fake.fake_set_capacity(1 << 36)
+from paper_2303_03681_amd import serving
+from workloads.configs import build_serving_fragments
+frag = serving.Fragment.from_dict(build_serving_fragments(1, 1, qubits=({qubits},), bonds=({bond},),
+                                                          max_strings={strings})[0])
+back = serving.GpuBackend.__new__(serving.GpuBackend)
+back.binding, back.prec, back.plans = binding, "c64", {{}}
+server = serving.Server([frag], back, hbm_budget=1 << 40)
+m = back.create(frag)
+binding.apply_gates_multi([m], [layers({qubits}, 10)])
+try:
+    back.expect_many([(m, frag)])
+except binding.MpsError as e:  # the stand-in computes no norm
+    assert e.name == "MPS_ERR_NONFINITE"
+print(json.dumps([server._need(frag), m.device_bytes(), int(m.bond_dims().max()), back.plan_updates(frag)]))
+""")
+    est, held, most, updates = r
+    print(f"{qubits} qubits D = {bond}: estimate {est / 1e6:.1f} MB, held {held / 1e6:.1f} MB, {updates} updates")
+    assert most == bond
+    assert held <= est <= 3 * held
