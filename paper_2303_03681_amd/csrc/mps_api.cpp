@@ -2092,9 +2092,12 @@ mps_status run_set_up(mps_state* drv, const CallLists& c, mps_state* const* hs, 
 
 // One merged depth: fused updates while the dims are small (c128 and c64), else
 // one launch per GEMM half.
+bool env_fused(const EnvMerged& m, int prec) {
+  return prec <= MPS_PREC_C64 && m.max_dl <= kEnvFused && m.max_dr <= kEnvFused;
+}
+int env_launches(const EnvMerged& m, int prec) { return env_fused(m, prec) ? 1 : 2; }
 hipError_t run_env_merged(const EnvMerged& m, int prec, hipStream_t s) {
-  if (prec <= MPS_PREC_C64 && m.max_dl <= kEnvFused && m.max_dr <= kEnvFused) return launch_env_small(m, prec, s);
-  return launch_env_merged(m, prec, s);
+  return env_fused(m, prec) ? launch_env_small(m, prec, s) : launch_env_merged(m, prec, s);
 }
 
 // The expectation's set-up on h's stream: the plan's device layout, the site
@@ -2199,7 +2202,7 @@ mps_status expect_impl(mps_state* h, const mps_psum* ps, int prec, double* energ
       HIP_TRY(h, run_env_merged(lists.placed(m), prec, h->stream));
       if (timed) {
         HIP_TRY(h, hipEventRecord(e, h->stream));
-        h->tm.env_launches += 2;
+        h->tm.env_launches += env_launches(m, prec);
       }
     }
     for (int pass = 0; pass < 2; ++pass)
@@ -2355,7 +2358,8 @@ mps_status expect_multi_impl(mps_state* const* hs, const mps_psum* const* ps, in
       hs[i]->chain_version = hs[i]->version;
       hs[i]->chain_rmin = rmin[i];
     }
-  if (drv->timing) drv->tm.env_launches += 2 * (int64_t)lists.env.size();
+  if (drv->timing)
+    for (const EnvMerged& m : lists.env) drv->tm.env_launches += env_launches(m, prec);
   std::vector<double> e2(2 * (size_t)count, 0.0);
   std::vector<double2> nn(count, make_double2(1.0, 0.0));
   for (int i = 0; i < count; ++i) {

@@ -20,7 +20,7 @@ namespace {
 std::mutex mtx;
 std::map<void*, size_t> live;
 std::map<const void*, std::string> kernels;
-std::map<std::string, long long> blocks;  // thread blocks launched, by kernel name
+std::map<std::string, long long> blocks, launches;  // thread blocks and launches, by kernel name
 size_t capacity = (size_t)1 << 34, used = 0;
 long long mallocs = 0, frees = 0;
 thread_local dim3 cfg_grid, cfg_block;
@@ -39,13 +39,15 @@ void fake_set_capacity(size_t bytes) { capacity = bytes; }
 size_t fake_used() { return used; }
 long long fake_mallocs() { return mallocs; }
 long long fake_frees() { return frees; }
-long long fake_blocks(const char* kernel) {
+static long long count(const std::map<std::string, long long>& by_name, const char* kernel) {
   std::lock_guard<std::mutex> l(mtx);
   long long n = 0;
-  for (auto& b : blocks)
+  for (auto& b : by_name)
     if (b.first.find(kernel) != std::string::npos) n += b.second;
   return n;
 }
+long long fake_blocks(const char* kernel) { return count(blocks, kernel); }
+long long fake_launches(const char* kernel) { return count(launches, kernel); }
 
 hipError_t hipMalloc(void** p, size_t n) {
   std::lock_guard<std::mutex> l(mtx);
@@ -152,6 +154,7 @@ hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void** args, size_t, 
     std::lock_guard<std::mutex> l(mtx);
     name = kernels[f];
     blocks[name] += (long long)grid.x * grid.y * grid.z;
+    ++launches[name];
   }
   auto is = [&](const char* k) { return name.find(k) != std::string::npos; };
   if (is("15finalize_kernel")) {

@@ -16,7 +16,7 @@ PRELUDE = """
 import ctypes, json, sys
 sys.modules["torch"] = None
 fake = ctypes.CDLL(sys.argv[1], mode=ctypes.RTLD_GLOBAL)
-for f in ("fake_mallocs", "fake_frees", "fake_blocks"):
+for f in ("fake_mallocs", "fake_frees", "fake_blocks", "fake_launches"):
     getattr(fake, f).restype = ctypes.c_longlong
 fake.fake_used.restype = ctypes.c_size_t
 fake.fake_set_capacity.argtypes = [ctypes.c_size_t]
@@ -280,3 +280,26 @@ print(json.dumps([server._need(frag), m.device_bytes(), int(m.bond_dims().max())
     print(f"{qubits} qubits D = {bond}: estimate {est / 1e6:.1f} MB, held {held / 1e6:.1f} MB, {updates} updates")
     assert most == bond
     assert held <= est <= 3 * held
+
+
+@pytest.mark.parametrize("D,prec", [(8, "c128"), (32, "c64"), (33, "c128"), (80, "c64"), (16, "split_f16")])
+def test_environment_launches_are_counted_as_made(fake, D, prec):
+    """mps_timing.env_launches against the launches of the environment kernels,
+    alone and together with another state."""
+    r = fake(FULL + f"""
+def made():
+    return fake.fake_launches(b"env_small_kernel") + fake.fake_launches(b"EnvG")
+a, b = state(16, {D}), state(16, {D})
+for m in (a, b):
+    m.canonicalize()
+plan, other = strings(16, 400), strings(16, 90)
+out = []
+for run in (lambda: a.expect(plan, "{prec}"), lambda: binding.expect_multi([a, b], [plan, other], "{prec}")):
+    a.set_timing(True)
+    before = made()
+    run()
+    out += [made() - before, a.timing()["env_launches"]]
+print(json.dumps(out))
+""")
+    assert r[0] > 0 and r[2] > 0
+    assert r[1] == r[0] and r[3] == r[2]
