@@ -71,9 +71,12 @@ def test_uccsd_chain_keeps_its_state(gpu_lib, fused):
     m.set_fused_gates(fused)
     m.apply_gates(*pack_gates(gates))
     v = m.to_statevector()
+    m.canonicalize()
+    w = m.to_statevector()
     m.close()
     err = 1.0 - abs(np.vdot(psi, v)) / np.linalg.norm(v)
     print(f"fused {fused}: 1 - overlap {err:.1e}, norm - 1 {np.linalg.norm(v) - 1:.1e}", flush=True)
     # 300 gates, each within its tolerance above of the exact product; the overlap is quadratic in them
     assert err <= 1e-12
     assert abs(np.linalg.norm(v) - 1.0) <= 300 * 2e-12
+    assert 1.0 - abs(np.vdot(psi, w)) / np.linalg.norm(w) <= 1e-12  # in exact canonical form too
