@@ -7,6 +7,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
+#include <vector>
 
 namespace mps {
 
@@ -313,8 +314,14 @@ hipError_t launch_roots(const double* lam, void* lroot, void* rroot, int d, int 
 int gram_splits(int max_kdim);  // K splits of the closing-trace tiles
 hipError_t launch_gram(const GramItem* items_dev, const GramTile* tiles_dev, int n_tiles, int elem_bytes,
                        double* part, int splits, hipStream_t s);
-// whether a bond's traces are taken pair by pair rather than in 64 x 64 tiles
-bool gram_as_pairs(int64_t pairs, int64_t tiles, int kdim, int elem_bytes);
+// Work of one bond's closing traces: needed pairs, groups of up to kGramGroup of
+// them with one left environment, 64 x 64 tiles that hold one, elements of each.
+struct GramWork {
+  int64_t pairs, groups, tiles;
+  int kdim;
+};
+// which bonds' traces are taken pair by pair rather than in tiles
+std::vector<char> gram_choose(const std::vector<GramWork>& bonds, int elem_bytes);
 hipError_t launch_gram_pairs(const GramGroup* groups_dev, const GramPair* pairs_dev, int groups, int elem_bytes,
                              hipStream_t s);
 hipError_t launch_rows(const double* per_term, const int64_t* row_ptr, const int64_t* cols, const double* vals,

@@ -20,6 +20,7 @@
 #include <cstdint>
 #include <mutex>
 #include <type_traits>
+#include <vector>
 
 #include "gemm_core.h"
 #include "gemm_split.h"
@@ -2170,16 +2171,52 @@ __global__ __launch_bounds__(256) void gram_pairs_kernel(const GramGroup* groups
   }
 }
 
-// Tiles run at about 38 TFLOP/s of whole tiles (a 64 x 64 tile at D = 256
-// takes 28 us of the chip however many of its 4096 pairs are needed), or, when
-// there are too few to fill it, at 1.6 us per chunk of 16 along K on one
-// workgroup each; pairs stream at about 5 TB/s (0.10 us of the chip per pair
-// at D = 256 in c64, 0.26 us in c128).  32,769 strings on 50 qubits, D = 256,
-// c64: 15.1 ms in tiles, 3.4 ms as pairs.
-bool gram_as_pairs(int64_t pairs, int64_t tiles, int kdim, int elem_bytes) {
-  const double tile_us = std::max((double)tiles * 4096 * 4 * kdim / 38e6, kdim / 16 * 1.6 / gram_splits(kdim));
-  const double pair_us = 3.0 + (double)pairs * kdim * elem_bytes * 1.3 / 5e6;
-  return pair_us <= tile_us;
+// Tiles take the matrix cores' time for all of their 4096 pairs, 22.5 us of the
+// chip per 65536 elements in c128 and 28 us in c64 (converted on the way), and,
+// however few they are, that of one tile's K range on one workgroup, 0.1 and
+// 0.2 us an element (a third of it also where they are many).  Pairs stream their
+// environments (the left one once per group) at about 7.5 TB/s, after 5 us.  All bonds' tiles are one launch and all
+// pairs another, so the choice is made for all bonds together: the k bonds that
+// gain most as tiles are tiles, for the k of least total.  Closes of molecular
+// sums in ms, as tiles / as pairs / by this rule / chosen bond by bond, where the
+// few tiles of every bond seemed bound by one workgroup's K range:
+//   40 qubits D = 128 c128,  16,385 strings  1.53   0.89  0.89   0.90
+//                           200,001          2.16   8.47  2.19   4.20
+//   50 qubits D = 256 c128,  32,769         12.6    7.20  7.17   7.18
+//                           262,144         11.9   46.2  11.8   13.9
+//   50 qubits D = 256 c64,   32,769         14.8    3.44  3.46   3.46
+//                           262,144         14.1   23.9  14.3   15.6
+std::vector<char> gram_choose(const std::vector<GramWork>& bonds, int elem_bytes) {
+  const int n = (int)bonds.size();
+  const double per_tile = elem_bytes == 16 ? 22.5 : 28.0, per_k = elem_bytes == 16 ? 0.1 : 0.2;
+  std::vector<double> pair_us(n), tile_us(n);
+  double pairs = 0.0;
+  for (int i = 0; i < n; ++i) {
+    pair_us[i] = (double)(bonds[i].pairs + bonds[i].groups) * bonds[i].kdim * elem_bytes / 7.5e6;
+    tile_us[i] = (double)bonds[i].tiles * bonds[i].kdim * per_tile / 65536;
+    pairs += pair_us[i];
+  }
+  std::vector<int> order(n);
+  for (int i = 0; i < n; ++i) order[i] = i;
+  std::stable_sort(order.begin(), order.end(),
+                   [&](int a, int b) { return pair_us[a] - tile_us[a] > pair_us[b] - tile_us[b]; });
+  int best = 0, longest = 0;
+  double least = 5.0 + pairs, tiles = 0.0;
+  for (int k = 1; k <= n; ++k) {
+    const int i = order[k - 1];
+    tiles += tile_us[i];
+    pairs -= pair_us[i];
+    longest = std::max(longest, bonds[i].kdim);
+    const double one = per_k * longest / gram_splits(longest);
+    const double cost = std::max(one, tiles + 0.3 * one) + (k < n ? 5.0 + pairs : 0.0);
+    if (cost < least) {
+      least = cost;
+      best = k;
+    }
+  }
+  std::vector<char> as_pairs(n, 1);
+  for (int k = 0; k < best; ++k) as_pairs[order[k]] = 0;
+  return as_pairs;
 }
 
 hipError_t launch_gram_pairs(const GramGroup* groups_dev, const GramPair* pairs_dev, int groups, int elem_bytes,

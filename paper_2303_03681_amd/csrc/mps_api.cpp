@@ -1562,11 +1562,22 @@ mps_status build_expect_with(mps_state* h, const mps_psum* ps, int prec, bool ap
   std::vector<std::vector<const void*>> lptrs, rptrs;
   ex.gram_flops = 0.0;
   ex.pair_flops = 0.0;
+  struct BondCloses {
+    int bond;
+    std::vector<int32_t> lref, rref;
+    std::vector<int> pa, pb;      // pair endpoints (first-appearance indices)
+    std::vector<int> lpos, rpos;  // their places in the tiles
+    std::vector<char> used;       // tiles with a needed pair
+  };
+  std::vector<BondCloses> closes;
+  std::vector<GramWork> work;
   for (int c = 0; c <= n; ++c) {
     if (by_bond[c].empty()) continue;
+    closes.push_back(BondCloses{c, {}, {}, {}, {}, {}, {}, {}});
+    BondCloses& bc = closes.back();
     std::unordered_map<int32_t, int> li, ri;
-    std::vector<int32_t> lref, rref;
-    std::vector<int> pa, pb;  // pair endpoints (first-appearance indices)
+    std::vector<int32_t>&lref = bc.lref, &rref = bc.rref;
+    std::vector<int>&pa = bc.pa, &pb = bc.pb, &lpos = bc.lpos, &rpos = bc.rpos;
     for (int64_t k : by_bond[c]) {
       auto a = li.emplace(P.close_left[k], (int)lref.size());
       if (a.second) lref.push_back(P.close_left[k]);
@@ -1576,14 +1587,17 @@ mps_status build_expect_with(mps_state* h, const mps_psum* ps, int prec, bool ap
       pb.push_back(b.first->second);
     }
     const int nl = (int)lref.size(), nr = (int)rref.size();
-    int64_t n_distinct = 0;
+    GramWork gw{0, 0, 0, D[c] * D[c]};
     {  // the method's own work: Re Tr(L R) = 4 D^2 FLOPs per distinct pair
       std::unordered_set<int64_t> distinct;
-      for (size_t q = 0; q < pa.size(); ++q) distinct.insert((int64_t)pa[q] * nr + pb[q]);
-      n_distinct = (int64_t)distinct.size();
-      ex.pair_flops += 4.0 * (double)n_distinct * D[c] * D[c];
+      std::vector<int> of_left(nl, 0);
+      for (size_t q = 0; q < pa.size(); ++q)
+        if (distinct.insert((int64_t)pa[q] * nr + pb[q]).second && of_left[pa[q]]++ % kGramGroup == 0) ++gw.groups;
+      gw.pairs = (int64_t)distinct.size();
+      ex.pair_flops += 4.0 * (double)gw.pairs * D[c] * D[c];
     }
-    std::vector<int> lpos(nl), rpos(nr);
+    lpos.resize(nl);
+    rpos.resize(nr);
     for (int i = 0; i < nl; ++i) lpos[i] = i;
     for (int i = 0; i < nr; ++i) rpos[i] = i;
     if (nl > 64 && nr > 64) {
@@ -1610,17 +1624,25 @@ mps_status build_expect_with(mps_state* h, const mps_psum* ps, int prec, bool ap
         }
       }
     }
-    const int item = (int)gram.size();
     const int tcols = (nr + 63) / 64;
-    std::vector<char> used((size_t)((nl + 63) / 64) * tcols, 0);
-    int64_t n_used = 0;
+    bc.used.assign((size_t)((nl + 63) / 64) * tcols, 0);
     for (size_t q = 0; q < pa.size(); ++q) {
-      char& u = used[(size_t)(lpos[pa[q]] / 64) * tcols + rpos[pb[q]] / 64];
-      n_used += !u;
+      char& u = bc.used[(size_t)(lpos[pa[q]] / 64) * tcols + rpos[pb[q]] / 64];
+      gw.tiles += !u;
       u = 1;
     }
+    work.push_back(gw);
+  }
+  const std::vector<char> as_pairs = gram_choose(work, (int)el);
+  for (size_t i = 0; i < closes.size(); ++i) {
+    const BondCloses& bc = closes[i];
+    const int c = bc.bond, nl = (int)bc.lref.size(), nr = (int)bc.rref.size(), tcols = (nr + 63) / 64;
+    const std::vector<int32_t>&lref = bc.lref, &rref = bc.rref;
+    const std::vector<int>&pa = bc.pa, &pb = bc.pb, &lpos = bc.lpos, &rpos = bc.rpos;
+    const std::vector<char>& used = bc.used;
+    const int item = (int)gram.size();
     // few needed pairs per tile: each pair by itself, the pairs of one prefix together
-    if (gram_as_pairs(n_distinct, n_used, D[c] * D[c], (int)el)) {
+    if (as_pairs[i]) {
       std::vector<std::pair<int64_t, int64_t>> key(pa.size());  // (pair, string)
       for (size_t q = 0; q < pa.size(); ++q) key[q] = {(int64_t)pa[q] * nr + pb[q], by_bond[c][q]};
       std::sort(key.begin(), key.end());

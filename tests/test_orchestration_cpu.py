@@ -303,3 +303,41 @@ print(json.dumps(out))
 """)
     assert r[0] > 0 and r[2] > 0
     assert r[1] == r[0] and r[3] == r[2]
+
+
+CLOSES = """
+def exchange(n, count):
+    rng = np.random.default_rng(n)
+    idx = np.sort(np.argsort(rng.random((count, n)), axis=1)[:, :4], axis=1)
+    cols, rows = np.arange(n), np.arange(count)
+    p, q, r, s = (idx[:, k:k + 1] for k in range(4))
+    codes = 3 * (((cols > p) & (cols < q)) | ((cols > r) & (cols < s))).astype(np.uint8)
+    for k in range(4):
+        codes[rows, idx[:, k]] = 1 + rng.integers(0, 2, count)
+    codes = np.unique(codes, axis=0)
+    return binding.PauliSum(codes, np.ones(len(codes)))
+
+def dense(n, sites):  # every string on the middle sites
+    codes = np.zeros((4 ** sites, n), np.uint8)
+    codes[:, (n - sites) // 2:(n - sites) // 2 + sites] = np.array(np.unravel_index(np.arange(4 ** sites), (4,) * sites)).T
+    return binding.PauliSum(codes, np.ones(len(codes)))
+"""
+
+
+@pytest.mark.parametrize("n,D,count,prec,pairs", [(48, 32, 220000, "c128", False), (48, 32, 220000, "c64", True),
+                                                  (48, 32, 3000, "c128", True), (40, 64, 200000, "c128", False),
+                                                  (12, 32, 200, "c64", True), (16, 32, 8, "c128", False),
+                                                  (16, 128, 8, "c128", False), (18, 16, 9, "c64", False)])
+def test_closes_are_chosen_for_all_bonds_together(fake, n, D, count, prec, pairs):
+    """Sums whose bonds each have few tiles but together fill the chip (48 qubits
+    D = 32, 200,001 strings: 0.25 ms as tiles, 0.37 as pairs in c128, 0.34 and
+    0.17 in c64) are not split up as if every bond's tiles ran by themselves."""
+    r = fake(FULL + CLOSES + f"""
+m = state({n}, {D})
+m.canonicalize()
+plan = exchange({n}, {count}) if {count} > 99 else dense({n}, {count})
+m.expect(plan, "{prec}")
+print(json.dumps([fake.fake_blocks(b"gram_pairs"), fake.fake_blocks(b"GramTileP") + fake.fake_blocks(b"GramSplitP")]))
+""")
+    print(f"{n} qubits D = {D} {count} {prec}: {r[0]} pair groups, {r[1]} tile blocks")
+    assert (r[0] > 0) == pairs and (r[1] == 0) == pairs
