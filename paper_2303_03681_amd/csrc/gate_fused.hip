@@ -38,7 +38,15 @@ namespace {
 constexpr int FW = 8;      // waves per workgroup
 constexpr int FB = 8;      // rows per block
 constexpr int FMAXN = 128; // rows (2 D_l) and row length (2 D_r) limit
-constexpr int FPRE = 32 * 32;  // matrices of more elements are LQ-factorised before Algorithm 1
+// Matrices of more elements (or more than twice as many rows as columns) are
+// LQ-factorised before Algorithm 1.  A gate in us, factorised / directly, on random
+// matrices graded over six decades: 16 x 16 116 / 94, 16 x 32 117 / 84, 24 x 24 214 /
+// 192, 32 x 32 246 / 198, 64 x 64 503 / 455, but tall 32 x 16 150 / 204, 66 x 32 325 /
+// 1,004, 60 x 14 149 / 664.  On the matrices of a UCCSD chain, whose rows are closer to
+// parallel, it gains: 40 gates on 12 qubits D = 64 8.3 / 23.1 ms.  With the line at 512
+// elements that step of the program takes 9.2 instead of 8.8 ms and one on ten-qubit
+// fragments (32 x 32) 8.0 instead of 7.6.
+constexpr int FPRE = 32 * 32;
 
 // ---------------------------------------------------------------------------
 // Eight pairs at a time.  The 16 per-lane partial sums (Re and Im of x^+y of 8

@@ -260,7 +260,8 @@ hipError_t launch_copy(double2* dst, const double2* src, size_t count, hipStream
 hipError_t launch_fill_ident(double2* dst, int d, hipStream_t s);
 
 // environment products: c128 on FP64 MFMA, c64 on FP32 MFMA, with a choice of
-// workgroup tile shapes (BM, BN, BK); index 0 is the default
+// workgroup tile shapes (BM, BN, BK).  Index 0 is the default: env_gemm_kernel, whose
+// shape depends on type and size (launch_env_64) and which keeps its listed name
 constexpr int kEnvTiles = 8;
 constexpr int kEnvTileShape[kEnvTiles][3] = {{64, 64, 16},  {32, 32, 16},   {128, 64, 16}, {64, 128, 16},
                                              {64, 64, 32},  {32, 64, 16},   {128, 128, 16}, {128, 128, 8}};

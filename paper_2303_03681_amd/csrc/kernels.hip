@@ -1378,9 +1378,6 @@ struct EnvG2P {
   }
 };
 
-// One environment GEMM with tile shape kEnvTileShape[tile] (all shapes give
-// bitwise-identical results: every output element accumulates its K range in
-// the same order of 16x16x4 steps whatever the tile).
 // The address of a wave's operand as a scalar; load_g reads from memory at it.
 __device__ __forceinline__ size_t uniform_addr(const void* p) {
   const size_t v = (size_t)p;
@@ -1633,6 +1630,9 @@ hipError_t launch_env_64(const P& p, int count, int m, int n, hipStream_t s) {
   else return launch_env_gemm<64, 64, 16>(p, count, m, n, s);
 }
 
+// One environment GEMM with tile kEnvTileShape[tile] (all give bitwise-identical
+// results: every output element accumulates its K range in the same order of
+// 16x16x4 steps whatever the tile).
 template <class P>
 hipError_t launch_env_tile(const P& p, int tile, int count, int m, int n, hipStream_t s) {
   switch (tile) {
@@ -1733,9 +1733,15 @@ hipError_t launch_env_merged(const EnvMerged& m, int prec, hipStream_t s) {
 // A whole update L' = sum_s A^{s+} (phase X^{s^flip}), X = L [A^0 | A^1], of one
 // child per workgroup, X in LDS, operands straight from L2.  Small dims are
 // bound by launches and by the latency of a staged K loop (6 + 12 us for the
-// two GEMMs at D = 32); X is recomputed for every child of a parent, which
-// costs nothing while the launch has fewer children than the chip has
-// compute units.  Per element the same operations in the same order as
+// two GEMMs at D = 32).  X is recomputed for every child of a parent, which is
+// cheaper than a launch and a round trip of X up to dims of 32, whether the launch
+// has fewer children than the chip has compute units or fills it many times over,
+// and with up to four children per parent.  Whole expectations in c128 ms, the two
+// GEMMs / this kernel: 16 qubits D = 8, 16 strings 0.19 / 0.15, 20,000 (7,600
+// children a launch) 1.71 / 0.60; D = 32, 1,000 strings 0.63 / 0.34, 20,000 5.03 /
+// 2.38; every string on seven sites (three children per parent) 0.27 / 0.24.
+// Above: D = 48 0.25 / 0.34 (16 strings) and 8.18 / 7.81 (20,000), D = 64 0.27 / 0.47
+// and 11.3 / 20.5.  Per element the same operations in the same order as
 // cgemm_kernel on EnvG1P and EnvG2P.
 template <typename T>
 __global__ __launch_bounds__(256) void env_small_kernel(const EnvSeg* segs, int n_segs) {

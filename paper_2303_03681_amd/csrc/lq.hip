@@ -250,7 +250,7 @@ hipError_t launch_lq_e(const LqItem* items_dev, int items, int max_rows, hipStre
 
 // LQ factorisation of every matrix (max_rows x max_len the largest): rows
 // become Q in place (in processing order), the factor goes to r as L^+.
-// Blocks of 32 rows, 16 where a row takes 64 registers per lane.
+// Blocks of 16 rows (32 take 74 us a panel at 8 matrices of 512 columns, 16 take 27).
 hipError_t launch_lq(const LqItem* items_dev, int items, int max_rows, int max_len, hipStream_t s) {
   if (items <= 0 || max_rows <= 0 || max_len <= 0) return hipSuccess;
   if (max_len <= 128) return launch_lq_e<2, 8, 2, 4>(items_dev, items, max_rows, s);

@@ -40,7 +40,12 @@ constexpr int kMaxStatevectorQubits = 26;
 constexpr double kEpsScale = 1.1102230246251565e-16;  // 2^-53: eps = m * 2^-53 (Algorithm 1)
 constexpr double kCanonCutoff = 1e-14;                  // round-off singular values only
 constexpr int kDefaultSweeps = 60;
-constexpr int kPreMin = 32 * 32;  // batched SVDs of more elements are LQ-preconditioned
+// Batched SVDs of more elements are LQ-preconditioned.  The gates of a brickwork
+// layer on a saturated state in ms, so / directly: 24 qubits D = 64 4.7 / 7.8, 31
+// qubits D = 150 18.9 / 32.0, 36 qubits D = 256 37.6 / 62.3, 28 qubits D = 512 146 /
+// 257.  About even at the line (24 qubits D = 32 2.8 / 2.8, and D = 17 2.1 / 1.8);
+// from 512 elements on the D = 64 layer gains 1%.
+constexpr int kPreMin = 32 * 32;
 constexpr int kMaxBond = 512;                           // finalize handles 2D <= 1024 vectors
 constexpr int kMaxJacobiGroups = 3;      // streams of the batched register Jacobi rounds
 constexpr int kDefaultJacobiGroups = 2;
@@ -1941,7 +1946,7 @@ struct RowsSpec {
 // state and, where their GEMM1 outputs are apart, of both passes -- as merged
 // launches.
 constexpr int64_t kMergeTiles = 1024;  // 64 x 64 tiles of a launch that fills the chip
-constexpr int kEnvFused = 32;  // updates up to these dims run as one launch (launch_env_small)
+constexpr int kEnvFused = 32;  // updates up to these dims run as one launch (env_small_kernel has both sides)
 
 struct CallLists {
   std::vector<char> blob;
