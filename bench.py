@@ -38,9 +38,10 @@ if ROOT not in sys.path:
 PEAK_TFLOPS = {"c128": 78.6, "c64": 157.3, "split_bf16": 2500.0, "split_f16": 2500.0}
 SPLIT_PRODUCTS = 3  # 16-bit MFMA products per real FP32 multiply in the split precisions
 # HBM bytes per environment launch on this workload from two rocprofv3 --pmc passes
-# (FETCH_SIZE x 2.000, WRITE_SIZE x 1.000 by a 256 MiB copy), environment kernels
-# unchanged since; profiles/env_gemm_traffic_50q_D256.md has the commands and figures.
-ENV_TRAFFIC_BYTES = {"c64": 449.7e6, "c128": 916.6e6, "split_bf16": 428.8e6, "split_f16": 430.4e6}
+# (FETCH_SIZE x 2.000, WRITE_SIZE x 1.000 by a 256 MiB copy) over env_gemm_kernel (c128,
+# c64) and cgemm_split_kernel; profiles/env_gemm_traffic_50q_D256.md has the commands and
+# figures.
+ENV_TRAFFIC_BYTES = {"c64": 486.8e6, "c128": 996.8e6, "split_bf16": 429.2e6, "split_f16": 430.3e6}
 METRIC = "Pauli-string expectations/s at 50q D=256 vs complex128 path; p50/p99 latency"
 
 
@@ -291,8 +292,9 @@ def serving_sample(n_fragments: int, prec: str, n_updates: int = 1, qubits=(12, 
 
 
 def autotune_summary(binding, enabled):
-    """Tuned environment GEMM classes: how many, which tiles won, and the
-    summed time of the chosen tiles against the default tile."""
+    """Tuned environment GEMM classes: how many, which tiles won (by their listed
+    shapes; 64x64x16 is the default tile, whose own shape depends on the type),
+    and the summed time of the chosen tiles against the default tile."""
     rows = binding.autotune_table()
     hist = {}
     for r in rows:
@@ -323,7 +325,7 @@ def env_roofline(tm, prec):
         "algorithmic_tflops": rate,
         "traffic": ENV_TRAFFIC_BYTES.get(prec),
         "traffic_unit": "bytes per launch (HBM, scaled PMC FETCH_SIZE + WRITE_SIZE)",
-        "kernel": "cgemm_kernel<EnvG1P/EnvG2P> (transfer-matrix update)" if prec in ("c128", "c64")
+        "kernel": "env_gemm_kernel/cgemm_kernel<EnvG1P/EnvG2P> (transfer-matrix update)" if prec in ("c128", "c64")
         else "cgemm_split_kernel<EnvG1P/EnvG2P> (transfer-matrix update)",
         "flops_per_launch": tm["env_flops"] / max(1, tm["env_launches"]),
         "avg_launch_ms": tm["env_ms"] / max(1, tm["env_launches"]),
