@@ -150,7 +150,8 @@ struct mps_state {
   int device = 0;  // current device at create
   hipStream_t stream = nullptr;
   bool own_stream = false;
-  size_t budget = 0, held = 0;
+  size_t budget = 0;
+  std::atomic<size_t> held{0};  // changed under alloc_mutex
   bool poisoned = false;
   std::vector<int> dims, cap;
   std::vector<double2*> site[2];
@@ -888,12 +889,13 @@ struct GateRef {
 
 // Eqs. (C), (C~), (svd), (Bl) for gates on disjoint bonds, possibly of several
 // handles (whose streams are idle): one batched contraction, one batched
-// Jacobi SVD and one batched site update.  Counters, descriptors and launches
-// are the driver's (on its stream); each gate works in its own handle's
-// workspace.  Results go to spare buffers.  all_or_nothing: any failed gate
-// fails the call and nothing is committed (the single-handle contract);
-// otherwise the gates that succeeded are committed and err[b] / msg[b] report
-// the failed ones (their handles unchanged).
+// Jacobi SVD and one batched site update.  Counters and launches are the
+// driver's (on its stream), the descriptors too where it has room for those of
+// preconditioned gates; each gate works in its own handle's workspace.  Results
+// go to spare buffers.  all_or_nothing: any failed gate fails the call and
+// nothing is committed (the single-handle contract); otherwise the gates that
+// succeeded are committed and err[b] / msg[b] report the failed ones (their
+// handles unchanged).
 mps_status apply_2q_refs(mps_state* drv, const std::vector<GateRef>& g, bool all_or_nothing,
                          std::vector<mps_status>& err, std::vector<std::string>& msg) {
   const int items = (int)g.size();
